@@ -20,14 +20,21 @@ int dgemm(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, dou
           const double* A, int64_t lda, const double* B, int64_t ldb, double beta, double* C,
           int64_t ldc);
 
-int sgemm(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, float alpha,
-          const float* A, int64_t lda, const float* B, int64_t ldb, float beta, float* C,
-          int64_t ldc);
+// What a product of the network does with its sums before they are stored.
+enum { EPI_NONE = 0, EPI_BIAS = 1, EPI_DSILU = 2 };  // C = s, s + bias[n], s * silu'(Z[m][n])
+struct GemmEpi {
+    const float* bias = nullptr;  // EPI_BIAS: N values
+    const float* Z = nullptr;     // EPI_DSILU: M x N, rows ldc apart
+};
 
-// C = op(A) op(B) (no scaling, C overwritten) with the FP32 operands rounded
-// once to bfloat16 and products on the 16-bit matrix cores, FP32 sums.
-int bgemm(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
-          const float* B, int64_t ldb, float* C, int64_t ldc);
+// C = op(A) op(B) in FP32 (row-major, contraction in 4-deep matrix-core
+// steps), or, with bf16, the FP32 operands rounded once to bfloat16 and the
+// products on the 16-bit matrix cores (FP32 sums).  With kslab > 0 the
+// contraction is cut into slabs of kslab terms and slab s writes its own
+// product to C + s * M * ldc (epi must be EPI_NONE then).
+int net_gemm(hipStream_t st, bool bf16, bool ta, bool tb, int64_t M, int64_t N, int64_t K, const float* A,
+             int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int64_t kslab = 0,
+             int epi = EPI_NONE, GemmEpi e = GemmEpi());
 
 // out[t] = a_t . b_t for t < nd, summed in a fixed order (bitwise reproducible).
 // part needs dots_part_elems(nd) doubles.

@@ -174,69 +174,257 @@ __global__ __launch_bounds__(256, 2) void gemm_nn_wide(int64_t M, int64_t N, int
             }
 }
 
-// C = op(A) op(B) with FP32 operands rounded once to bfloat16 (RNE) as they
-// are staged, products on v_mfma_f32_16x16x32_bf16, FP32 accumulation and
-// output.  64 x 64 tile per workgroup, 2 x 2 waves of 32 x 32 (2 x 2 steps of
-// 16 x 16); K in chunks of 32, both operands held k-contiguous in LDS (row =
-// m or n, 32 bfloat16 + 8 of padding: 16-byte pieces of 16 consecutive rows
-// fall on distinct banks).
+// ---------------------------------------------------------------- network products
+// The FP32 and BF16 products of the perceptron: activations (n x hidden),
+// the input gradient and the weight gradient.  128 x 128 tile per workgroup,
+// 2 x 2 wavefronts of 64 x 64 (16 accumulator blocks of 16 x 16 each), the
+// contraction in chunks staged through registers into two LDS buffers.  The
+// products are bound by the FP32 matrix cores (256 x 256 weights: 64 flop per
+// byte of activation), so each operand element read from LDS is used four
+// times and the chunk loop holds nothing but loads, LDS moves and products.
+// The weight gradient contracts over the batch rows: its slabs are the third
+// grid dimension of ONE launch.  Measured at 65536 rows, 256 x 256 weights:
+// 32 launches of 16 workgroups each, on 64 x 64 tiles without prefetch, took
+// 10.9 ms; one launch of 4 x 128 workgroups takes 0.091 ms (94 TFLOP/s).
+//
+// Operand panels are kept as rows of the contraction index k.  FP32 rows are
+// 144 floats apart (16 modulo 64 banks, so the 4 rows of an operand read use
+// disjoint banks) and row k keeps column m at m ^ 16 (k / 4 % 4): a thread
+// that holds 4 consecutive k of one column (operand contiguous along k)
+// stores them to 4 rows without bank conflicts, and the reads, whose k / 4 is
+// the step number, only see their 16-column groups renumbered.
+constexpr int NT_M = 128, NT_K = 16, NT_P = NT_M + 16;
+
+// 4 consecutive floats from any float address; elements at or past lim are 0
+__device__ inline void load4(float (&v)[4], const float* __restrict__ p, int64_t lim) {
+    if (lim >= 4) {
+        __builtin_memcpy(v, p, 16);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = e < lim ? p[e] : 0.f;
+    }
+}
+
+__device__ inline float dsilu_f(float z) {
+    const float s = 1.f / (1.f + __expf(-z));
+    return s * (1.f + z * (1.f - s));
+}
+
+template <int EPI>
+__device__ __attribute__((always_inline)) inline void net_store(const v4f (&acc)[4][4], int64_t m0, int64_t n0, int wm, int wn, int lane,
+                                 int64_t M, int64_t N, float* __restrict__ C, int64_t ldc, const GemmEpi& e) {
+#pragma unroll
+    for (int tj = 0; tj < 4; ++tj) {
+        const int64_t gn = n0 + wn * 64 + tj * 16 + (lane & 15);
+        if (gn >= N) continue;
+        const float bias = EPI == EPI_BIAS ? e.bias[gn] : 0.f;
+#pragma unroll
+        for (int ti = 0; ti < 4; ++ti)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int64_t gm = m0 + wm * 64 + ti * 16 + 4 * (lane >> 4) + r;
+                if (gm >= M) continue;
+                float v = acc[ti][tj][r];
+                if (EPI == EPI_BIAS) v += bias;
+                if (EPI == EPI_DSILU) v *= dsilu_f(e.Z[gm * ldc + gn]);
+                C[gm * ldc + gn] = v;
+            }
+    }
+}
+
+// Tile and slab of this workgroup.  Workgroups go round-robin to the 8 XCDs;
+// those that read the same rows (the column tiles of 128 rows, or all tiles
+// of one slab) are numbered 8 apart, so one XCD's L2 fetches the rows once.
+__device__ inline bool net_tile(int64_t M, int64_t N, int64_t K, int64_t kslab, int64_t& m0, int64_t& n0,
+                                int64_t& slab) {
+    const int64_t nbn = cdiv(N, NT_M), nbm = cdiv(M, NT_M);
+    const int64_t inner = kslab ? nbm * nbn : nbn, q = blockIdx.x >> 3;
+    const int64_t unit = q / inner * 8 + (blockIdx.x & 7), t = q % inner;
+    n0 = t % nbn * NT_M;
+    m0 = (kslab ? t / nbn : unit) * NT_M;
+    slab = kslab ? unit : 0;
+    return unit < (kslab ? cdiv(K, kslab) : nbm);
+}
+
+template <bool TA, bool TB, int EPI>
+__global__ __launch_bounds__(256, 3) void sgemm_net(int64_t M, int64_t N, int64_t K, const float* __restrict__ A,
+                                                     int64_t lda, const float* __restrict__ B, int64_t ldb,
+                                                     float* __restrict__ C, int64_t ldc, int64_t kslab, GemmEpi e) {
+    __shared__ __attribute__((aligned(16))) float sA[2][NT_K][NT_P];
+    __shared__ __attribute__((aligned(16))) float sB[2][NT_K][NT_P];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    int64_t m0, n0, slab;
+    if (!net_tile(M, N, K, kslab, m0, n0, slab)) return;
+    const int64_t kbeg = slab * kslab;
+    const int64_t kend = kslab && kbeg + kslab < K ? kbeg + kslab : K;
+    // k-contiguous operand: thread holds k quad tid % 4 of rows tid / 4 and
+    // tid / 4 + 64; row-contiguous: quad tid % 32 of k rows tid / 32 and + 8
+    const int cr = tid >> 2, cq = 4 * (tid & 3), rr = tid >> 5, rq = 4 * (tid & 31);
+    float ra[2][4], rb[2][4];
+    auto load1 = [&](float (&v)[2][4], const float* __restrict__ S, int64_t ld, bool rows, int64_t lim, int64_t o0,
+                     int64_t k0) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (rows) {  // S[k][o]
+                const int64_t k = k0 + rr + 8 * j;
+                load4(v[j], S + k * ld + o0 + rq, k < kend ? lim - (o0 + rq) : 0);
+            } else {  // S[o][k]
+                const int64_t o = o0 + cr + 64 * j;
+                load4(v[j], S + o * ld + k0 + cq, o < lim ? kend - (k0 + cq) : 0);
+            }
+        }
+    };
+    auto store1 = [&](const float (&v)[2][4], float (*S)[NT_P], bool rows) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (rows) {
+                const int k = rr + 8 * j;
+                __builtin_memcpy(&S[k][rq ^ (16 * ((k >> 2) & 3))], v[j], 16);
+            } else {
+                const int o = (cr + 64 * j) ^ (16 * (cq >> 2));
+#pragma unroll
+                for (int d = 0; d < 4; ++d) S[cq + d][o] = v[j][d];
+            }
+        }
+    };
+    v4f acc[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
+    load1(ra, A, lda, TA, M, m0, kbeg);
+    load1(rb, B, ldb, !TB, N, n0, kbeg);
+    store1(ra, sA[0], TA);
+    store1(rb, sB[0], !TB);
+    __syncthreads();
+    int buf = 0;
+    for (int64_t k0 = kbeg; k0 < kend; k0 += NT_K, buf ^= 1) {
+        const bool more = k0 + NT_K < kend;
+        if (more) {
+            load1(ra, A, lda, TA, M, m0, k0 + NT_K);
+            load1(rb, B, ldb, !TB, N, n0, k0 + NT_K);
+        }
+#pragma unroll
+        for (int kk = 0; kk < NT_K / 4; ++kk) {
+            const int kr = kk * 4 + (lane >> 4);
+            float a[4], b[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                a[q] = sA[buf][kr][wm * 64 + (q ^ kk) * 16 + (lane & 15)];
+                b[q] = sB[buf][kr][wn * 64 + (q ^ kk) * 16 + (lane & 15)];
+            }
+#pragma unroll
+            for (int ti = 0; ti < 4; ++ti)
+#pragma unroll
+                for (int tj = 0; tj < 4; ++tj) acc[ti][tj] = Mma<float>::step(a[ti], b[tj], acc[ti][tj]);
+        }
+        if (more) {
+            store1(ra, sA[buf ^ 1], TA);
+            store1(rb, sB[buf ^ 1], !TB);
+        }
+        __syncthreads();
+    }
+    C += slab * M * ldc;
+    net_store<EPI>(acc, m0, n0, wm, wn, lane, M, N, C, ldc, e);
+}
+
+// BF16 form: the operands are rounded once to bfloat16 (RNE) as they are
+// staged; LDS rows are m (or n), 32 bfloat16 of k each, 8 of padding (16-byte
+// pieces of 16 consecutive rows fall on distinct banks); one 16 x 16 x 32
+// step per block and chunk.
 typedef __bf16 v8bf_d __attribute__((ext_vector_type(8)));
 typedef uint32_t u4_d __attribute__((ext_vector_type(4)));
 constexpr int BK = 32, BROW = BK + 8;
 
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void bgemm_kernel(int64_t M, int64_t N, int64_t K, const float* __restrict__ A,
+__device__ inline uint32_t pack_bf16(float lo, float hi) {
+    return (uint32_t)float_to_bf16_rne(lo) | ((uint32_t)float_to_bf16_rne(hi) << 16);
+}
+
+template <bool TA, bool TB, int EPI>
+__global__ __launch_bounds__(256, 2) void bgemm_net(int64_t M, int64_t N, int64_t K, const float* __restrict__ A,
                                                      int64_t lda, const float* __restrict__ B, int64_t ldb,
-                                                     float* __restrict__ C, int64_t ldc) {
-    __shared__ uint16_t sA[GT][BROW];  // sA[m][k] = bf16(op(A)[m][k])
-    __shared__ uint16_t sB[GT][BROW];  // sB[n][k] = bf16(op(B)[k][n])
+                                                     float* __restrict__ C, int64_t ldc, int64_t kslab, GemmEpi e) {
+    __shared__ __attribute__((aligned(16))) uint16_t sA[2][NT_M][BROW];
+    __shared__ __attribute__((aligned(16))) uint16_t sB[2][NT_M][BROW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int64_t m0 = (int64_t)blockIdx.y * GT, n0 = (int64_t)blockIdx.x * GT;
-    typedef float v4 __attribute__((ext_vector_type(4)));
-    v4 acc[2][2];
-    for (int a = 0; a < 2; ++a)
-        for (int b = 0; b < 2; ++b) acc[a][b] = v4{0.f, 0.f, 0.f, 0.f};
-    for (int64_t k0 = 0; k0 < K; k0 += BK) {
-        for (int e = tid; e < BK * GT; e += 256) {
-            // element (m, k) of op(A) and (n, k) of op(B); the mapping reads
-            // memory contiguously
-            int k, m;
-            if (TA) { k = e / GT; m = e % GT; } else { m = e / BK; k = e % BK; }
-            const int64_t gm = m0 + m, gk = k0 + k;
-            float v = 0.f;
-            if (gm < M && gk < K) v = TA ? A[gk * lda + gm] : A[gm * lda + gk];
-            sA[m][k] = float_to_bf16_rne(v);
-            int kb, n;
-            if (TB) { n = e / BK; kb = e % BK; } else { kb = e / GT; n = e % GT; }
-            const int64_t gn = n0 + n, gkb = k0 + kb;
-            float w = 0.f;
-            if (gn < N && gkb < K) w = TB ? B[gn * ldb + gkb] : B[gkb * ldb + gn];
-            sB[n][kb] = float_to_bf16_rne(w);
-        }
-        __syncthreads();
-        u4_d a[2], b[2];
-        for (int q = 0; q < 2; ++q) {
-            a[q] = *reinterpret_cast<const u4_d*>(&sA[wm * 32 + q * 16 + (lane & 15)][8 * (lane >> 4)]);
-            b[q] = *reinterpret_cast<const u4_d*>(&sB[wn * 32 + q * 16 + (lane & 15)][8 * (lane >> 4)]);
-        }
-        for (int ti = 0; ti < 2; ++ti)
-            for (int tj = 0; tj < 2; ++tj) {
-                v8bf_d av, bv;
-                __builtin_memcpy(&av, &a[ti], 16);
-                __builtin_memcpy(&bv, &b[tj], 16);
-                acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[ti][tj], 0, 0, 0);
+    int64_t m0, n0, slab;
+    if (!net_tile(M, N, K, kslab, m0, n0, slab)) return;
+    const int64_t kbeg = slab * kslab;
+    const int64_t kend = kslab && kbeg + kslab < K ? kbeg + kslab : K;
+    // k-contiguous operand: 8 k at 8 (tid % 4) of rows tid / 4 and + 64;
+    // row-contiguous: the k pair 2 (tid / 32) (and + 16) of columns 4 (tid % 32)
+    const int cr = tid >> 2, cq = 8 * (tid & 3), rr = 2 * (tid >> 5), rq = 4 * (tid & 31);
+    float ra[2][8], rb[2][8];
+    auto load1 = [&](float (&v)[2][8], const float* __restrict__ S, int64_t ld, bool rows, int64_t lim, int64_t o0,
+                     int64_t k0) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int d = 0; d < 2; ++d) {
+                float w[4];
+                if (rows) {
+                    const int64_t k = k0 + rr + 16 * j + d;
+                    load4(w, S + k * ld + o0 + rq, k < kend ? lim - (o0 + rq) : 0);
+                } else {
+                    const int64_t o = o0 + cr + 64 * j, k = k0 + cq + 4 * d;
+                    load4(w, S + o * ld + k, o < lim ? kend - k : 0);
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[j][4 * d + q] = w[q];
             }
+    };
+    auto store1 = [&](const float (&v)[2][8], uint16_t (*S)[BROW], bool rows) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (rows) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<uint32_t*>(&S[rq + q][rr + 16 * j]) = pack_bf16(v[j][q], v[j][4 + q]);
+            } else {
+                const u4_d w = u4_d{pack_bf16(v[j][0], v[j][1]), pack_bf16(v[j][2], v[j][3]),
+                                    pack_bf16(v[j][4], v[j][5]), pack_bf16(v[j][6], v[j][7])};
+                *reinterpret_cast<u4_d*>(&S[cr + 64 * j][cq]) = w;
+            }
+        }
+    };
+    v4f acc[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
+    load1(ra, A, lda, TA, M, m0, kbeg);
+    load1(rb, B, ldb, !TB, N, n0, kbeg);
+    store1(ra, sA[0], TA);
+    store1(rb, sB[0], !TB);
+    __syncthreads();
+    int buf = 0;
+    for (int64_t k0 = kbeg; k0 < kend; k0 += BK, buf ^= 1) {
+        const bool more = k0 + BK < kend;
+        if (more) {
+            load1(ra, A, lda, TA, M, m0, k0 + BK);
+            load1(rb, B, ldb, !TB, N, n0, k0 + BK);
+        }
+        v8bf_d a[4], b[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            __builtin_memcpy(&a[q], &sA[buf][wm * 64 + q * 16 + (lane & 15)][8 * (lane >> 4)], 16);
+            __builtin_memcpy(&b[q], &sB[buf][wn * 64 + q * 16 + (lane & 15)][8 * (lane >> 4)], 16);
+        }
+#pragma unroll
+        for (int ti = 0; ti < 4; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < 4; ++tj)
+                acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ti], b[tj], acc[ti][tj], 0, 0, 0);
+        if (more) {
+            store1(ra, sA[buf ^ 1], TA);
+            store1(rb, sB[buf ^ 1], !TB);
+        }
         __syncthreads();
     }
-    // result row 4 (lane / 16) + r, column lane % 16 of each 16 x 16 block
-    for (int ti = 0; ti < 2; ++ti)
-        for (int tj = 0; tj < 2; ++tj)
-            for (int r = 0; r < 4; ++r) {
-                const int64_t gm = m0 + wm * 32 + ti * 16 + 4 * (lane >> 4) + r;
-                const int64_t gn = n0 + wn * 32 + tj * 16 + (lane & 15);
-                if (gm < M && gn < N) C[gm * ldc + gn] = acc[ti][tj][r];
-            }
+    C += slab * M * ldc;
+    net_store<EPI>(acc, m0, n0, wm, wn, lane, M, N, C, ldc, e);
 }
 
 // ---------------------------------------------------------------- reductions
@@ -460,22 +648,6 @@ __global__ void set_identity(double* __restrict__ V, int n) {
 
 }  // namespace
 
-template <typename T>
-int gemm_t(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, T alpha, const T* A,
-           int64_t lda, const T* B, int64_t ldb, T beta, T* C, int64_t ldc) {
-    const dim3 grid((unsigned)cdiv(N, GT), (unsigned)cdiv(M, GT));
-    if (!ta && !tb)
-        gemm_kernel<T, false, false><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-    else if (ta && !tb)
-        gemm_kernel<T, true, false><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-    else if (!ta && tb)
-        gemm_kernel<T, false, true><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-    else
-        gemm_kernel<T, true, true><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-    DFJK_LAUNCH_CHECK("gemm_kernel");
-    return DFJK_OK;
-}
-
 int dgemm(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha,
           const double* A, int64_t lda, const double* B, int64_t ldb, double beta, double* C,
           int64_t ldc) {
@@ -490,23 +662,45 @@ int dgemm(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, dou
         DFJK_LAUNCH_CHECK("gemm_nn_wide");
         return DFJK_OK;
     }
-    return gemm_t<double>(st, ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-}
-
-int sgemm(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, float alpha,
-          const float* A, int64_t lda, const float* B, int64_t ldb, float beta, float* C,
-          int64_t ldc) {
-    return gemm_t<float>(st, ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-}
-
-int bgemm(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
-          const float* B, int64_t ldb, float* C, int64_t ldc) {
     const dim3 grid((unsigned)cdiv(N, GT), (unsigned)cdiv(M, GT));
-    if (!ta && !tb) bgemm_kernel<false, false><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc);
-    else if (ta && !tb) bgemm_kernel<true, false><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc);
-    else if (!ta && tb) bgemm_kernel<false, true><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc);
-    else bgemm_kernel<true, true><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc);
-    DFJK_LAUNCH_CHECK("bgemm_kernel");
+    if (!ta && !tb)
+        gemm_kernel<double, false, false><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
+    else if (ta && !tb)
+        gemm_kernel<double, true, false><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
+    else if (!ta && tb)
+        gemm_kernel<double, false, true><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
+    else
+        gemm_kernel<double, true, true><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
+    DFJK_LAUNCH_CHECK("gemm_kernel");
+    return DFJK_OK;
+}
+
+template <bool TA, bool TB, int EPI>
+void launch_net(hipStream_t st, bool bf16, dim3 grid, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
+                const float* B, int64_t ldb, float* C, int64_t ldc, int64_t kslab, const GemmEpi& e) {
+    if (bf16)
+        bgemm_net<TA, TB, EPI><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
+    else
+        sgemm_net<TA, TB, EPI><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
+}
+
+int net_gemm(hipStream_t st, bool bf16, bool ta, bool tb, int64_t M, int64_t N, int64_t K, const float* A,
+             int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int64_t kslab, int epi, GemmEpi e) {
+    const int64_t nbn = cdiv(N, NT_M), nbm = cdiv(M, NT_M);
+    const int64_t units = kslab ? cdiv(K, kslab) : nbm, inner = kslab ? nbm * nbn : nbn;
+    const dim3 grid((unsigned)(cdiv(units, 8) * 8 * inner));
+    // the three forms the network uses
+    if (!ta && tb && epi == EPI_BIAS)
+        launch_net<false, true, EPI_BIAS>(st, bf16, grid, M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
+    else if (!ta && !tb && epi == EPI_DSILU)
+        launch_net<false, false, EPI_DSILU>(st, bf16, grid, M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
+    else if (ta && !tb && epi == EPI_NONE)
+        launch_net<true, false, EPI_NONE>(st, bf16, grid, M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
+    else {
+        set_error("net_gemm: form not provided");
+        return DFJK_E_INVALID;
+    }
+    DFJK_LAUNCH_CHECK("net_gemm");
     return DFJK_OK;
 }
 
