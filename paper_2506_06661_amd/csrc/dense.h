@@ -41,20 +41,35 @@ int net_gemm(hipStream_t st, bool bf16, bool ta, bool tb, int64_t M, int64_t N, 
 int dots(hipStream_t st, const DotList& list, int nd, int64_t n, double* part, double* out);
 size_t dots_part_elems(int nd);
 
-// Symmetric eigendecomposition by parallel cyclic Jacobi in one workgroup.
-// A (n x n) is overwritten; V (n x n) holds a basis as ROWS (set to the
-// identity first when v_identity): on entry A must be expressed in that basis
-// (A = V F V^T); on exit row k of V is the eigenvector of F with eigenvalue
-// A[k][k].
-// work: >= n + 2 doubles; iwork: >= n + 2 ints (iwork[0] = sweeps used,
-// iwork[1 + r] = index of the r-th smallest eigenvalue); w: n eigenvalues in
-// ascending order.
-int eigh(hipStream_t st, double* A, double* V, int n, bool v_identity, double* work, int* iwork,
-         double* w);
+// Workspace of the eigensolver for n x n matrices, carved from one buffer.
+constexpr int kEigLdsN = 198;       // largest n solved in LDS (eigen.hip)
+constexpr int kEigMaxSweeps = 40;   // the log of rotations holds them all
+struct EigWork {
+    double* A;    // n x n (larger n only)
+    double* work; // n + 2 (larger n only)
+    double* log;  // log_elems(n): rotations to apply to the eigenvectors
+    int* iwork;   // iwork_elems(n): sweeps, index of each rank, rank of each index, ...
+    double* w;    // n eigenvalues in ascending order
+    __host__ __device__ static int rank_at(int n) { return n + 2; }
+    __host__ __device__ static int rounds_at(int n) { return 2 * n + 2; }
+    static size_t iwork_elems(int64_t n) { return 2 * (size_t)n + 3; }
+    static size_t log_elems(int64_t n) {
+        const int64_t h = (n + 1) / 2;
+        return n <= kEigLdsN ? (size_t)(2 * kEigMaxSweeps * (2 * h - 1) * h) : 0;
+    }
+};
 
-// out (n x ncol) = eigenvector columns of the ncol smallest eigenvalues; mode 1
-// scales column c by sqrt|w_c| and writes sign(w_c) to sign.
-int eig_gather(hipStream_t st, const double* V, int n, const int* iwork, int ncol, const double* w,
-               int mode, double* out, double* sign);
+// Eigendecomposition of F = (X + X^T) / 2 by cyclic Jacobi.  V (n x n) holds a
+// basis as ROWS: on entry X must be expressed in that basis (X = V F V^T; with
+// v_identity V is taken as the identity and need not be set), on exit row k of
+// V is an eigenvector of F.  out (n x ncol) = eigenvector columns of the ncol
+// smallest eigenvalues; mode 1 scales column c by sqrt|w_c| and writes
+// sign(w_c) to sign.
+int eigh_cols(hipStream_t st, const double* X, double* V, int n, bool v_identity, const EigWork& ws, int ncol,
+              int mode, double* out, double* sign);
+
+// The form for n <= kEigLdsN (eigen.hip).
+int eig_lds(hipStream_t st, const double* X, double* V, int n, bool v_identity, const EigWork& ws, int ncol,
+            int mode, double* out, double* sign);
 
 }  // namespace dfjk

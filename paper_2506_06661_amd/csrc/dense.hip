@@ -1,6 +1,6 @@
 // Dense FP64 helpers for the SCF step and the density path of K:
 // a general matrix product on the FP64 matrix cores, deterministic
-// reductions, and a one-workgroup parallel cyclic Jacobi eigensolver.
+// reductions, and the eigensolver for matrices too large for LDS.
 #include "dense.h"
 
 #include "mma.h"
@@ -459,7 +459,8 @@ __global__ void dots_finish(const double* __restrict__ part, int nd, double* __r
 }
 
 // ---------------------------------------------------------------- Jacobi
-// Parallel cyclic Jacobi on a symmetric n x n matrix A (overwritten; the
+// n > kEigLdsN (smaller matrices: eigen.hip).
+// Parallel cyclic Jacobi in one workgroup on a symmetric n x n matrix A (overwritten; the
 // eigenvalues end on its diagonal).  Vt (n x n) holds the basis as ROWS: it
 // starts as the caller's basis (rows orthonormal) and its row k ends as the
 // eigenvector of diagonal entry k.  Each sweep visits every pair (p,q) once in
@@ -472,7 +473,6 @@ __global__ void dots_finish(const double* __restrict__ part, int nd, double* __r
 // A[{p,q}][{a,b}], so one thread updates each such block in place and a round
 // needs a single barrier.
 constexpr int JT = 1024;
-constexpr int kJacobiShN = 128;  // A in LDS up to 128 x 128 doubles (128 KB)
 
 __device__ inline void pair_of(int r, int k, int m, int& p, int& q) {
     // circle method on m (even) players; player m-1 fixed
@@ -496,18 +496,11 @@ __device__ inline void rot(double c, double s, double xp, double xq, double& yp,
     yq = s * xp + c * xq;
 }
 
-template <bool SH>
-__global__ __launch_bounds__(JT) void jacobi_kernel(double* __restrict__ Ag, double* __restrict__ Vt,
+__global__ __launch_bounds__(JT) void jacobi_kernel(double* __restrict__ A, double* __restrict__ Vt,
                                                      int n, double* __restrict__ cs, int max_sweeps,
                                                      double tol, int* __restrict__ sweeps_done) {
-    extern __shared__ double smem[];
     __shared__ double red[JT / 64];
     __shared__ int stop;
-    double* __restrict__ A = SH ? smem : Ag;
-    if (SH) {
-        for (int64_t e = threadIdx.x; e < (int64_t)n * n; e += JT) A[e] = Ag[e];
-        __syncthreads();
-    }
     const int m = n + (n & 1);
     const int half = m / 2;
     double* cc = cs;
@@ -607,9 +600,6 @@ __global__ __launch_bounds__(JT) void jacobi_kernel(double* __restrict__ Ag, dou
             __syncthreads();
         }
     }
-    if (SH) {
-        for (int64_t e = threadIdx.x; e < (int64_t)n * n; e += JT) Ag[e] = A[e];
-    }
     if (threadIdx.x == 0) *sweeps_done = sweep;
 }
 
@@ -644,6 +634,14 @@ __global__ void gather_cols(const double* __restrict__ Vt, int n, const int* __r
 __global__ void set_identity(double* __restrict__ V, int n) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e < (int64_t)n * n) V[e] = (e / n == e % n) ? 1.0 : 0.0;
+}
+
+// Y = (X + X^T) / 2
+__global__ void symmetrize(const double* __restrict__ X, int64_t n, double* __restrict__ Y) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n * n) return;
+    const int64_t r = i / n, c = i % n;
+    Y[i] = 0.5 * (X[r * n + c] + X[c * n + r]);
 }
 
 }  // namespace
@@ -718,43 +716,30 @@ int dots(hipStream_t st, const DotList& list, int nd, int64_t n, double* part, d
 
 size_t dots_part_elems(int nd) { return (size_t)nd * RBLK; }
 
-int eigh(hipStream_t st, double* A, double* V, int n, bool v_identity, double* work, int* iwork,
-         double* w) {
+int eigh_cols(hipStream_t st, const double* X, double* V, int n, bool v_identity, const EigWork& ws, int ncol,
+              int mode, double* out, double* sign) {
     if (n < 1 || n > kMaxEighN) {
-        set_error("eigh: n=%d outside [1, %d]", n, kMaxEighN);
+        set_error("eigensolver: n=%d outside [1, %d]", n, kMaxEighN);
         return DFJK_E_INVALID;
     }
+    if (n <= kEigLdsN) return eig_lds(st, X, V, n, v_identity, ws, ncol, mode, out, sign);
+    const unsigned g2 = (unsigned)cdiv((int64_t)n * n, 256);
+    symmetrize<<<g2, 256, 0, st>>>(X, n, ws.A);
+    DFJK_LAUNCH_CHECK("symmetrize");
     if (v_identity) {
-        set_identity<<<dim3((unsigned)cdiv((int64_t)n * n, 256)), 256, 0, st>>>(V, n);
+        set_identity<<<g2, 256, 0, st>>>(V, n);
         DFJK_LAUNCH_CHECK("set_identity");
     }
     // stop when the off-diagonal norm is below 1e-13 of the matrix norm
     // (convergence is quadratic, so the sweep after reaching ~1e-7 lands at
     // the rounding floor; a bound at n*eps can sit below that floor and is
     // then never met)
-    if (n <= kJacobiShN) {
-        const size_t bytes = sizeof(double) * (size_t)n * n;
-        static bool attr_set = false;
-        if (!attr_set) {
-            DFJK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&jacobi_kernel<true>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)(sizeof(double) * kJacobiShN * kJacobiShN)));
-            attr_set = true;
-        }
-        jacobi_kernel<true><<<1, JT, bytes, st>>>(A, V, n, work, 40, 1e-13, iwork);
-    } else {
-        jacobi_kernel<false><<<1, JT, 0, st>>>(A, V, n, work, 40, 1e-13, iwork);
-    }
+    jacobi_kernel<<<1, JT, 0, st>>>(ws.A, V, n, ws.work, 40, 1e-13, ws.iwork);
     DFJK_LAUNCH_CHECK("jacobi_kernel");
-    eig_rank<<<dim3((unsigned)cdiv(n, 256)), 256, 0, st>>>(A, n, iwork + 1, w);
+    eig_rank<<<dim3((unsigned)cdiv(n, 256)), 256, 0, st>>>(ws.A, n, ws.iwork + 1, ws.w);
     DFJK_LAUNCH_CHECK("eig_rank");
-    return DFJK_OK;
-}
-
-int eig_gather(hipStream_t st, const double* V, int n, const int* iwork, int ncol, const double* w,
-               int mode, double* out, double* sign) {
-    gather_cols<<<dim3((unsigned)cdiv((int64_t)n * ncol, 256)), 256, 0, st>>>(V, n, iwork + 1, ncol, w,
-                                                                               mode, out, sign);
+    gather_cols<<<dim3((unsigned)cdiv((int64_t)n * ncol, 256)), 256, 0, st>>>(V, n, ws.iwork + 1, ncol, ws.w, mode,
+                                                                               out, sign);
     DFJK_LAUNCH_CHECK("gather_cols");
     return DFJK_OK;
 }

@@ -220,8 +220,8 @@ __global__ void scf_record(const double* __restrict__ en, const double* __restri
 
 // Workspace carved from h->eig: see scf_ws().
 struct ScfWs {
-    double *A, *V, *w, *work, *Cf, *sign;  // eigen-work (also used by the D path of K)
-    int* iwork;
+    EigWork eig;                           // eigen-work (also used by the D path of K)
+    double *V, *Cf, *sign;
     double *J, *K, *F, *G, *Fx;            // SCF matrices
     double *Fh, *Eh;                       // DIIS history: space x n^2 each
     double *gram, *coef, *dotv, *part, *en, *e_prev, *diis_first;
@@ -238,7 +238,7 @@ static int scf_ws(dfjk_ctx* h, bool scf, ScfWs& ws) {
         return off;
     };
     const size_t oA = take(n2), oV = take(n2), ow = take(n), owork = take(n + 2), oCf = take(n2),
-                 osign = take(n), oiw = take((n + 2 + 1) / 2);
+                 osign = take(n), oiw = take((EigWork::iwork_elems(n) + 1) / 2), olog = take(EigWork::log_elems(n));
     size_t oJ = 0, oK = 0, oF = 0, oG = 0, oFx = 0, oFh = 0, oEh = 0, ogr = 0, oco = 0, odv = 0,
            opart = 0, oen = 0, oep = 0, orec = 0, ofirst = 0;
     if (scf) {
@@ -252,13 +252,10 @@ static int scf_ws(dfjk_ctx* h, bool scf, ScfWs& ws) {
     int rc = h->eig.ensure(need * sizeof(double));
     if (rc) return rc;
     double* base = static_cast<double*>(h->eig.ptr);
-    ws.A = base + oA;
+    ws.eig = EigWork{base + oA, base + owork, base + olog, reinterpret_cast<int*>(base + oiw), base + ow};
     ws.V = base + oV;
-    ws.w = base + ow;
-    ws.work = base + owork;
     ws.Cf = base + oCf;
     ws.sign = base + osign;
-    ws.iwork = reinterpret_cast<int*>(base + oiw);
     if (scf) {
         ws.J = base + oJ;
         ws.K = base + oK;
@@ -295,20 +292,19 @@ int k_build_from_D(dfjk_ctx* h, const double* D, double* K) {
     int rc = scf_ws(h, h->scf_ready, ws);
     if (rc) return rc;
     const hipStream_t st = h->stream;
-    symmetrize_kernel<<<dim3((unsigned)cdiv(n * n, 256)), 256, 0, st>>>(D, n, ws.A);
-    DFJK_LAUNCH_CHECK("symmetrize_kernel");
     if (n >= kPairFromD && h->opts.max_ncol == 0) {
         // K = 1/2 sum_P [(B_P D)(B_P I)^T + (B_P I)(B_P D)^T]: two factors of
         // nao columns each, no eigensolver (whose one-workgroup sweeps take
         // seconds from nao ~ 500 on); a reserved workspace (at most nao
         // columns) keeps the eigen-factor path, which fits it
+        symmetrize_kernel<<<dim3((unsigned)cdiv(n * n, 256)), 256, 0, st>>>(D, n, ws.eig.A);
+        DFJK_LAUNCH_CHECK("symmetrize_kernel");
         identity_kernel<<<dim3((unsigned)cdiv(n * n, 256)), 256, 0, st>>>(n, ws.V);
         DFJK_LAUNCH_CHECK("identity_kernel");
-        return k_build_pair(h, ws.A, ws.V, n, 1, 0.5, K);
+        return k_build_pair(h, ws.eig.A, ws.V, n, 1, 0.5, K);
     }
-    if ((rc = eigh(st, ws.A, ws.V, (int)n, true, ws.work, ws.iwork, ws.w))) return rc;
     // D = sum_c w_c v_c v_c^T = sum_c sign_c (sqrt|w_c| v_c)(sqrt|w_c| v_c)^T
-    if ((rc = eig_gather(st, ws.V, (int)n, ws.iwork, (int)n, ws.w, 1, ws.Cf, ws.sign))) return rc;
+    if ((rc = eigh_cols(st, D, ws.V, (int)n, true, ws.eig, (int)n, 1, ws.Cf, ws.sign))) return rc;
     return k_build_factored(h, ws.Cf, n, ws.sign, 1.0, K);
 }
 
@@ -323,10 +319,7 @@ int aufbau(dfjk_ctx* h, const double* F, int64_t nocc, double* C, double* D) {
     int rc = scf_ws(h, h->scf_ready, ws);
     if (rc) return rc;
     const hipStream_t st = h->stream;
-    symmetrize_kernel<<<dim3((unsigned)cdiv(n * n, 256)), 256, 0, st>>>(F, n, ws.A);
-    DFJK_LAUNCH_CHECK("symmetrize_kernel");
-    if ((rc = eigh(st, ws.A, ws.V, (int)n, true, ws.work, ws.iwork, ws.w))) return rc;
-    if ((rc = eig_gather(st, ws.V, (int)n, ws.iwork, (int)nocc, ws.w, 0, C, nullptr))) return rc;
+    if ((rc = eigh_cols(st, F, ws.V, (int)n, true, ws.eig, (int)nocc, 0, C, nullptr))) return rc;
     if (D) return dgemm(st, false, true, n, n, nocc, 2.0, C, nocc, C, nocc, 0.0, D, n);
     return DFJK_OK;
 }
@@ -439,11 +432,8 @@ int scf_tail(dfjk_ctx* h, const double* H, double* D, double* C, int64_t nocc, c
         if ((rc = dgemm(st, false, true, n, n, n, 1.0, ws.Fx, n, ws.V, n, 0.0, ws.G, n))) return rc;
         if ((rc = dgemm(st, false, false, n, n, n, 1.0, ws.V, n, ws.G, n, 0.0, ws.Fx, n))) return rc;
     }
-    symmetrize_kernel<<<g2, 256, 0, st>>>(ws.Fx, n, ws.A);
-    DFJK_LAUNCH_CHECK("symmetrize_kernel");
-    if ((rc = eigh(st, ws.A, ws.V, (int)n, !warm, ws.work, ws.iwork, ws.w))) return rc;
+    if ((rc = eigh_cols(st, ws.Fx, ws.V, (int)n, !warm, ws.eig, (int)nocc, 0, C, nullptr))) return rc;
     h->scf_v_warm = true;
-    if ((rc = eig_gather(st, ws.V, (int)n, ws.iwork, (int)nocc, ws.w, 0, C, nullptr))) return rc;
     if ((rc = dgemm(st, false, true, n, n, nocc, 2.0, C, nocc, C, nocc, 0.0, D, n))) return rc;
 
     h->scf_iter = iter;
