@@ -50,216 +50,180 @@ __device__ inline float to_compute<float, _Float16>(_Float16 x) {
     return (float)x;
 }
 
+// Keeps a branch that is rarely taken a branch: without it the compiler turns
+// the zeroing of a last, partial chunk into selects on every chunk.
+__device__ inline void rare_path() { asm volatile("" ::: "memory"); }
+
 // ---------------------------------------------------------------- GEMM1
 // Workgroup tile: BI = 16*NI rows i (all waves) x BM = 64*WM columns mu
 // (each of the 4 waves owns 16*WM columns).  Per 16-deep nu chunk each thread
-// stages its share of C (VC consecutive orbitals of a row per load) and of
-// B_P (VB consecutive elements of a packed row per load: along nu below the
-// diagonal, along mu above it) in registers, then LDS.  VC = VB = 1 is one
-// element per load; the wider forms use 16-byte loads of C where its rows
-// are 16-byte aligned and loads of up to 16 bytes of B at any alignment (the
-// GPU's global loads take unaligned addresses), with element loads at the
-// edges (past ncol or nao).
+// stages 16 bytes of C per load (VC orbitals of a row) and up to 16 bytes of
+// B_P (VB consecutive elements of a packed row: along nu below the diagonal,
+// along mu above it; the GPU's global loads take unaligned addresses) in
+// registers, then LDS.
 //
-// Address arithmetic is incremental: a thread's C elements and its
-// below-diagonal B elements (packed row mu, column nu) advance by a constant
-// per chunk; its above-diagonal B elements (packed row nu, column mu) follow
-// the triangular row starts T(nu + 16) = T(nu) + 16 nu + 136.
-template <typename T, int NI, int VC>
-struct G1C {
-    static constexpr int V = VC;                  // orbitals per load
-    static constexpr int VPR = 16 * NI / V;       // loads per row of the C tile
+// The products of a chunk keep the matrix cores busy for 64 (FP64) or 32 (FP32)
+// cycles a step, so what costs is the vector work around them: an FP64 (7,1)
+// chunk is 1792 cycles of products, and 64-bit addresses, bounds and selects of
+// every element took longer than that.  So every address is a uniform base that
+// advances in scalar registers plus a 32-bit thread offset that stays the same
+// (C, and B below the diagonal) or takes one multiply-add (B above it: packed
+// row T(nu0 + k) = T(nu0) + k nu0 + k(k+1)/2).  Columns past the operands are
+// clamped to valid ones (their products are never stored); rows nu past nao are
+// zeroed, in the last chunk only.  A chunk's loads are issued when the chunk
+// before it has been stored to LDS, a whole chunk of products before they are
+// used.  nao=1024, naux=4096, nocc=200, FP64: 35.1 -> 31.6 ms (matrix cores 74-79%
+// busy at 2.2 GHz; the chip is at its power limit); nao=701, FP32: 5.37 -> 4.57.
+template <typename T, typename TS, int NI, int WM>
+struct G1 {
+    static constexpr int VC = 16 / sizeof(T);     // orbitals per load
+    static constexpr int VPR = 16 * NI / VC;      // loads per row of the C tile
     static constexpr int NV = KC * VPR;           // loads per chunk
-    static constexpr int NCV = (NV + kThreads - 1) / kThreads;  // per thread
-};
-
-// B elements per load: with wide C staging, 16 bytes' worth, at most the
-// 4*WM elements a thread stages per chunk
-template <typename TS, int WM, int VC>
-constexpr int g1_vb() {
-    return VC == 1 ? 1 : (4 * WM < (int)(16 / sizeof(TS)) ? 4 * WM : (int)(16 / sizeof(TS)));
-}
-
-template <int WM, int VB>
-struct G1B {
+    static constexpr int NC = (NV + kThreads - 1) / kThreads;  // per thread
+    static constexpr int VB = 4 * WM < (int)(16 / sizeof(TS)) ? 4 * WM : (int)(16 / sizeof(TS));  // B elements per load
     static constexpr int NP = 4 * WM / VB;        // loads per thread per chunk
     static constexpr int TLO = KC / VB;           // below: threads per packed row mu
     static constexpr int RLO = kThreads / TLO;    // below: rows mu per pass
     static constexpr int TUP = 64 * WM / VB;      // above: threads per packed row nu
     static constexpr int RUP = kThreads / TUP;    // above: rows nu per pass
-};
+    // LDS rows are nu; an operand read covers 16 consecutive columns of 4 rows.
+    // FP32: row pitches of 16 or 48 modulo 64 words put the four rows on
+    // disjoint banks; FP64 (two rows per 256 bytes): 16 modulo 32 elements.
+    static constexpr int G = sizeof(T) == 4 ? 64 : 32;
+    static constexpr int PC = (16 * NI) % G % 32 == 16 ? 16 * NI : 16 * NI + 16;
+    static constexpr int PB = 64 * WM + 16;
+    // B below the diagonal is written transposed (VB rows from one thread), so
+    // row k keeps column m at m ^ swz(k): the rows one store covers fall on
+    // different banks.  FP32 moves whole groups of 16 columns (k / 4 is the
+    // step number of a read); FP64 permutes pairs inside a group.
+    __device__ static int swz(int k) { return sizeof(T) == 4 ? 16 * ((k >> 2) & 3) : 2 * ((k >> 1) & 7); }
 
-template <typename T, int NI, int WM, int VC, int VB>
-struct G1Stage {
-    T b[G1B<WM, VB>::NP][VB];
-    T c[G1C<T, NI, VC>::NCV][VC];
-};
+    T c[NC][VC];
+    TS b[NP][VB];
+    uint32_t coff[NC];   // C: k * ldc + column
+    uint32_t loff[NP];   // B below: T(mu) - T(mu0) + k
+    uint32_t ucon[NP];   // B above: k(k+1)/2 + column
+    int phase;           // of the chunk in b: 0 below, 1 crossing, 2 above the diagonal
+    int klive;           // rows of the chunk below nao
 
-template <typename T, int NI, int WM, int VC, int VB>
-struct G1Addr {
-    int64_t c_off[G1C<T, NI, VC>::NCV];  // offset of C[nu0 + k][i] for the current chunk
-    int c_lim[G1C<T, NI, VC>::NCV];      // orbitals below ncol among the VC (0 for no load)
-    int64_t lo_off[G1B<WM, VB>::NP];     // below-diagonal: mu(mu+1)/2 + nu0 + k
-    int64_t up_row[G1B<WM, VB>::NP];     // above-diagonal: T(nu0 + k)
-    bool mu_ok_lo[G1B<WM, VB>::NP];
-    int up_lim;                          // above: columns mu below nao among the VB
-};
-
-template <typename T, int NI, int WM, int VC, int VB>
-__device__ inline void g1_addr_init(G1Addr<T, NI, WM, VC, VB>& ad, int64_t nao, int64_t ldc, int64_t ncol,
-                                    int64_t mu0, int64_t i0, int tid) {
-    using G = G1C<T, NI, VC>;
-    using GB = G1B<WM, VB>;
+    __device__ inline void init(int nao, int ldc, int mu0, int i0, int tid) {
 #pragma unroll
-    for (int j = 0; j < G::NCV; ++j) {
-        const int e = tid + j * kThreads;
-        const int k = e / G::VPR, ii = (e % G::VPR) * G::V;
-        const int64_t lim = ncol - (i0 + ii);
-        ad.c_off[j] = (int64_t)k * ldc + i0 + ii;
-        ad.c_lim[j] = e < G::NV ? (int)(lim < 0 ? 0 : lim > G::V ? G::V : lim) : 0;
+        for (int j = 0; j < NC; ++j) {
+            const int e = tid + j * kThreads;
+            const int k = e < NV ? e / VPR : 0, ii = (e % VPR) * VC;
+            coff[j] = (uint32_t)(k * ldc + min(i0 + ii, ldc - VC));
+        }
+        const uint32_t t0 = (uint32_t)mu0 * (uint32_t)(mu0 + 1) / 2;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const uint32_t mu = (uint32_t)min(mu0 + tid / TLO + RLO * j, nao - 1);
+            loff[j] = mu * (mu + 1) / 2 - t0 + (tid % TLO) * VB;
+            const int k = tid / TUP + RUP * j;
+            ucon[j] = (uint32_t)(k * (k + 1) / 2 + (tid % TUP) * VB);
+        }
     }
-#pragma unroll
-    for (int j = 0; j < GB::NP; ++j) {
-        const int64_t mu = mu0 + tid / GB::TLO + GB::RLO * j;
-        ad.lo_off[j] = mu * (mu + 1) / 2 + (tid % GB::TLO) * VB;
-        ad.mu_ok_lo[j] = mu < nao;
-        const int64_t nu = tid / GB::TUP + GB::RUP * j;
-        ad.up_row[j] = nu * (nu + 1) / 2;
-    }
-    const int64_t ul = nao - (mu0 + (tid % GB::TUP) * VB);
-    ad.up_lim = (int)(ul < 0 ? 0 : ul > VB ? VB : ul);
-}
 
-// n consecutive elements of B (n = VB, or fewer: zeros after them), converted
-template <typename T, typename TS, int VB>
-__device__ inline void g1_bvec(T (&v)[VB], const TS* __restrict__ src, int n) {
-    if (VB > 1 && n == VB) {
-        TS w[VB];
-        __builtin_memcpy(w, src, VB * sizeof(TS));
+    // chunk of rows nu0 .. nu0 + 15 (Cn: row nu0 of C)
+    __device__ inline void load(const TS* __restrict__ Bp, const T* __restrict__ Cn, int nao, int ldc, int nu0,
+                                int mu0, int tid) {
+        klive = min(nao - nu0, KC);
+        if (__builtin_expect(klive < KC, 0)) {
+            rare_path();
 #pragma unroll
-        for (int e = 0; e < VB; ++e) v[e] = to_compute<T, TS>(w[e]);
-    } else {
-#pragma unroll
-        for (int e = 0; e < VB; ++e) v[e] = e < n ? to_compute<T, TS>(src[e]) : T(0);
-    }
-}
-
-template <typename T, typename TS, int NI, int WM, int VC, int VB>
-__device__ inline void g1_load(G1Stage<T, NI, WM, VC, VB>& st, const G1Addr<T, NI, WM, VC, VB>& ad,
-                               const TS* __restrict__ Bp, int64_t nao,
-                               const T* __restrict__ C, bool cvec, int64_t nu0, int64_t mu0, int tid) {
-    using G = G1C<T, NI, VC>;
-    using GB = G1B<WM, VB>;
-    constexpr int BM = 64 * WM;
-#pragma unroll
-    for (int j = 0; j < G::NCV; ++j) {
-        const int k = (tid + j * kThreads) / G::VPR;
-        const int lim = nu0 + k < nao ? ad.c_lim[j] : 0;
-        if (VC > 1 && cvec && lim == VC) {
-            __builtin_memcpy(st.c[j], C + ad.c_off[j], VC * sizeof(T));
+            for (int j = 0; j < NC; ++j) {
+                const int e = tid + j * kThreads, k = e < NV ? e / VPR : 0;  // as coff
+                __builtin_memcpy(c[j], Cn + (coff[j] - (uint32_t)(max(k - klive + 1, 0) * ldc)), VC * sizeof(T));
+            }
         } else {
 #pragma unroll
-            for (int e = 0; e < G::V; ++e) st.c[j][e] = e < lim ? C[ad.c_off[j] + e] : T(0);
+            for (int j = 0; j < NC; ++j) __builtin_memcpy(c[j], Cn + coff[j], VC * sizeof(T));
         }
-    }
-    if (nu0 + KC <= mu0) {
-        // every nu < mu: packed row mu, columns nu0 .. nu0+15
+        phase = nu0 + KC <= mu0 ? 0 : nu0 < mu0 + 64 * WM ? 1 : 2;
+        if (phase == 0) {
+            // every nu < mu: packed row mu, columns nu0 .. nu0+15
+            const TS* base = Bp + ((int64_t)mu0 * (mu0 + 1) / 2 + nu0);
 #pragma unroll
-        for (int j = 0; j < GB::NP; ++j) g1_bvec<T, TS, VB>(st.b[j], Bp + ad.lo_off[j], ad.mu_ok_lo[j] ? VB : 0);
-    } else if (nu0 >= mu0 + BM - 1) {
-        // every nu >= mu: packed row nu, columns mu0 .. mu0+BM-1
-        const int m = (tid % GB::TUP) * VB;
+            for (int j = 0; j < NP; ++j) __builtin_memcpy(b[j], base + loff[j], VB * sizeof(TS));
+        } else if (phase == 2) {
+            // every nu > mu: packed row nu, columns mu0 .. mu0+BM-1
+            const TS* base = Bp + ((int64_t)nu0 * (nu0 + 1) / 2 + mu0);
+            if (__builtin_expect(klive < KC, 0)) {
+                rare_path();
 #pragma unroll
-        for (int j = 0; j < GB::NP; ++j) {
-            const int64_t nu = nu0 + tid / GB::TUP + GB::RUP * j;
-            g1_bvec<T, TS, VB>(st.b[j], Bp + ad.up_row[j] + mu0 + m, nu < nao ? ad.up_lim : 0);
-        }
-    } else {
-        // chunk crossing the diagonal (above-diagonal layout, element loads)
-        const int m = (tid % GB::TUP) * VB;
+                for (int j = 0; j < NP; ++j) {
+                    const int k = min(tid / TUP + RUP * j, klive - 1);
+                    const uint32_t off = (uint32_t)(k * nu0 + k * (k + 1) / 2 + (tid % TUP) * VB);
+                    __builtin_memcpy(b[j], base + off, VB * sizeof(TS));
+                }
+            } else {
 #pragma unroll
-        for (int j = 0; j < GB::NP; ++j) {
-            const int64_t nu = nu0 + tid / GB::TUP + GB::RUP * j;
+                for (int j = 0; j < NP; ++j)
+                    __builtin_memcpy(b[j], base + ((uint32_t)(tid / TUP + RUP * j) * (uint32_t)nu0 + ucon[j]),
+                                     VB * sizeof(TS));
+            }
+        } else {
+            // chunk crossing the diagonal (rows as above it, element loads)
+            const TS* base = Bp + (int64_t)mu0 * (mu0 + 1) / 2;
+            const int dnu = nu0 - mu0, dmax = nao - 1 - mu0;
 #pragma unroll
-            for (int e = 0; e < VB; ++e) {
-                const int64_t mu = mu0 + m + e;
-                st.b[j][e] = (nu < nao && mu < nao) ? to_compute<T, TS>(Bp[pidx(nu, mu)]) : T(0);
+            for (int j = 0; j < NP; ++j) {
+                const int k0 = tid / TUP + RUP * j;
+#pragma unroll
+                for (int q = 0; q < VB; ++q) {
+                    // offsets from mu0: row hi, T(mu0 + hi) - T(mu0) = hi mu0 + hi(hi+1)/2
+                    const int dm = min((tid % TUP) * VB + q, dmax), dn = min(dnu + k0, dmax);
+                    const int hi = max(dm, dn), lo = min(dm, dn);
+                    b[j][q] = base[(uint32_t)(hi * mu0 + hi * (hi + 1) / 2 + mu0 + lo)];
+                }
             }
         }
     }
-}
 
-// Move the addresses from chunk nu0 to chunk nu0 + KC.
-template <typename T, int NI, int WM, int VC, int VB>
-__device__ inline void g1_addr_next(G1Addr<T, NI, WM, VC, VB>& ad, int64_t nu0, int64_t ldc, int tid) {
-    using GB = G1B<WM, VB>;
+    // The loaded values are first looked at here, a chunk of products after
+    // their loads were issued: zeroing the rows past nao while loading made the
+    // wavefront wait for the loads before those products.
+    __device__ inline void store(T (*sC)[PC], T (*sB)[PB], int tid) {
+        if (__builtin_expect(klive < KC, 0)) {
+            rare_path();
 #pragma unroll
-    for (int j = 0; j < G1C<T, NI, VC>::NCV; ++j) ad.c_off[j] += (int64_t)KC * ldc;
+            for (int j = 0; j < NC; ++j)
 #pragma unroll
-    for (int j = 0; j < GB::NP; ++j) {
-        ad.lo_off[j] += KC;
-        const int64_t nu = nu0 + tid / GB::TUP + GB::RUP * j;
-        ad.up_row[j] += (int64_t)KC * nu + (KC * (KC + 1)) / 2;
-    }
-}
-
-// LDS row pitches of the GEMM1 tiles.  An FP32 operand read covers 4 rows x
-// 16 consecutive columns (64 lanes, 64 banks): a pitch of 16 or 48 modulo 64
-// words puts the four rows on disjoint banks.  The B tile is also written
-// transposed (16 rows x 4 columns per wavefront), so its columns are XOR-ed
-// with g1_swz(row) < 16, which keeps every 16-column group in place for the
-// reads and spreads the transposed writes over all banks.  FP64 reads go 16
-// lanes at a time, so the FP64 tiles keep a pitch of one extra element.  The
-// per-row XOR costs address registers: on MI355X the bank-free layout was
-// faster only for FP32 storage and the (5, 1) tile (26.0 -> 25.0 ms at
-// nao=1024, naux=4096, nocc=200); for the (13, 1) tile it ran 22.1 against
-// 21.6 ms (FP32 B) and 460 against 450 ms (BF16 B, nao=2048, nocc=400), so
-// the other tiles keep the padded layout.
-template <typename T, typename TS, int NI, int WM>
-constexpr bool g1_bankfree() { return sizeof(T) == 4 && sizeof(TS) == 4 && WM == 1 && NI <= 5; }
-template <typename T, typename TS, int NI, int WM>
-constexpr int g1_pitch_c() {
-    return g1_bankfree<T, TS, NI, WM>() ? ((16 * NI) % 32 == 16 ? 16 * NI : 16 * NI + 16) : 16 * NI + 1;
-}
-template <typename T, typename TS, int NI, int WM>
-constexpr int g1_pitch_b() { return g1_bankfree<T, TS, NI, WM>() ? 64 * WM + 16 : 64 * WM + 1; }
-template <typename T, typename TS, int NI, int WM>
-__device__ inline int g1_swz(int row) { return g1_bankfree<T, TS, NI, WM>() ? 2 * ((row >> 1) & 7) : 0; }
-
-template <typename T, typename TS, int NI, int WM, int VC, int VB>
-__device__ inline void g1_store(const G1Stage<T, NI, WM, VC, VB>& st, T (*sC)[g1_pitch_c<T, TS, NI, WM>()],
-                                T (*sB)[g1_pitch_b<T, TS, NI, WM>()], bool lower, int tid) {
-    using G = G1C<T, NI, VC>;
-    using GB = G1B<WM, VB>;
+                for (int q = 0; q < VC; ++q)
+                    if ((tid + j * kThreads) / VPR >= klive) c[j][q] = T(0);
 #pragma unroll
-    for (int j = 0; j < G::NCV; ++j) {
-        const int e = tid + j * kThreads;
-        if (G::NV % kThreads == 0 || e < G::NV) {
-            const int k = e / G::VPR, ii = (e % G::VPR) * G::V;
+            for (int j = 0; j < NP; ++j)
 #pragma unroll
-            for (int q = 0; q < G::V; ++q) sC[k][ii + q] = st.c[j][q];
+                for (int q = 0; q < VB; ++q)
+                    if (tid / TUP + RUP * j >= klive) b[j][q] = TS(0);
         }
-    }
-    if (lower) {
-        // element e of load j: row nu0 + (tid % TLO) * VB + e, column mu
 #pragma unroll
-        for (int j = 0; j < GB::NP; ++j) {
-            const int m = tid / GB::TLO + GB::RLO * j;
+        for (int j = 0; j < NC; ++j) {
+            const int e = tid + j * kThreads;
+            if (NV % kThreads == 0 || e < NV) __builtin_memcpy(&sC[e / VPR][(e % VPR) * VC], c[j], VC * sizeof(T));
+        }
+        if (phase == 0) {
+            // element q of load j: row (tid % TLO) * VB + q, column mu
 #pragma unroll
-            for (int e = 0; e < VB; ++e) {
-                const int r = (tid % GB::TLO) * VB + e;
-                sB[r][m ^ g1_swz<T, TS, NI, WM>(r)] = st.b[j][e];
+            for (int j = 0; j < NP; ++j) {
+                const int m = tid / TLO + RLO * j;
+#pragma unroll
+                for (int q = 0; q < VB; ++q) {
+                    const int r = (tid % TLO) * VB + q;
+                    sB[r][m ^ swz(r)] = to_compute<T, TS>(b[j][q]);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                const int r = tid / TUP + RUP * j, m = (tid % TUP) * VB;
+                T v[VB];
+#pragma unroll
+                for (int q = 0; q < VB; ++q) v[q] = to_compute<T, TS>(b[j][q]);
+                __builtin_memcpy(&sB[r][m ^ swz(r)], v, VB * sizeof(T));
             }
         }
-    } else {
-#pragma unroll
-        for (int j = 0; j < GB::NP; ++j) {
-            const int r = tid / GB::TUP + GB::RUP * j, m = (tid % GB::TUP) * VB;
-#pragma unroll
-            for (int e = 0; e < VB; ++e) sB[r][(m + e) ^ g1_swz<T, TS, NI, WM>(r)] = st.b[j][e];
-        }
     }
-}
+};
 
 // Block order: consecutive hardware block ids go round-robin to the 8 XCDs.
 // Renumber so that runs of consecutive logical ids share an XCD (and its L2):
@@ -276,17 +240,17 @@ __device__ inline int64_t xcd_logical(int64_t hw, int64_t nblk) {
 // X[(P*ncol + i)*ldx + mu] = sum_nu C[nu][i] B_P[nu][mu]
 // 1-D grid of nib * nmb * naux blocks; logical id -> (i block fastest, mu block, P)
 // Columns [ioff, iend) of the ncol orbital columns (a launch may cover part of
-// them with one tile and the rest with another).
-// VC: orbitals of C per load (1, or 16 bytes' worth).
-template <typename T, typename TS, int NI, int WM, int VC = 1, int VB = g1_vb<TS, WM, VC>()>
+// them with one tile and the rest with another).  ldc is a multiple of VC.
+template <typename T, typename TS, int NI, int WM>
 __device__ __attribute__((always_inline)) inline void k_gemm1_body(int64_t lid, const TS* __restrict__ B, int64_t ldB, int64_t nao,
                                     const T* __restrict__ C, int64_t ldc, int64_t ncol,
                                     T* __restrict__ X, int64_t ldx, int64_t nib, int64_t nmb,
                                     int64_t ioff = 0, int64_t iend = -1) {
+    using S = G1<T, TS, NI, WM>;
     constexpr int BI = 16 * NI, BM = 64 * WM;
     if (iend < 0) iend = ncol;
-    __shared__ T sC[2][KC][g1_pitch_c<T, TS, NI, WM>()];
-    __shared__ T sB[2][KC][g1_pitch_b<T, TS, NI, WM>()];
+    __shared__ __attribute__((aligned(16))) T sC[2][KC][S::PC];
+    __shared__ __attribute__((aligned(16))) T sB[2][KC][S::PB];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t ib = lid % nib, mb = (lid / nib) % nmb, P = lid / (nib * nmb);
     const int64_t i0 = ioff + ib * BI, mu0 = mb * BM;
@@ -298,49 +262,51 @@ __device__ __attribute__((always_inline)) inline void k_gemm1_body(int64_t lid, 
 #pragma unroll
         for (int b = 0; b < WM; ++b) acc[a][b] = Mma<T>::zero();
 
-    const int64_t nchunks = cdiv(nao, KC);
-    G1Stage<T, NI, WM, VC, VB> st;
-    G1Addr<T, NI, WM, VC, VB> ad;
-    // 16-byte loads of C where its rows are 16-byte aligned
-    const bool cvec = VC > 1 && ldc % VC == 0 && i0 % VC == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
-    g1_addr_init<T, NI, WM, VC, VB>(ad, nao, ldc, iend, mu0, i0, tid);
-    g1_load<T, TS, NI, WM, VC, VB>(st, ad, Bp, nao, C, cvec, 0, mu0, tid);
-    g1_store<T, TS, NI, WM, VC, VB>(st, sC[0], sB[0], KC <= mu0, tid);
+    // operand columns of this lane before the row's swizzle
+    const int ca = lane & 15, cb = wave * 16 * WM + ((lane & 15) ^ (sizeof(T) == 8 ? 2 * (lane >> 5) : 0));
+    S st;
+    const int nao_ = (int)nao, ldc_ = (int)ldc, mu0_ = (int)mu0;
+    st.init(nao_, ldc_, mu0_, (int)i0, tid);
+    const T* Cn = C;
+    st.load(Bp, Cn, nao_, ldc_, 0, mu0_, tid);
+    st.store(sC[0], sB[0], tid);
+    if (KC < nao_) st.load(Bp, Cn += KC * ldc, nao_, ldc_, KC, mu0_, tid);
     __syncthreads();
-    for (int64_t ch = 0; ch < nchunks; ++ch) {
-        const int buf = ch & 1;
-        const int64_t nnext = (ch + 1) * KC;
-        const bool more = ch + 1 < nchunks;
-        if (more) {
-            g1_addr_next<T, NI, WM, VC, VB>(ad, ch * KC, ldc, tid);
-            g1_load<T, TS, NI, WM, VC, VB>(st, ad, Bp, nao, C, cvec, nnext, mu0, tid);
-        }
+    int buf = 0;
+    for (int nu0 = 0; nu0 < nao_; nu0 += KC, buf ^= 1) {
 #pragma unroll
         for (int kk = 0; kk < KC / 4; ++kk) {
             const int kr = kk * 4 + (lane >> 4);
             T a[NI], b[WM];
 #pragma unroll
-            for (int t = 0; t < NI; ++t) a[t] = sC[buf][kr][t * 16 + (lane & 15)];
+            for (int t = 0; t < NI; ++t) a[t] = sC[buf][kr][t * 16 + ca];
 #pragma unroll
-            for (int t = 0; t < WM; ++t) b[t] = sB[buf][kr][(wave * 16 * WM + t * 16 + (lane & 15)) ^ g1_swz<T, TS, NI, WM>(kr)];
+            for (int t = 0; t < WM; ++t)
+                b[t] = sB[buf][kr][sizeof(T) == 8 ? t * 16 + (cb ^ (4 * kk)) : (t * 16 + cb) ^ (16 * kk)];
 #pragma unroll
             for (int ti = 0; ti < NI; ++ti)
 #pragma unroll
                 for (int tj = 0; tj < WM; ++tj) acc[ti][tj] = Mma<T>::step(a[ti], b[tj], acc[ti][tj]);
         }
-        if (more) g1_store<T, TS, NI, WM, VC, VB>(st, sC[buf ^ 1], sB[buf ^ 1], nnext + KC <= mu0, tid);
+        if (nu0 + KC < nao_) {
+            st.store(sC[buf ^ 1], sB[buf ^ 1], tid);
+            if (nu0 + 2 * KC < nao_) st.load(Bp, Cn += KC * ldc, nao_, ldc_, nu0 + 2 * KC, mu0_, tid);
+        }
         __syncthreads();
     }
+    T* Xp = X + (P * ncol + i0) * ldx + mu0;
 #pragma unroll
-    for (int ti = 0; ti < NI; ++ti)
+    for (int tj = 0; tj < WM; ++tj) {
+        const int m = wave * 16 * WM + tj * 16 + (lane & 15);
+        if (mu0 + m >= nao) continue;
 #pragma unroll
-        for (int tj = 0; tj < WM; ++tj)
+        for (int ti = 0; ti < NI; ++ti)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int64_t i = i0 + ti * 16 + Mma<T>::row(lane, r);
-                const int64_t mu = mu0 + wave * 16 * WM + tj * 16 + (lane & 15);
-                if (i < iend && mu < nao) X[(P * ncol + i) * ldx + mu] = acc[ti][tj][r];
+                const int i = ti * 16 + Mma<T>::row(lane, r);
+                if (i0 + i < iend) Xp[(int64_t)i * ldx + m] = acc[ti][tj][r];
             }
+    }
 }
 
 // FP32 form on v_mfma_f32_32x32x2f32 (4096 flop per step; lane l supplies
@@ -353,16 +319,17 @@ __device__ __attribute__((always_inline)) inline void k_gemm1_body(int64_t lid, 
 // register-only: 0.98 of the FP32 peak with 4 chains per wavefront).
 typedef float v16f_k __attribute__((ext_vector_type(16)));
 
-template <typename TS, int NJ, int WJ, int VC = 1>
+template <typename TS, int NJ, int WJ>
 __device__ __attribute__((always_inline)) inline void k_gemm1w_body(int64_t lid, const TS* __restrict__ B, int64_t ldB, int64_t nao,
                                      const float* __restrict__ C, int64_t ldc, int64_t ncol,
                                      float* __restrict__ X, int64_t ldx, int64_t nib, int64_t nmb,
                                      int64_t ioff = 0, int64_t iend = -1) {
     constexpr int NI = 2 * NJ, WM = 2 * WJ;
+    using S = G1<float, TS, NI, WM>;
     constexpr int BI = 16 * NI, BM = 64 * WM;
     if (iend < 0) iend = ncol;
-    __shared__ float sC[2][KC][g1_pitch_c<float, TS, NI, WM>()];
-    __shared__ float sB[2][KC][g1_pitch_b<float, TS, NI, WM>()];
+    __shared__ __attribute__((aligned(16))) float sC[2][KC][S::PC];
+    __shared__ __attribute__((aligned(16))) float sB[2][KC][S::PB];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t ib = lid % nib, mb = (lid / nib) % nmb, P = lid / (nib * nmb);
     const int64_t i0 = ioff + ib * BI, mu0 = mb * BM;
@@ -376,24 +343,16 @@ __device__ __attribute__((always_inline)) inline void k_gemm1w_body(int64_t lid,
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
-    const int64_t nchunks = cdiv(nao, KC);
-    constexpr int VB = g1_vb<TS, WM, VC>();
-    G1Stage<float, NI, WM, VC, VB> st;
-    G1Addr<float, NI, WM, VC, VB> ad;
-    // 16-byte loads of C where its rows are 16-byte aligned
-    const bool cvec = VC > 1 && ldc % VC == 0 && i0 % VC == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
-    g1_addr_init<float, NI, WM, VC, VB>(ad, nao, ldc, iend, mu0, i0, tid);
-    g1_load<float, TS, NI, WM, VC, VB>(st, ad, Bp, nao, C, cvec, 0, mu0, tid);
-    g1_store<float, TS, NI, WM, VC, VB>(st, sC[0], sB[0], KC <= mu0, tid);
+    S st;
+    const int nao_ = (int)nao, ldc_ = (int)ldc, mu0_ = (int)mu0;
+    st.init(nao_, ldc_, mu0_, (int)i0, tid);
+    const float* Cn = C;
+    st.load(Bp, Cn, nao_, ldc_, 0, mu0_, tid);
+    st.store(sC[0], sB[0], tid);
+    if (KC < nao_) st.load(Bp, Cn += KC * ldc, nao_, ldc_, KC, mu0_, tid);
     __syncthreads();
-    for (int64_t ch = 0; ch < nchunks; ++ch) {
-        const int buf = ch & 1;
-        const int64_t nnext = (ch + 1) * KC;
-        const bool more = ch + 1 < nchunks;
-        if (more) {
-            g1_addr_next<float, NI, WM, VC, VB>(ad, ch * KC, ldc, tid);
-            g1_load<float, TS, NI, WM, VC, VB>(st, ad, Bp, nao, C, cvec, nnext, mu0, tid);
-        }
+    int buf = 0;
+    for (int nu0 = 0; nu0 < nao_; nu0 += KC, buf ^= 1) {
 #pragma unroll
         for (int kp = 0; kp < KC / 2; ++kp) {
             const int kr = kp * 2 + (lane >> 5);
@@ -402,14 +361,17 @@ __device__ __attribute__((always_inline)) inline void k_gemm1w_body(int64_t lid,
             for (int t = 0; t < NJ; ++t) a[t] = sC[buf][kr][t * 32 + (lane & 31)];
 #pragma unroll
             for (int t = 0; t < WJ; ++t)
-                b[t] = sB[buf][kr][(wave * 32 * WJ + t * 32 + (lane & 31)) ^ g1_swz<float, TS, NI, WM>(kr)];
+                b[t] = sB[buf][kr][(wave * 32 * WJ + t * 32 + (lane & 31)) ^ (16 * (kp >> 1))];
 #pragma unroll
             for (int ti = 0; ti < NJ; ++ti)
 #pragma unroll
                 for (int tj = 0; tj < WJ; ++tj)
                     acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ti], b[tj], acc[ti][tj], 0, 0, 0);
         }
-        if (more) g1_store<float, TS, NI, WM, VC, VB>(st, sC[buf ^ 1], sB[buf ^ 1], nnext + KC <= mu0, tid);
+        if (nu0 + KC < nao_) {
+            st.store(sC[buf ^ 1], sB[buf ^ 1], tid);
+            if (nu0 + 2 * KC < nao_) st.load(Bp, Cn += KC * ldc, nao_, ldc_, nu0 + 2 * KC, mu0_, tid);
+        }
         __syncthreads();
     }
 #pragma unroll
@@ -429,7 +391,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm1w(const TS* __restrict__ B, i
                                                       const float* __restrict__ C, int64_t ldc, int64_t ncol,
                                                       float* __restrict__ X, int64_t ldx, int64_t nib,
                                                       int64_t nmb, int64_t nblk, int64_t ioff, int64_t iend) {
-    k_gemm1w_body<TS, NJ, WJ, 4>(xcd_logical(blockIdx.x, nblk), B, ldB, nao, C, ldc, ncol, X, ldx, nib, nmb,
+    k_gemm1w_body<TS, NJ, WJ>(xcd_logical(blockIdx.x, nblk), B, ldB, nao, C, ldc, ncol, X, ldx, nib, nmb,
                               ioff, iend);
 }
 
@@ -450,28 +412,11 @@ __global__ __launch_bounds__(kThreads, (g1_waves<T, TS, NI, WM>())) void k_gemm1
                                                      const T* __restrict__ C, int64_t ldc, int64_t ncol,
                                                      T* __restrict__ X, int64_t ldx, int64_t nib,
                                                      int64_t nmb, int64_t nblk, int64_t ioff, int64_t iend) {
-    // FP32: C and B staged up to 16 bytes per load (measured faster: 21.5 ->
-    // 19.05 ms for the (13,1) tile at nao=1024, nocc=200); FP64 keeps one
-    // element per load (wide C ran 36.9 against 35.7 ms, wide B no faster)
-    k_gemm1_body<T, TS, NI, WM, sizeof(T) == 4 ? 4 : 1>(xcd_logical(blockIdx.x, nblk), B, ldB, nao, C, ldc, ncol, X, ldx, nib,
-                                nmb, ioff, iend);
+    k_gemm1_body<T, TS, NI, WM>(xcd_logical(blockIdx.x, nblk), B, ldB, nao, C, ldc, ncol, X, ldx, nib, nmb, ioff,
+                                iend);
 }
 
 // ---------------------------------------------------------------- GEMM2 (SYRK)
-// Staging of one KC-deep chunk of the two 128-wide operand panels, 8
-// elements of each per thread.  Vector form (rows 16-byte aligned): each
-// load moves V = 16 / sizeof(T) consecutive elements of a row, rows RPP
-// apart.  Element form (any row stride): one element per load, the 256
-// threads covering two rows of 128 per pass.
-template <typename T>
-struct SyStage {
-    static constexpr int V = 16 / sizeof(T);          // elements per vector load
-    static constexpr int TPR = SY_T / V;              // threads per panel row
-    static constexpr int RPP = kThreads / TPR;        // rows per pass
-    static constexpr int NP = KC / RPP;               // passes per chunk
-    T a[8], b[8];
-};
-
 // GEMM2 modes.  SY_SYM: K = sum_k s_k x_k x_k^T over the rows of one X,
 // lower tiles.  For two factors (D = L R^T) X holds X_L (rows 0..n) and then
 // X_R (rows n..2n), and row k of the second operand is row (k + n) mod 2n:
@@ -480,105 +425,168 @@ struct SyStage {
 // transpose (sum_k xL_k xR_k^T + xR_k xL_k^T, a symmetric result).
 enum { SY_SYM = 0, SY_PAIR_LOWER = 1, SY_PAIR_FULL = 2 };
 
-// V elements of row xr from column c0 (zeros at or past nao); one 16-byte
-// load when all of them are below nao
+// Staging of one KC-deep chunk of a 128-wide operand panel: 16-byte loads (rows
+// of X start 16-byte aligned: ldx is a multiple of V), 8 elements per thread.
+// Addresses are a uniform base plus a 32-bit offset that stays the same for
+// every chunk; columns past the rows are clamped to the last vector of a row
+// (they feed output rows or columns at or past nao, which are never read);
+// contraction rows past kend are zeroed, in the last chunk only.
+constexpr int SY_P = SY_T + 16;  // LDS pitch: 16 modulo 64 floats / 32 doubles, so a read's rows use different banks
+
 template <typename T>
-__device__ inline void sy_vec(T* v, const T* __restrict__ xr, int64_t c0, int64_t nao, bool ok) {
-    constexpr int V = SyStage<T>::V;
-    if (ok && c0 + V <= nao) {
-        __builtin_memcpy(v, xr + c0, 16);
-    } else {
-#pragma unroll
-        for (int e = 0; e < V; ++e) v[e] = (ok && c0 + e < nao) ? xr[c0 + e] : T(0);
-    }
-}
+struct SyPanel {
+    static constexpr int V = 16 / sizeof(T);          // elements per load
+    static constexpr int TPR = SY_T / V;              // threads per panel row
+    static constexpr int RPP = kThreads / TPR;        // rows per pass
+    static constexpr int NP = KC / RPP;               // passes per chunk
+    T v[NP][V];
+    uint32_t off[NP];
 
-template <typename T, int MODE, bool VEC>
-__device__ inline void sy_load(SyStage<T>& st, const T* __restrict__ X, int64_t ldx,
-                               int64_t nrows, int64_t nao, int64_t ncol, const double* __restrict__ sign,
-                               int64_t k0, int64_t kend, int64_t mu0, int64_t nu0, int64_t boff, int tid) {
-    using S = SyStage<T>;
-    auto rows = [&](int k, const T*& xr, const T*& xb, bool& ok, bool& neg) {
-        const int64_t row = k0 + k;
-        ok = row < kend;
-        xr = X + row * ldx;
-        xb = xr;
-        if constexpr (MODE != SY_SYM) {
-            const int64_t rb = row + boff;
-            xb = X + (rb >= 2 * boff ? rb - 2 * boff : rb) * ldx;
-        }
-        neg = sign && ok && sign[row % ncol] < 0;
-    };
-    if constexpr (VEC) {
+    __device__ inline void init(int64_t ldx, int64_t col0, int tid) {
+        const int64_t c = col0 + (tid % TPR) * V <= ldx - V ? col0 + (tid % TPR) * V : ldx - V;
 #pragma unroll
-        for (int p = 0; p < S::NP; ++p) {
-            const int k = tid / S::TPR + S::RPP * p, m = (tid % S::TPR) * S::V;
-            const T *xr, *xb;
-            bool ok, neg;
-            rows(k, xr, xb, ok, neg);
-            sy_vec<T>(&st.a[p * S::V], xr, mu0 + m, nao, ok);
-            sy_vec<T>(&st.b[p * S::V], xb, nu0 + m, nao, ok);
+        for (int p = 0; p < NP; ++p) off[p] = (uint32_t)((tid / TPR + RPP * p) * ldx + c);
+    }
+    // rows base .. base + 15 (base: uniform)
+    __device__ inline void load(const T* __restrict__ base) {
 #pragma unroll
-            for (int e = 0; e < S::V; ++e)
-                if (neg) st.b[p * S::V + e] = -st.b[p * S::V + e];
-        }
-    } else {
+        for (int p = 0; p < NP; ++p) __builtin_memcpy(v[p], base + off[p], 16);
+    }
+    // the same with klive < 16 rows (the others repeat the last one), and
+    // `shift` more elements for the rows at or past `from`
+    __device__ inline void load_part(const T* __restrict__ base, int klive, int64_t ldx, int tid, int from,
+                                     int64_t shift) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int k = tid / SY_T + 2 * j, m = tid % SY_T;
-            const T *xr, *xb;
-            bool ok, neg;
-            rows(k, xr, xb, ok, neg);
-            st.a[j] = (ok && mu0 + m < nao) ? xr[mu0 + m] : T(0);
-            const T bv = (ok && nu0 + m < nao) ? xb[nu0 + m] : T(0);
-            st.b[j] = neg ? -bv : bv;
+        for (int p = 0; p < NP; ++p) {
+            const int k = tid / TPR + RPP * p;
+            const T* src = base + off[p];
+            if (k >= klive) src -= (k - klive + 1) * ldx;
+            if (min(k, klive - 1) >= from) src += shift;
+            __builtin_memcpy(v[p], src, 16);
         }
     }
-}
+    // (the loaded values are first looked at here, a chunk of products after their loads)
+    __device__ inline void store(T (*s)[SY_P], int klive, int tid) {
+        if (__builtin_expect(klive < KC, 0)) {
+            rare_path();
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+                if (tid / TPR + RPP * p >= klive)
+#pragma unroll
+                    for (int e = 0; e < V; ++e) v[p][e] = T(0);
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p) __builtin_memcpy(&s[tid / TPR + RPP * p][(tid % TPR) * V], v[p], 16);
+    }
+};
 
-template <typename T, bool VEC>
-__device__ inline void sy_store(const SyStage<T>& st, T (*sA)[SY_T + (sizeof(T) == 4 ? 16 : 1)],
-                                T (*sB)[SY_T + (sizeof(T) == 4 ? 16 : 1)], int tid) {
-    using S = SyStage<T>;
-    if constexpr (VEC) {
-#pragma unroll
-        for (int p = 0; p < S::NP; ++p) {
-            const int k = tid / S::TPR + S::RPP * p, m = (tid % S::TPR) * S::V;
-#pragma unroll
-            for (int e = 0; e < S::V; ++e) {
-                sA[k][m + e] = st.a[p * S::V + e];
-                sB[k][m + e] = st.b[p * S::V + e];
+// The chunk loop of one output tile: stages the panels and calls step(sA, sB,
+// kr) for every 4-deep step.  A chunk's loads are issued when the chunk before
+// it has been stored, so they have a whole chunk of products to arrive.  ONE:
+// both operands are the same panel (a diagonal tile of an unsigned symmetric
+// product), staged once.
+template <typename T, int MODE, bool SIGN, bool ONE, typename F>
+__device__ __attribute__((always_inline)) inline void sy_loop(const T* __restrict__ X, int64_t ldx, int64_t mu0, int64_t nu0, int64_t ncol,
+                                                              const double* __restrict__ sign, int64_t kbeg, int64_t kend,
+                                                              int64_t boff, T (*sA)[KC][SY_P], T (*sB)[KC][SY_P],
+                                                              F&& step) {
+    if (kbeg >= kend) return;
+    using S = SyPanel<T>;
+    const int tid = threadIdx.x, lane = tid & 63;
+    S pa, pb;
+    pa.init(ldx, mu0, tid);
+    if (!ONE) pb.init(ldx, nu0, tid);
+    const T* base = X + kbeg * ldx;      // next chunk to load
+    int rows = (int)(kend - kbeg);       // rows from there on
+    int64_t left = boff - kbeg;          // rows from there on below boff (pairs)
+    int klive = KC;                      // rows of the chunk in the panels
+    double sg[S::NP];
+    auto load = [&]() {
+        klive = min(rows, KC);
+        if (__builtin_expect(klive < KC, 0)) {
+            rare_path();
+            pa.load_part(base, klive, ldx, tid, KC, 0);
+        } else {
+            pa.load(base);
+        }
+        if (!ONE) {
+            // pairs: row k goes with row (k + boff) mod 2 boff
+            const T* bb = MODE == SY_SYM ? base : left > 0 ? base + boff * ldx : base - boff * ldx;
+            if (__builtin_expect(klive < KC || (MODE != SY_SYM && left > 0 && left < KC), 0)) {
+                rare_path();
+                const bool wraps = MODE != SY_SYM && left > 0 && left < KC;
+                pb.load_part(bb, klive, ldx, tid, wraps ? (int)left : KC, -2 * boff * ldx);
+            } else {
+                pb.load(bb);
             }
         }
-    } else {
+        if (SIGN) {
+            const int64_t row0 = kend - rows;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            sA[tid / SY_T + 2 * j][tid % SY_T] = st.a[j];
-            sB[tid / SY_T + 2 * j][tid % SY_T] = st.b[j];
+            for (int p = 0; p < S::NP; ++p) {
+                const int64_t row = row0 + min(tid / S::TPR + S::RPP * p, klive - 1);
+                sg[p] = sign[row % ncol];
+            }
         }
+        base += KC * ldx;
+        rows -= KC;
+        left -= KC;
+    };
+    auto store = [&](int buf) {
+        pa.store(sA[buf], klive, tid);
+        if (ONE) return;
+        if (SIGN) {
+#pragma unroll
+            for (int p = 0; p < S::NP; ++p)
+#pragma unroll
+                for (int e = 0; e < S::V; ++e) pb.v[p][e] = sg[p] < 0 ? -pb.v[p][e] : pb.v[p][e];
+        }
+        pb.store(sB[buf], klive, tid);
+    };
+    int todo = (int)cdiv(kend - kbeg, KC);  // chunks not yet multiplied
+    load();
+    store(0);
+    if (todo > 1) load();
+    __syncthreads();
+    for (int buf = 0; todo > 0; --todo, buf ^= 1) {
+#pragma unroll
+        for (int kk = 0; kk < KC / 4; ++kk) {
+            const int kr = kk * 4 + (lane >> 4);
+            step(sA[buf][kr], ONE ? sA[buf][kr] : sB[buf][kr]);
+        }
+        if (todo > 1) {
+            store(buf ^ 1);
+            if (todo > 2) load();
+        }
+        __syncthreads();
     }
 }
 
 // partial[(s*ntl + t)][m][n] = sum_{k in split s} X[k][mu0+m] * sign_k * X[k'][nu0+n]
 // (k' = k, or the row paired with k for two factors); block id = s*ntl + t,
 // t a lower tile (I >= J) or, for SY_PAIR_FULL, any tile (I = t / nt).
-// VEC: staging with 16-byte loads (X and ldx * sizeof(T) 16-byte aligned).
-template <typename T, int MODE = SY_SYM, bool VEC = false>
+// Three forms, all computing the 16 x 16 blocks the finish reads, every block
+// summed over k in the same 4-deep steps:
+//   whole tiles: 2 x 2 wavefronts of 64 x 64 (4 x 4 blocks);
+//   diagonal tiles of a symmetric result: the 36 blocks on or below the
+//     diagonal dealt to the four wavefronts, 9 each (fewer at the edge of K);
+//   tiles with rows past nao: each wavefront takes two block columns and the
+//     block rows below nao, so no wavefront idles.
+// One loop with a branch per product and 64-bit addresses took 16.2 ms at
+// nao=1024, naux=4096, nocc=200 in FP64 (every product sat between two jumps and
+// waited for its own operands); this takes 14.1 (61 TFLOP/s, matrix cores 80%
+// busy).  nao=701 in FP32, whose rows were not 16-byte aligned before ldx was
+// padded: 2.62 -> 1.83 ms.
+template <typename T, int MODE, bool SIGN>
 __device__ __attribute__((always_inline)) inline void k_syrk_body(int64_t lid, const T* __restrict__ X, int64_t ldx, int64_t nrows,
                                    int64_t nao, int64_t ncol, const double* __restrict__ sign,
                                    int64_t kchunk, int64_t ntl, T* __restrict__ part, int64_t boff = 0) {
-    // FP32 reads cover 4 rows x 16 columns over 64 banks: pitch 144 = 16 mod 64
-    constexpr int PS = sizeof(T) == 4 ? SY_T + 16 : SY_T + 1;
-    __shared__ T sA[2][KC][PS];
-    __shared__ T sB[2][KC][PS];
-    const int tid = threadIdx.x, lane = tid & 63;
-    // the wave index is the same in all lanes: keep it (and what follows from
-    // it) in scalar registers
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
-    const int64_t t = lid % ntl;
+    __shared__ __attribute__((aligned(16))) T sA[2][KC][SY_P];
+    __shared__ __attribute__((aligned(16))) T sB[2][KC][SY_P];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t t = lid % ntl, s = lid / ntl;
     int64_t I, J;
-    if constexpr (MODE == SY_PAIR_FULL) {
+    if (MODE == SY_PAIR_FULL) {
         const int64_t nt = cdiv(nao, SY_T);
         I = t / nt;
         J = t % nt;
@@ -589,98 +597,107 @@ __device__ __attribute__((always_inline)) inline void k_syrk_body(int64_t lid, c
         J = t - I * (I + 1) / 2;
     }
     const int64_t mu0 = I * SY_T, nu0 = J * SY_T;
-    const int64_t s = lid / ntl;
-    const int64_t kbeg = s * kchunk;
-    const int64_t kend = kbeg + kchunk < nrows ? kbeg + kchunk : nrows;
-
-    // Wave -> 64 x 64 sub-tile (rows ab.., columns bb.. of the tile) and the
-    // 16 x 16 blocks of it that are computed: those the finish reads (rows
-    // and columns below nao, on or below the diagonal of K).  Off the
-    // diagonal the four waves take the 2 x 2 sub-tiles; a diagonal tile of a
-    // symmetric result needs 36 of the 64 blocks, spread as the two halves
-    // of its lower-left sub-tile (8 blocks each) and the lower block
-    // triangles of the two diagonal sub-tiles (10 each).  The blocks computed
-    // come out bitwise as with the plain 2 x 2 split.
-    const bool diag = MODE != SY_PAIR_FULL && I == J;
-    int ab = wm * 64, bb = wn * 64;
-    uint32_t pat = 0xFFFFu;
-    if (diag) {
-        ab = wave == 2 ? 0 : 64;
-        bb = wave == 3 ? 64 : 0;
-        pat = wave == 0 ? 0x00FFu : wave == 1 ? 0xFF00u : 0xF731u;
-    }
-    uint32_t live = 0;
-#pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 4; ++tj) {
-            const bool on = mu0 + ab + ti * 16 < nao && nu0 + bb + tj * 16 < nao;
-            live |= (uint32_t)on << (ti * 4 + tj);
-        }
-    live &= pat;
-
-    typename Mma<T>::acc_t acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = Mma<T>::zero();
-
-    if (kbeg < kend) {
-        const int64_t nchunks = cdiv(kend - kbeg, KC);
-        SyStage<T> st;
-        sy_load<T, MODE, VEC>(st, X, ldx, nrows, nao, ncol, sign, kbeg, kend, mu0, nu0, boff, tid);
-        sy_store<T, VEC>(st, sA[0], sB[0], tid);
-        __syncthreads();
-        for (int64_t ch = 0; ch < nchunks; ++ch) {
-            const int buf = ch & 1;
-            const bool more = ch + 1 < nchunks;
-            if (more)
-                sy_load<T, MODE, VEC>(st, X, ldx, nrows, nao, ncol, sign, kbeg + (ch + 1) * KC, kend, mu0,
-                                      nu0, boff, tid);
-#pragma unroll
-            for (int kk = 0; kk < KC / 4; ++kk) {
-                const int kr = kk * 4 + (lane >> 4);
-                T a[4], b[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    a[q] = sA[buf][kr][ab + q * 16 + (lane & 15)];
-                    b[q] = sB[buf][kr][bb + q * 16 + (lane & 15)];
-                }
-#pragma unroll
-                for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-                    for (int tj = 0; tj < 4; ++tj)
-                        if ((live >> (ti * 4 + tj)) & 1u) acc[ti][tj] = Mma<T>::step(a[ti], b[tj], acc[ti][tj]);
-            }
-            if (more) sy_store<T, VEC>(st, sA[buf ^ 1], sB[buf ^ 1], tid);
-            __syncthreads();
-        }
-    }
+    const int64_t kbeg = s * kchunk, kend = kbeg + kchunk < nrows ? kbeg + kchunk : nrows;
     T* out = part + (s * ntl + t) * (int64_t)(SY_T * SY_T);
+    const int nbr = nao - mu0 < SY_T ? (int)cdiv(nao - mu0, 16) : SY_T / 16;  // block rows below nao
+    const int lc = lane & 15;
+    auto put = [&](const typename Mma<T>::acc_t& a, int br, int bc) {
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
+        for (int r = 0; r < 4; ++r) out[(br * 16 + Mma<T>::row(lane, r)) * SY_T + bc * 16 + lc] = a[r];
+    };
+    if (MODE != SY_PAIR_FULL && I == J) {
+        constexpr int NB = 9;
+        const int total = nbr * (nbr + 1) / 2;
+        int br[NB], bc[NB];
+        typename Mma<T>::acc_t acc[NB];
 #pragma unroll
-        for (int tj = 0; tj < 4; ++tj) {
-            if (!((live >> (ti * 4 + tj)) & 1u)) continue;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = ab + ti * 16 + Mma<T>::row(lane, r);
-                const int n = bb + tj * 16 + (lane & 15);
-                out[m * SY_T + n] = acc[ti][tj][r];
-            }
+        for (int q = 0; q < NB; ++q) {
+            const int b = wave + 4 * q;
+            int i = 0;
+            while ((i + 1) * (i + 2) / 2 <= b) ++i;
+            br[q] = b < total ? i : 0;
+            bc[q] = b < total ? b - i * (i + 1) / 2 : 0;
+            acc[q] = Mma<T>::zero();
         }
+        const int mine = (total - wave + 3) / 4;
+        sy_loop<T, MODE, SIGN, MODE == SY_SYM && !SIGN>(
+            X, ldx, mu0, nu0, ncol, sign, kbeg, kend, boff, sA, sB, [&](const T* ra, const T* rb) {
+                T a[NB], b[NB];
+#pragma unroll
+                for (int q = 0; q < NB; ++q) {
+                    a[q] = ra[br[q] * 16 + lc];
+                    b[q] = rb[bc[q] * 16 + lc];
+                }
+                if (mine == NB) {
+#pragma unroll
+                    for (int q = 0; q < NB; ++q) acc[q] = Mma<T>::step(a[q], b[q], acc[q]);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < NB; ++q)
+                        if (q < mine) acc[q] = Mma<T>::step(a[q], b[q], acc[q]);
+                }
+            });
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+            if (q < mine) put(acc[q], br[q], bc[q]);
+    } else if (nbr < SY_T / 16) {
+        typename Mma<T>::acc_t acc[8][2];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i][0] = acc[i][1] = Mma<T>::zero();
+        sy_loop<T, MODE, SIGN, false>(X, ldx, mu0, nu0, ncol, sign, kbeg, kend, boff, sA, sB,
+                                      [&](const T* ra, const T* rb) {
+                                          const T b0 = rb[wave * 32 + lc], b1 = rb[wave * 32 + 16 + lc];
+                                          T a[8];
+#pragma unroll
+                                          for (int i = 0; i < 8; ++i) a[i] = ra[i * 16 + lc];
+#pragma unroll
+                                          for (int i = 0; i < 8; ++i)
+                                              if (i < nbr) {
+                                                  acc[i][0] = Mma<T>::step(a[i], b0, acc[i][0]);
+                                                  acc[i][1] = Mma<T>::step(a[i], b1, acc[i][1]);
+                                              }
+                                      });
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (i < nbr) {
+                put(acc[i][0], i, 2 * wave);
+                put(acc[i][1], i, 2 * wave + 1);
+            }
+    } else {
+        const int wm = wave >> 1, wn = wave & 1;
+        typename Mma<T>::acc_t acc[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = Mma<T>::zero();
+        sy_loop<T, MODE, SIGN, false>(X, ldx, mu0, nu0, ncol, sign, kbeg, kend, boff, sA, sB,
+                                      [&](const T* ra, const T* rb) {
+                                          T a[4], b[4];
+#pragma unroll
+                                          for (int q = 0; q < 4; ++q) {
+                                              a[q] = ra[wm * 64 + q * 16 + lc];
+                                              b[q] = rb[wn * 64 + q * 16 + lc];
+                                          }
+#pragma unroll
+                                          for (int i = 0; i < 4; ++i)
+#pragma unroll
+                                              for (int j = 0; j < 4; ++j) acc[i][j] = Mma<T>::step(a[i], b[j], acc[i][j]);
+                                      });
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) put(acc[i][j], wm * 4 + i, wn * 4 + j);
+    }
 }
 
-// FP32 held to 4 waves per SIMD (3 by its registers otherwise; LDS allows 4):
-// nao=1024, nocc=200: 8.26 -> 7.50 ms.
-template <typename T, int MODE = SY_SYM, bool VEC = false>
-__global__ __launch_bounds__(kThreads, (sizeof(T) == 4 ? 4 : 1)) void k_syrk(const T* __restrict__ X, int64_t ldx, int64_t nrows,
+template <typename T, int MODE, bool SIGN = false>
+__global__ __launch_bounds__(kThreads, (sizeof(T) == 4 ? 4 : 2)) void k_syrk(const T* __restrict__ X, int64_t ldx, int64_t nrows,
                                                     int64_t nao, int64_t ncol,
                                                     const double* __restrict__ sign, int64_t kchunk,
                                                     int64_t ntl, int64_t nblk, T* __restrict__ part,
                                                     int64_t boff) {
     // all tiles of one split run on one XCD and share its L2 copy of the X rows
-    k_syrk_body<T, MODE, VEC>(xcd_logical(blockIdx.x, nblk), X, ldx, nrows, nao, ncol, sign, kchunk, ntl, part,
+    k_syrk_body<T, MODE, SIGN>(xcd_logical(blockIdx.x, nblk), X, ldx, nrows, nao, ncol, sign, kchunk, ntl, part,
                          boff);
 }
 
@@ -745,24 +762,24 @@ __global__ __launch_bounds__(kThreads) void k_pair_finish(const T* __restrict__ 
 }
 
 template <typename T, typename TS, int NI, int WM>
-int launch_gemm1(const dfjk_ctx* h, const void* C, int64_t ncol, void* X, int64_t ldx, int64_t ioff,
+int launch_gemm1(const dfjk_ctx* h, const void* C, int64_t ldc, int64_t ncol, void* X, int64_t ldx, int64_t ioff,
                  int64_t iend) {
     const int64_t nib = cdiv(iend - ioff, 16 * NI), nmb = cdiv(h->nao, 64 * WM);
     const int64_t nblk = nib * nmb * h->naux;
     k_gemm1<T, TS, NI, WM><<<dim3((unsigned)nblk), kThreads, 0, h->stream>>>(
-        static_cast<const TS*>(h->B), h->ldB, h->nao, static_cast<const T*>(C), ncol, ncol,
+        static_cast<const TS*>(h->B), h->ldB, h->nao, static_cast<const T*>(C), ldc, ncol,
         static_cast<T*>(X), ldx, nib, nmb, nblk, ioff, iend);
     DFJK_LAUNCH_CHECK("k_gemm1");
     return DFJK_OK;
 }
 
 template <typename TS, int NJ, int WJ>
-int launch_gemm1w(const dfjk_ctx* h, const void* C, int64_t ncol, void* X, int64_t ldx, int64_t ioff,
+int launch_gemm1w(const dfjk_ctx* h, const void* C, int64_t ldc, int64_t ncol, void* X, int64_t ldx, int64_t ioff,
                   int64_t iend) {
     const int64_t nib = cdiv(iend - ioff, 32 * NJ), nmb = cdiv(h->nao, 128 * WJ);
     const int64_t nblk = nib * nmb * h->naux;
     k_gemm1w<TS, NJ, WJ><<<dim3((unsigned)nblk), kThreads, 0, h->stream>>>(
-        static_cast<const TS*>(h->B), h->ldB, h->nao, static_cast<const float*>(C), ncol, ncol,
+        static_cast<const TS*>(h->B), h->ldB, h->nao, static_cast<const float*>(C), ldc, ncol,
         static_cast<float*>(X), ldx, nib, nmb, nblk, ioff, iend);
     DFJK_LAUNCH_CHECK("k_gemm1w");
     return DFJK_OK;
@@ -771,7 +788,7 @@ int launch_gemm1w(const dfjk_ctx* h, const void* C, int64_t ncol, void* X, int64
 // Compiled GEMM1 tiles: (NI, WM) = (i tiles of 16, mu tiles of 16 per wave),
 // one launcher per B storage type (FP64 on the FP64 matrix cores; FP32, BF16
 // and FP16 dequantised exactly on load and run on the FP32 matrix cores).
-typedef int (*G1Launch)(const dfjk_ctx*, const void*, int64_t, void*, int64_t, int64_t, int64_t);
+typedef int (*G1Launch)(const dfjk_ctx*, const void*, int64_t, int64_t, void*, int64_t, int64_t, int64_t);
 struct G1Tile {
     int ni, wm;
     G1Launch by_dtype[4];  // indexed by dfjk_dtype
@@ -805,10 +822,35 @@ const G1Tile kG1Tiles[] = {
 constexpr int kNumG1Tiles = sizeof(kG1Tiles) / sizeof(kG1Tiles[0]);
 constexpr int kFirstRestTile = 12;  // (6,1) and (3,1): defaults only for the rest of a split
 
-// FP64 -> FP32 copy of C (one rounding per element).
-__global__ void to_f32(const double* __restrict__ x, int64_t n, float* __restrict__ y) {
+// Copy of C (nao x ncol) with rows ldc apart, FP32 with one rounding per
+// element (the columns past ncol stay as they are: GEMM1 does not store their
+// products).
+template <typename T>
+__global__ void c_rows(const double* __restrict__ x, int64_t nao, int64_t ncol, int64_t ldc, T* __restrict__ y) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] = (float)x[i];
+    if (i < nao * ncol) y[i / ncol * ldc + i % ncol] = (T)x[i];
+}
+
+// Row stride of C for GEMM1: whole 16-byte vectors.  FP64 reads the caller's C
+// when that holds already (an even ncol), else a copy; FP32 always a copy.
+int64_t c_stride(int64_t ncol, bool f32) { return f32 ? cdiv(ncol, 4) * 4 : cdiv(ncol, 2) * 2; }
+template <typename T>
+int c_operand(dfjk_ctx* h, const double* C, int64_t ncol, T* copy, const T** out) {
+    const int64_t ldc = c_stride(ncol, sizeof(T) == 4);
+    if (sizeof(T) == 8 && ldc == ncol) {
+        *out = reinterpret_cast<const T*>(C);
+        return DFJK_OK;
+    }
+    c_rows<T><<<dim3((unsigned)cdiv(h->nao * ncol, 256)), 256, 0, h->stream>>>(C, h->nao, ncol, ldc, copy);
+    DFJK_LAUNCH_CHECK("c_rows");
+    *out = copy;
+    return DFJK_OK;
+}
+// Bytes of the copies of n factors
+size_t c_bytes(const dfjk_ctx* h, int64_t ncol, int n) {
+    const bool f32 = h->dtype != DFJK_F64;
+    if (!f32 && c_stride(ncol, false) == ncol) return 0;
+    return (f32 ? 4 : 8) * (size_t)(n * h->nao * c_stride(ncol, f32));
 }
 
 // Default tile: least padded work, where each extra i block costs another
@@ -865,17 +907,18 @@ G1Split pick_g1_split(int64_t ncol, bool f32) {
 // X = (B_P C)^T for every P, with the handle's forced tile or the default
 // split (profiled as the GEMM1 phase).
 int run_gemm1(dfjk_ctx* h, const void* C, int64_t ncol, void* X, int64_t ldx, bool f32) {
+    const int64_t ldc = c_stride(ncol, f32);
     if (h->g1_tile >= 0 && h->g1_tile < kNumG1Tiles) {
         const G1Launch f = kG1Tiles[h->g1_tile].by_dtype[h->dtype];
         if (!f) {
             set_error("GEMM1 tile %d has no FP64 form", h->g1_tile);
             return DFJK_E_INVALID;
         }
-        return f(h, C, ncol, X, ldx, 0, ncol);
+        return f(h, C, ldc, ncol, X, ldx, 0, ncol);
     }
     G1Split sp = pick_g1_split(ncol, f32);
-    int rc = kG1Tiles[sp.t0].by_dtype[h->dtype](h, C, ncol, X, ldx, 0, sp.n0);
-    if (!rc && sp.n0 < ncol) rc = kG1Tiles[sp.t1].by_dtype[h->dtype](h, C, ncol, X, ldx, sp.n0, ncol);
+    int rc = kG1Tiles[sp.t0].by_dtype[h->dtype](h, C, ldc, ncol, X, ldx, 0, sp.n0);
+    if (!rc && sp.n0 < ncol) rc = kG1Tiles[sp.t1].by_dtype[h->dtype](h, C, ldc, ncol, X, ldx, sp.n0, ncol);
     return rc;
 }
 
@@ -903,23 +946,31 @@ void syrk_splits(int64_t nrows, int64_t ntl, bool f32, int64_t* nsplit_out, int6
 struct KBytes {
     size_t X, kpart;
 };
+// Row stride of X: whole 16-byte vectors, for the SYRK's loads
+int64_t x_stride(const dfjk_ctx* h, size_t elem) {
+    const int64_t V = 16 / (int64_t)elem;
+    return cdiv(h->nao, V) * V;
+}
 KBytes k_bytes(const dfjk_ctx* h, size_t elem, int64_t xrows, int64_t nrows, int64_t ntl) {
     int64_t nsplit, kchunk;
     syrk_splits(nrows, ntl, elem == 4, &nsplit, &kchunk);
-    return KBytes{elem * (size_t)xrows * (size_t)h->nao, elem * (size_t)(nsplit * ntl) * SY_T * SY_T};
+    return KBytes{elem * (size_t)xrows * (size_t)x_stride(h, elem), elem * (size_t)(nsplit * ntl) * SY_T * SY_T};
 }
 
 template <typename T>
-int k_build_t(dfjk_ctx* h, const void* C, int64_t ncol, const double* sign, double scale, double* K) {
-    const int64_t ldx = h->nao;
+int k_build_t(dfjk_ctx* h, const double* C_in, int64_t ncol, const double* sign, double scale, double* K) {
+    const int64_t ldx = x_stride(h, sizeof(T));
     const int64_t nrows = h->naux * ncol;
     const int64_t nt = cdiv(h->nao, SY_T);
     const int64_t ntl = nt * (nt + 1) / 2;
     const KBytes need = k_bytes(h, sizeof(T), nrows, nrows, ntl);
     int rc;
-    if ((rc = h->X.ensure(need.X)) || (rc = h->kpart.ensure(need.kpart))) return rc;
+    if ((rc = h->X.ensure(need.X)) || (rc = h->kpart.ensure(need.kpart)) || (rc = h->Cw.ensure(c_bytes(h, ncol, 1))))
+        return rc;
     T* X = static_cast<T*>(h->X.ptr);
 
+    const T* C = nullptr;
+    if ((rc = c_operand<T>(h, C_in, ncol, static_cast<T*>(h->Cw.ptr), &C))) return rc;
     h->prof.begin(PH_K, h->stream);
     h->prof.begin(PH_K_GEMM1, h->stream);
     rc = run_gemm1(h, C, ncol, X, ldx, sizeof(T) == 4);
@@ -930,12 +981,12 @@ int k_build_t(dfjk_ctx* h, const void* C, int64_t ncol, const double* sign, doub
     syrk_splits(nrows, ntl, sizeof(T) == 4, &nsplit, &kchunk);
     T* part = static_cast<T*>(h->kpart.ptr);
     h->prof.begin(PH_K_SYRK, h->stream);
-    if (ldx % SyStage<T>::V == 0)
+    if (sign)
         k_syrk<T, SY_SYM, true><<<dim3((unsigned)(ntl * nsplit)), kThreads, 0, h->stream>>>(
             X, ldx, nrows, h->nao, ncol, sign, kchunk, ntl, ntl * nsplit, part, 0);
     else
-        k_syrk<T><<<dim3((unsigned)(ntl * nsplit)), kThreads, 0, h->stream>>>(
-            X, ldx, nrows, h->nao, ncol, sign, kchunk, ntl, ntl * nsplit, part, 0);
+        k_syrk<T, SY_SYM><<<dim3((unsigned)(ntl * nsplit)), kThreads, 0, h->stream>>>(
+            X, ldx, nrows, h->nao, ncol, nullptr, kchunk, ntl, ntl * nsplit, part, 0);
     h->prof.end(PH_K_SYRK, h->stream);
     DFJK_LAUNCH_CHECK("k_syrk");
     h->prof.begin(PH_K_FINISH, h->stream);
@@ -952,17 +1003,23 @@ int k_build_t(dfjk_ctx* h, const void* C, int64_t ncol, const double* sign, doub
 //   sym = 0: K = scale * sum_P X_L^T X_R            (all output tiles)
 //   sym = 1: K = scale * sum_P (X_L^T X_R + X_R^T X_L)  (lower tiles, mirrored)
 template <typename T>
-int k_build_pair_t(dfjk_ctx* h, const void* L, const void* R, int64_t ncol, int sym, double scale, double* K) {
-    const int64_t ldx = h->nao;
+int k_build_pair_t(dfjk_ctx* h, const double* L_in, const double* R_in, int64_t ncol, int sym, double scale, double* K) {
+    const int64_t ldx = x_stride(h, sizeof(T));
     const int64_t n1 = h->naux * ncol;  // rows of X_L (and of X_R)
     const int64_t nt = cdiv(h->nao, SY_T);
     const int64_t ntl = sym ? nt * (nt + 1) / 2 : nt * nt;
     const int64_t nrows = sym ? 2 * n1 : n1;  // contraction length
     const KBytes need = k_bytes(h, sizeof(T), 2 * n1, nrows, ntl);
     int rc;
-    if ((rc = h->X.ensure(need.X)) || (rc = h->kpart.ensure(need.kpart))) return rc;
+    if ((rc = h->X.ensure(need.X)) || (rc = h->kpart.ensure(need.kpart)) || (rc = h->Cw.ensure(c_bytes(h, ncol, 2))))
+        return rc;
     T* X = static_cast<T*>(h->X.ptr);
 
+    const T *L = nullptr, *R = nullptr;
+    T* copy = static_cast<T*>(h->Cw.ptr);
+    if ((rc = c_operand<T>(h, L_in, ncol, copy, &L)) ||
+        (rc = c_operand<T>(h, R_in, ncol, copy + h->nao * c_stride(ncol, sizeof(T) == 4), &R)))
+        return rc;
     h->prof.begin(PH_K, h->stream);
     h->prof.begin(PH_K_GEMM1, h->stream);
     rc = run_gemm1(h, L, ncol, X, ldx, sizeof(T) == 4);
@@ -975,19 +1032,12 @@ int k_build_pair_t(dfjk_ctx* h, const void* L, const void* R, int64_t ncol, int 
     T* part = static_cast<T*>(h->kpart.ptr);
     const dim3 grid((unsigned)(ntl * nsplit));
     h->prof.begin(PH_K_SYRK, h->stream);
-    const bool vec = ldx % SyStage<T>::V == 0;
-    if (sym && vec)
-        k_syrk<T, SY_PAIR_LOWER, true><<<grid, kThreads, 0, h->stream>>>(X, ldx, nrows, h->nao, ncol, nullptr,
-                                                                           kchunk, ntl, ntl * nsplit, part, n1);
-    else if (sym)
-        k_syrk<T, SY_PAIR_LOWER><<<grid, kThreads, 0, h->stream>>>(X, ldx, nrows, h->nao, ncol, nullptr, kchunk,
-                                                                     ntl, ntl * nsplit, part, n1);
-    else if (vec)
-        k_syrk<T, SY_PAIR_FULL, true><<<grid, kThreads, 0, h->stream>>>(X, ldx, nrows, h->nao, ncol, nullptr,
-                                                                          kchunk, ntl, ntl * nsplit, part, n1);
+    if (sym)
+        k_syrk<T, SY_PAIR_LOWER><<<grid, kThreads, 0, h->stream>>>(X, ldx, nrows, h->nao, ncol, nullptr, kchunk, ntl,
+                                                                     ntl * nsplit, part, n1);
     else
-        k_syrk<T, SY_PAIR_FULL><<<grid, kThreads, 0, h->stream>>>(X, ldx, nrows, h->nao, ncol, nullptr, kchunk,
-                                                                    ntl, ntl * nsplit, part, n1);
+        k_syrk<T, SY_PAIR_FULL><<<grid, kThreads, 0, h->stream>>>(X, ldx, nrows, h->nao, ncol, nullptr, kchunk, ntl,
+                                                                    ntl * nsplit, part, n1);
     h->prof.end(PH_K_SYRK, h->stream);
     DFJK_LAUNCH_CHECK("k_syrk (two factors)");
     h->prof.begin(PH_K_FINISH, h->stream);
@@ -1030,7 +1080,7 @@ __global__ __launch_bounds__(kThreads, 4) void kb_kernel(int kind, const MolDesc
             break;
         }
         case BP_SYRK:
-            k_syrk_body<float, SY_SYM, true>(lid, d.X, d.ldx, d.naux * d.nocc, d.nao, d.nocc, nullptr, d.kchunk,
+            k_syrk_body<float, SY_SYM, false>(lid, d.X, d.ldx, d.naux * d.nocc, d.nao, d.nocc, nullptr, d.kchunk,
                                              d.ntl,
                                d.kpart);
             break;
@@ -1053,7 +1103,7 @@ __global__ __launch_bounds__(kThreads, (kb_g1_waves<NI, WM>())) void kb_gemm1(co
     const int64_t b = xcd_logical(blockIdx.x, pl.nblk);
     const int j = find_mol_k(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
-    k_gemm1_body<float, TS, NI, WM, 4>(b - pl.prefix[j], static_cast<const TS*>(d.B), d.ldB, d.nao, d.Cf,
+    k_gemm1_body<float, TS, NI, WM>(b - pl.prefix[j], static_cast<const TS*>(d.B), d.ldB, d.nao, d.Cf,
                                         d.ldcf, d.nocc, d.X, d.ldx, d.g1_nib, d.g1_nmb);
 }
 
@@ -1075,7 +1125,7 @@ __global__ __launch_bounds__(kThreads) void kb_gemm1w(const MolDesc* __restrict_
     const int64_t b = xcd_logical(blockIdx.x, pl.nblk);
     const int j = find_mol_k(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
-    k_gemm1w_body<TS, NJ, WJ, 4>(b - pl.prefix[j], static_cast<const TS*>(d.B), d.ldB, d.nao, d.Cf, d.ldcf,
+    k_gemm1w_body<TS, NJ, WJ>(b - pl.prefix[j], static_cast<const TS*>(d.B), d.ldB, d.nao, d.Cf, d.ldcf,
                                  d.nocc, d.X, d.ldx, d.g1_nib, d.g1_nmb);
 }
 
@@ -1134,31 +1184,16 @@ int k_build_factored(dfjk_ctx* h, const double* C, int64_t ncol, const double* s
     if (h->dtype == DFJK_F64) return k_build_t<double>(h, C, ncol, sign, scale, K);
     if ((h->dtype == DFJK_BF16 || h->dtype == DFJK_F16) && h->opts.k16 && !sign)
         return k_build_16(h, C, ncol, scale, K);
-    {  // FP32 compute for FP32, BF16 and FP16 storage of B
-        int rc;
-        if ((rc = h->Cw.ensure(sizeof(float) * (size_t)(h->nao * ncol)))) return rc;
-        float* Cf = static_cast<float*>(h->Cw.ptr);
-        to_f32<<<dim3((unsigned)cdiv(h->nao * ncol, 256)), 256, 0, h->stream>>>(C, h->nao * ncol, Cf);
-        DFJK_LAUNCH_CHECK("to_f32");
-        return k_build_t<float>(h, Cf, ncol, sign, scale, K);
-    }
+    // FP32 compute for FP32, BF16 and FP16 storage of B
+    return k_build_t<float>(h, C, ncol, sign, scale, K);
 }
 
 int k_build_pair(dfjk_ctx* h, const double* L, const double* R, int64_t ncol, int sym, double scale, double* K) {
     if (h->dtype == DFJK_F64) return k_build_pair_t<double>(h, L, R, ncol, sym, scale, K);
     // FP32 compute for FP32, BF16 and FP16 storage of B (also with the k16
     // option: the 16-bit exchange takes one factor)
-    int rc;
-    const int64_t n = h->nao * ncol;
-    if ((rc = h->Cw.ensure(sizeof(float) * (size_t)(2 * n)))) return rc;
-    float* Lf = static_cast<float*>(h->Cw.ptr);
-    float* Rf = Lf + n;
-    to_f32<<<dim3((unsigned)cdiv(n, 256)), 256, 0, h->stream>>>(L, n, Lf);
-    to_f32<<<dim3((unsigned)cdiv(n, 256)), 256, 0, h->stream>>>(R, n, Rf);
-    DFJK_LAUNCH_CHECK("to_f32");
-    return k_build_pair_t<float>(h, Lf, Rf, ncol, sym, scale, K);
+    return k_build_pair_t<float>(h, L, R, ncol, sym, scale, K);
 }
-
 
 int k_reserve(dfjk_ctx* h, int64_t max_ncol) {
     const size_t elem = h->dtype == DFJK_F64 ? 8 : 4;
@@ -1175,7 +1210,13 @@ int k_reserve(dfjk_ctx* h, int64_t max_ncol) {
     int rc;
     if ((rc = h->X.ensure(a.X > b.X ? a.X : b.X))) return rc;
     if ((rc = h->kpart.ensure(kp))) return rc;
-    if (h->dtype != DFJK_F64 && (rc = h->Cw.ensure(sizeof(float) * (size_t)(h->nao * max_ncol)))) return rc;
+    // copies of C: one factor of up to max_ncol columns or two of half as many
+    // (an FP64 copy is only made for an odd number of columns; a call may use
+    // fewer columns than reserved)
+    const size_t f = h->dtype == DFJK_F64 ? 8 : 4;
+    const size_t one = f * (size_t)(h->nao * c_stride(max_ncol, f == 4));
+    const size_t two = 2 * f * (size_t)(h->nao * c_stride(max_ncol / 2, f == 4));
+    if ((rc = h->Cw.ensure(one > two ? one : two))) return rc;
     return DFJK_OK;
 }
 
