@@ -82,7 +82,7 @@ int64_t phase_blocks(int kind, const MolDesc& d, int dtype) {
         case BP_JFIN: return d.nao;
         case BP_CF32: return cdiv(d.nao * d.nocc, kT);
         case BP_SYRK: return d.ntl * d.nsplit;
-        case BP_KFIN: return d.ntl;
+        case BP_KFIN: return d.ntl * kFinSub;
         case BP_CT16:
         case BP_SYRK16:
         case BP_KFIN16: return k16_batch_blocks(kind, 0, d);

@@ -147,6 +147,8 @@ int k16_tile_info(int t, int* cols, int* rows);
 int k16_syrk_tile_count();
 int k16_syrk_tile_size(int t);
 
+constexpr int kFinSub = 16;  // GEMM2 finish: workgroups per output tile
+
 // Batched builds (batch.hip drives; j_kernels.hip / k_kernels.hip launch).
 // One descriptor per molecule; all pointers are device pointers.
 struct MolDesc {
@@ -204,6 +206,16 @@ int tile_nb(int tile, int64_t nao, int64_t ncol, int64_t* nib, int64_t* nmb);
 
 // quantisation (quantize.hip)
 int quantize(const double* src, void* dst, int dtype, int64_t n, hipStream_t s);
+
+// A pointer read from memory (a molecule's descriptor) as one to global memory:
+// the compiler otherwise uses flat loads, which also count as LDS accesses, so
+// every wait for an LDS read of a product waited for the staged loads too.
+#ifdef __HIPCC__
+template <typename P>
+__device__ inline P* as_global(P* p) {
+    return (P*)(__attribute__((address_space(1))) P*)(uintptr_t)p;
+}
+#endif
 
 inline size_t dtype_size(int dt) { return dt == DFJK_F64 ? 8 : dt == DFJK_F32 ? 4 : 2; }
 

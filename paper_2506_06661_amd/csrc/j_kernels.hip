@@ -527,30 +527,30 @@ __global__ __launch_bounds__(kThreads) void jb_kernel(int kind, const MolDesc* _
     const int j = find_mol(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
     const int64_t lid = b - pl.prefix[j];
-    const TB* B = static_cast<const TB*>(d.B);
+    const TB* B = as_global(static_cast<const TB*>(d.B));
     switch (kind) {
         case BP_PACK:
-            pack_density_body(lid, d.D, d.nao, d.dt);
+            pack_density_body(lid, as_global(d.D), d.nao, as_global(d.dt));
             break;
         case BP_RHO: {
             const int64_t nrb = cdiv(d.naux, kBatchR);
             j_rho_red_body<TB, kBatchR, ACC_F64>(lid % nrb, (int)(lid / nrb), B, d.ldB, d.naux, d.npair,
-                                                 d.dt, nullptr, nullptr, d.chunk, (int)d.j_chunks,
-                                                 d.vec != 0, d.rho_part);
+                                                 as_global(d.dt), nullptr, nullptr, d.chunk, (int)d.j_chunks,
+                                                 d.vec != 0, as_global(d.rho_part));
             break;
         }
         case BP_RHO_FIN:
-            rho_finish_body(lid * kThreads + threadIdx.x, d.rho_part, d.naux, (int)d.j_chunks, d.rho,
+            rho_finish_body(lid * kThreads + threadIdx.x, as_global(d.rho_part), d.naux, (int)d.j_chunks, as_global(d.rho),
                             nullptr);
             break;
         case BP_OUT: {
             const int64_t ncb = cdiv(d.npair, (int64_t)kThreads * Elem<TB>::V);
-            j_out_red_body<TB, ACC_F64>(lid % ncb, (int)(lid / ncb), B, d.ldB, d.naux, d.npair, d.rho,
-                                        nullptr, nullptr, d.prows, d.vec != 0, d.jpart);
+            j_out_red_body<TB, ACC_F64>(lid % ncb, (int)(lid / ncb), B, d.ldB, d.naux, d.npair, as_global(d.rho),
+                                        nullptr, nullptr, d.prows, d.vec != 0, as_global(d.jpart));
             break;
         }
         case BP_JFIN:
-            j_finish_body(lid, d.jpart, d.npair, (int)d.j_splits, d.nao, d.J);
+            j_finish_body(lid, as_global(d.jpart), d.npair, (int)d.j_splits, d.nao, as_global(d.J));
             break;
         default:
             break;

@@ -1404,13 +1404,14 @@ __global__ __launch_bounds__(kT) void kb16_kernel(int kind, const MolDesc* __res
         const int64_t e = lid * kT + threadIdx.x;
         if (e < d.ncp16 * d.ldd16) {
             const int64_t i = e / d.ldd16, nu = e % d.ldd16;
-            const double v = (i < d.nocc && nu < d.nao) ? d.C[nu * d.nocc + i] : 0.0;
-            static_cast<H*>(d.Ct16)[i * d.rs16 + nu] = Mma16<H>::from_double(v);
+            const double v = (i < d.nocc && nu < d.nao) ? as_global(d.C)[nu * d.nocc + i] : 0.0;
+            as_global(static_cast<H*>(d.Ct16))[i * d.rs16 + nu] = Mma16<H>::from_double(v);
         }
     } else if (kind == BP_SYRK16) {
-        syrk16_body<H>(lid, static_cast<const H*>(d.X16), d.nao, d.ncp16, d.naux, d.pchunk16, d.ntl, d.kpart16);
+        syrk16_body<H>(lid, as_global(static_cast<const H*>(d.X16)), d.nao, d.ncp16, d.naux, d.pchunk16, d.ntl,
+                       as_global(d.kpart16));
     } else if (kind == BP_KFIN16) {
-        syrk16_finish_body<128>(lid, d.kpart16, d.nsplit16, d.ntl, d.nao, 2.0, d.K);
+        syrk16_finish_body<128>(lid, as_global(d.kpart16), d.nsplit16, d.ntl, d.nao, 2.0, as_global(d.K));
     }
 }
 
@@ -1423,9 +1424,9 @@ __global__ __launch_bounds__(128 * kG16WM, 4) void kb16_gemm1(const MolDesc* __r
     const int64_t b = xcd_lid(blockIdx.x, pl.nblk);
     const int j = find_mol16(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
-    g1p_body<H, kG16WM, 2, 2, FN>(b - pl.prefix[j], static_cast<const H*>(d.B), d.ldB, d.nao,
-                                  static_cast<const H*>(d.Ct16), d.rs16, d.nocc, d.ncp16,
-                                  static_cast<H*>(d.X16), cdiv(d.ncp16, G::BI), cdiv(d.nao, G::BM));
+    g1p_body<H, kG16WM, 2, 2, FN>(b - pl.prefix[j], as_global(static_cast<const H*>(d.B)), d.ldB, d.nao,
+                                  as_global(static_cast<const H*>(d.Ct16)), d.rs16, d.nocc, d.ncp16,
+                                  as_global(static_cast<H*>(d.X16)), cdiv(d.ncp16, G::BI), cdiv(d.nao, G::BM));
 }
 
 template <typename H>

@@ -16,6 +16,8 @@
 // with the (P,i) contraction split over workgroups; each split writes its
 // own partial tile, and a last kernel adds the splits in a fixed order and
 // mirrors the result, so K is bitwise reproducible.
+#include <algorithm>
+
 #include "internal.h"
 #include "mma.h"
 
@@ -27,7 +29,6 @@ constexpr int kThreads = 256;
 constexpr int KC = 16;      // contraction chunk held in LDS
 constexpr int SY_T = 128;   // SYRK output tile
 constexpr int64_t kMaxSum32 = 16384;  // longest FP32 running sum in the SYRK
-constexpr int kFinSub = 16;           // SYRK finish: workgroups per output tile
 
 __host__ __device__ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -239,21 +240,18 @@ __device__ inline int64_t xcd_logical(int64_t hw, int64_t nblk) {
 
 // X[(P*ncol + i)*ldx + mu] = sum_nu C[nu][i] B_P[nu][mu]
 // 1-D grid of nib * nmb * naux blocks; logical id -> (i block fastest, mu block, P)
-// Columns [ioff, iend) of the ncol orbital columns (a launch may cover part of
-// them with one tile and the rest with another).  ldc is a multiple of VC.
+// ldc is a multiple of VC.
 template <typename T, typename TS, int NI, int WM>
 __device__ __attribute__((always_inline)) inline void k_gemm1_body(int64_t lid, const TS* __restrict__ B, int64_t ldB, int64_t nao,
                                     const T* __restrict__ C, int64_t ldc, int64_t ncol,
-                                    T* __restrict__ X, int64_t ldx, int64_t nib, int64_t nmb,
-                                    int64_t ioff = 0, int64_t iend = -1) {
+                                    T* __restrict__ X, int64_t ldx, int64_t nib, int64_t nmb) {
     using S = G1<T, TS, NI, WM>;
     constexpr int BI = 16 * NI, BM = 64 * WM;
-    if (iend < 0) iend = ncol;
     __shared__ __attribute__((aligned(16))) T sC[2][KC][S::PC];
     __shared__ __attribute__((aligned(16))) T sB[2][KC][S::PB];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t ib = lid % nib, mb = (lid / nib) % nmb, P = lid / (nib * nmb);
-    const int64_t i0 = ioff + ib * BI, mu0 = mb * BM;
+    const int64_t i0 = ib * BI, mu0 = mb * BM;
     const TS* Bp = B + P * ldB;
 
     typename Mma<T>::acc_t acc[NI][WM];
@@ -304,7 +302,7 @@ __device__ __attribute__((always_inline)) inline void k_gemm1_body(int64_t lid, 
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int i = ti * 16 + Mma<T>::row(lane, r);
-                if (i0 + i < iend) Xp[(int64_t)i * ldx + m] = acc[ti][tj][r];
+                if (i0 + i < ncol) Xp[(int64_t)i * ldx + m] = acc[ti][tj][r];
             }
     }
 }
@@ -322,17 +320,15 @@ typedef float v16f_k __attribute__((ext_vector_type(16)));
 template <typename TS, int NJ, int WJ>
 __device__ __attribute__((always_inline)) inline void k_gemm1w_body(int64_t lid, const TS* __restrict__ B, int64_t ldB, int64_t nao,
                                      const float* __restrict__ C, int64_t ldc, int64_t ncol,
-                                     float* __restrict__ X, int64_t ldx, int64_t nib, int64_t nmb,
-                                     int64_t ioff = 0, int64_t iend = -1) {
+                                     float* __restrict__ X, int64_t ldx, int64_t nib, int64_t nmb) {
     constexpr int NI = 2 * NJ, WM = 2 * WJ;
     using S = G1<float, TS, NI, WM>;
     constexpr int BI = 16 * NI, BM = 64 * WM;
-    if (iend < 0) iend = ncol;
     __shared__ __attribute__((aligned(16))) float sC[2][KC][S::PC];
     __shared__ __attribute__((aligned(16))) float sB[2][KC][S::PB];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t ib = lid % nib, mb = (lid / nib) % nmb, P = lid / (nib * nmb);
-    const int64_t i0 = ioff + ib * BI, mu0 = mb * BM;
+    const int64_t i0 = ib * BI, mu0 = mb * BM;
     const TS* Bp = B + P * ldB;
 
     v16f_k acc[NJ][WJ];
@@ -382,7 +378,7 @@ __device__ __attribute__((always_inline)) inline void k_gemm1w_body(int64_t lid,
             for (int r = 0; r < 16; ++r) {
                 const int64_t i = i0 + ti * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                 const int64_t mu = mu0 + wave * 32 * WJ + tj * 32 + (lane & 31);
-                if (i < iend && mu < nao) X[(P * ncol + i) * ldx + mu] = acc[ti][tj][r];
+                if (i < ncol && mu < nao) X[(P * ncol + i) * ldx + mu] = acc[ti][tj][r];
             }
 }
 
@@ -390,9 +386,8 @@ template <typename TS, int NJ, int WJ>
 __global__ __launch_bounds__(kThreads) void k_gemm1w(const TS* __restrict__ B, int64_t ldB, int64_t nao,
                                                       const float* __restrict__ C, int64_t ldc, int64_t ncol,
                                                       float* __restrict__ X, int64_t ldx, int64_t nib,
-                                                      int64_t nmb, int64_t nblk, int64_t ioff, int64_t iend) {
-    k_gemm1w_body<TS, NJ, WJ>(xcd_logical(blockIdx.x, nblk), B, ldB, nao, C, ldc, ncol, X, ldx, nib, nmb,
-                              ioff, iend);
+                                                      int64_t nmb, int64_t nblk) {
+    k_gemm1w_body<TS, NJ, WJ>(xcd_logical(blockIdx.x, nblk), B, ldB, nao, C, ldc, ncol, X, ldx, nib, nmb);
 }
 
 // Waves per SIMD the register allocation is held to (LDS allows them):
@@ -411,9 +406,8 @@ template <typename T, typename TS, int NI, int WM>
 __global__ __launch_bounds__(kThreads, (g1_waves<T, TS, NI, WM>())) void k_gemm1(const TS* __restrict__ B, int64_t ldB, int64_t nao,
                                                      const T* __restrict__ C, int64_t ldc, int64_t ncol,
                                                      T* __restrict__ X, int64_t ldx, int64_t nib,
-                                                     int64_t nmb, int64_t nblk, int64_t ioff, int64_t iend) {
-    k_gemm1_body<T, TS, NI, WM>(xcd_logical(blockIdx.x, nblk), B, ldB, nao, C, ldc, ncol, X, ldx, nib, nmb, ioff,
-                                iend);
+                                                     int64_t nmb, int64_t nblk) {
+    k_gemm1_body<T, TS, NI, WM>(xcd_logical(blockIdx.x, nblk), B, ldB, nao, C, ldc, ncol, X, ldx, nib, nmb);
 }
 
 // ---------------------------------------------------------------- GEMM2 (SYRK)
@@ -727,15 +721,19 @@ __device__ __attribute__((always_inline)) inline void k_syrk_finish_body(int64_t
     }
 }
 
-// grid: kFinSub blocks per lower tile, each adding up a contiguous slice of it
+// Workgroups per output tile of the finish: kFinSub, or 64 (one element per
+// thread) when a few tiles would leave most CUs idle: a thread's sums over the
+// splits are a serial chain.
+int fin_sub(int64_t ntl) { return ntl * kFinSub < 256 ? 64 : kFinSub; }
+
+// grid: nsub blocks per lower tile, each adding up a contiguous slice of it
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_syrk_finish(const T* __restrict__ part, int64_t nsplit,
-                                                           int64_t ntl, int64_t nao, double scale,
+                                                           int64_t ntl, int64_t nao, double scale, int nsub,
                                                            double* __restrict__ K) {
-    constexpr int per = SY_T * SY_T / kFinSub;
-    const int sub = (int)(blockIdx.x % kFinSub);
-    k_syrk_finish_body<T>(blockIdx.x / kFinSub, sub * per, (sub + 1) * per, part, nsplit, ntl, nao, scale,
-                          K);
+    const int per = SY_T * SY_T / nsub;
+    const int sub = (int)(blockIdx.x % nsub);
+    k_syrk_finish_body<T>(blockIdx.x / nsub, sub * per, (sub + 1) * per, part, nsplit, ntl, nao, scale, K);
 }
 
 // Full-tile finish (two factors, no symmetry): K[mu][nu] = scale * sum_s
@@ -762,25 +760,23 @@ __global__ __launch_bounds__(kThreads) void k_pair_finish(const T* __restrict__ 
 }
 
 template <typename T, typename TS, int NI, int WM>
-int launch_gemm1(const dfjk_ctx* h, const void* C, int64_t ldc, int64_t ncol, void* X, int64_t ldx, int64_t ioff,
-                 int64_t iend) {
-    const int64_t nib = cdiv(iend - ioff, 16 * NI), nmb = cdiv(h->nao, 64 * WM);
+int launch_gemm1(const dfjk_ctx* h, const void* C, int64_t ldc, int64_t ncol, void* X, int64_t ldx) {
+    const int64_t nib = cdiv(ncol, 16 * NI), nmb = cdiv(h->nao, 64 * WM);
     const int64_t nblk = nib * nmb * h->naux;
     k_gemm1<T, TS, NI, WM><<<dim3((unsigned)nblk), kThreads, 0, h->stream>>>(
         static_cast<const TS*>(h->B), h->ldB, h->nao, static_cast<const T*>(C), ldc, ncol,
-        static_cast<T*>(X), ldx, nib, nmb, nblk, ioff, iend);
+        static_cast<T*>(X), ldx, nib, nmb, nblk);
     DFJK_LAUNCH_CHECK("k_gemm1");
     return DFJK_OK;
 }
 
 template <typename TS, int NJ, int WJ>
-int launch_gemm1w(const dfjk_ctx* h, const void* C, int64_t ldc, int64_t ncol, void* X, int64_t ldx, int64_t ioff,
-                  int64_t iend) {
-    const int64_t nib = cdiv(iend - ioff, 32 * NJ), nmb = cdiv(h->nao, 128 * WJ);
+int launch_gemm1w(const dfjk_ctx* h, const void* C, int64_t ldc, int64_t ncol, void* X, int64_t ldx) {
+    const int64_t nib = cdiv(ncol, 32 * NJ), nmb = cdiv(h->nao, 128 * WJ);
     const int64_t nblk = nib * nmb * h->naux;
     k_gemm1w<TS, NJ, WJ><<<dim3((unsigned)nblk), kThreads, 0, h->stream>>>(
         static_cast<const TS*>(h->B), h->ldB, h->nao, static_cast<const float*>(C), ldc, ncol,
-        static_cast<float*>(X), ldx, nib, nmb, nblk, ioff, iend);
+        static_cast<float*>(X), ldx, nib, nmb, nblk);
     DFJK_LAUNCH_CHECK("k_gemm1w");
     return DFJK_OK;
 }
@@ -788,7 +784,7 @@ int launch_gemm1w(const dfjk_ctx* h, const void* C, int64_t ldc, int64_t ncol, v
 // Compiled GEMM1 tiles: (NI, WM) = (i tiles of 16, mu tiles of 16 per wave),
 // one launcher per B storage type (FP64 on the FP64 matrix cores; FP32, BF16
 // and FP16 dequantised exactly on load and run on the FP32 matrix cores).
-typedef int (*G1Launch)(const dfjk_ctx*, const void*, int64_t, int64_t, void*, int64_t, int64_t, int64_t);
+typedef int (*G1Launch)(const dfjk_ctx*, const void*, int64_t, int64_t, void*, int64_t);
 struct G1Tile {
     int ni, wm;
     G1Launch by_dtype[4];  // indexed by dfjk_dtype
@@ -816,11 +812,11 @@ const G1Tile kG1Tiles[] = {
     G1T(1, 2), G1T(2, 2), G1T(3, 2), G1T(4, 2), G1T(5, 2), G1T(6, 2),
     G1T(7, 2), G1T(8, 2), G1T(13, 1), G1T(4, 4), G1T(7, 1), G1T(5, 1), G1T(6, 1), G1T(3, 1),
     G1W(2, 1), G1W(1, 2), G1W(2, 2),
+    G1T(1, 1), G1T(2, 1), G1T(4, 1), G1T(8, 1), G1T(9, 1), G1T(10, 1), G1T(11, 1), G1T(12, 1),
 };
 #undef G1T
 #undef G1W
 constexpr int kNumG1Tiles = sizeof(kG1Tiles) / sizeof(kG1Tiles[0]);
-constexpr int kFirstRestTile = 12;  // (6,1) and (3,1): defaults only for the rest of a split
 
 // Copy of C (nao x ncol) with rows ldc apart, FP32 with one rounding per
 // element (the columns past ncol stay as they are: GEMM1 does not store their
@@ -853,55 +849,30 @@ size_t c_bytes(const dfjk_ctx* h, int64_t ncol, int n) {
     return (f32 ? 4 : 8) * (size_t)(n * h->nao * c_stride(ncol, f32));
 }
 
-// Default tile: least padded work, where each extra i block costs another
-// read of the B tile (weight 1/2 of a padded column block), among the tiles
-// that keep two waves per SIMD (FP64 sweep on MI355X, nao=1024, nocc=200:
-// (7,1) 43.8 TFLOP/s, (5,2) 43.5, (13,1) 40.4, (1,2) 32.6).
-// FP32 compute (FP32/BF16/FP16 storage) allows up to 14 accumulator tiles
-// (sweep at nocc=200, FP32 B, one element per staging load: (13,1) and
-// (7,2) 79.7 TFLOP/s, (5,2) 76.6, (7,1) 76.0, (5,1) 68.7, (8,2) 72.5,
-// (4,4) 62.5).
-int pick_g1_tile(int64_t ncol, bool f32 = false) {
+// Default tile: one launch of tiles 64 basis functions wide (nao is padded to
+// 64 only; two i blocks or fewer take 128, a wavefront needs independent
+// products) and ni <= 13 blocks of 16 orbitals (13 accumulator blocks keep two
+// FP64 or four FP32 wavefronts on a SIMD), ni chosen for the least padded
+// columns, each tile costing another read of B's chunk: weight 1 + w / ni.
+// Counting padded columns, FP32 tiles of 13 / 7 / 5 / 3 blocks run at 125 / 122 /
+// 119 / 112 TFLOP/s (w = 0.35), the FP64 ones at 57 / 58 / 61 / 55 (w = 0.1: the
+// matrix cores bound them all).  Useful TFLOP/s on MI355X, the rule's tile
+// first: nocc=200, nao=1024, FP32: (13,1) 120, (7,2) 110, (5,2) 101; FP64: (13,1)
+// 55, (7,1) + (6,1) in two launches, B read twice, 55, (5,2) 48; nocc=96,
+// nao=500, FP64: (6,1) 55, (3,2) 49; 400 columns, nao=400, FP64: (5,1) 52, (13,1) 48.
+int pick_g1_tile(int64_t ncol, bool f32) {
     int best = 0;
     double best_cost = 1e300;
-    for (int t = 0; t < kFirstRestTile; ++t) {
-        const int ni = kG1Tiles[t].ni, wm = kG1Tiles[t].wm;
-        if (ni * wm > (f32 ? 14 : 7)) continue;  // larger accumulator sets leave one wave per SIMD
-        const double padded = (double)(cdiv(ncol, 16 * ni) * 16 * ni);
-        const double cost = padded * (1.0 + 0.5 / ni);
+    for (int t = 0; t < kNumG1Tiles; ++t) {
+        const int ni = kG1Tiles[t].ni;
+        if (ni > 13 || kG1Tiles[t].wm != (ni <= 2 ? 2 : 1) || !kG1Tiles[t].by_dtype[DFJK_F64]) continue;
+        const double cost = (double)(cdiv(ncol, 16 * ni) * 16 * ni) * (1.0 + (f32 ? 0.35 : 0.1) / ni);
         if (cost < best_cost) {
             best_cost = cost;
             best = t;
         }
     }
     return best;
-}
-
-// Default for the single build: one tile, or the default tile over the
-// first columns (a whole number of its widths) and the narrowest tile with
-// one wavefront row (WM = 1) over the rest, when that pads fewer columns
-// (nocc=200: FP64 112 + 96 = 208 columns computed instead of 224; FP32
-// 160 + 48 = 208 instead of 240).
-struct G1Split {
-    int t0, t1;
-    int64_t n0;  // columns [0, n0) with tile t0, [n0, ncol) with t1
-};
-G1Split pick_g1_split(int64_t ncol, bool f32) {
-    const int single = pick_g1_tile(ncol, f32);
-    G1Split sp{single, single, ncol};
-    const int64_t w = 16 * kG1Tiles[single].ni;
-    if (kG1Tiles[single].wm != 1) return sp;
-    const int64_t padded_single = cdiv(ncol, w) * w;
-    const int64_t n0 = (ncol / w) * w, rest = ncol - n0;
-    if (n0 == 0 || rest == 0) return sp;
-    int best = -1;
-    for (int t = 0; t < kNumG1Tiles; ++t) {
-        const int ni = kG1Tiles[t].ni;
-        if (kG1Tiles[t].wm != 1 || 16 * ni < rest || ni > kG1Tiles[single].ni) continue;
-        if (best < 0 || ni < kG1Tiles[best].ni) best = t;
-    }
-    if (best >= 0 && n0 + 16 * kG1Tiles[best].ni < padded_single) sp = G1Split{single, best, n0};
-    return sp;
 }
 
 // X = (B_P C)^T for every P, with the handle's forced tile or the default
@@ -914,27 +885,32 @@ int run_gemm1(dfjk_ctx* h, const void* C, int64_t ncol, void* X, int64_t ldx, bo
             set_error("GEMM1 tile %d has no FP64 form", h->g1_tile);
             return DFJK_E_INVALID;
         }
-        return f(h, C, ldc, ncol, X, ldx, 0, ncol);
+        return f(h, C, ldc, ncol, X, ldx);
     }
-    G1Split sp = pick_g1_split(ncol, f32);
-    int rc = kG1Tiles[sp.t0].by_dtype[h->dtype](h, C, ldc, ncol, X, ldx, 0, sp.n0);
-    if (!rc && sp.n0 < ncol) rc = kG1Tiles[sp.t1].by_dtype[h->dtype](h, C, ldc, ncol, X, ldx, sp.n0, ncol);
-    return rc;
+    return kG1Tiles[pick_g1_tile(ncol, f32)].by_dtype[h->dtype](h, C, ldc, ncol, X, ldx);
 }
 
-// Splits of a GEMM2 contraction of nrows terms over ntl output tiles: about
-// 8192 workgroups (FP64) or 16384 (FP32, whose partials are half the size),
-// and for FP32 no running sum longer than kMaxSum32 terms (the split partials
-// are added in FP64).  On MI355X at nao=1024, naux=4096, nocc=200 the FP64
-// SYRK took 20.4 / 18.4 / 17.4 / 16.8 / 16.5 ms for about 1024 / 2048 / 4096 /
-// 8192 / 16384 workgroups while the finish, which reads every partial tile,
-// grew from 0.07 ms (2048) to 0.24 (8192) and 0.44 (16384); the FP32 SYRK took
-// 10.3 / 9.45 / 9.24 ms for 2048 / 8192 / 16384 (finish 0.04 / 0.14 / 0.25).
+// Splits of a GEMM2 contraction of nrows terms over ntl output tiles.
+// FP64: 512 workgroups are resident; about 4096 of them even out the tiles'
+// unequal lengths, and up to 8192 while a split keeps 2048 rows.  Every split
+// costs a partial tile to write and to add: nao=1024, naux=4096, nocc=200 GEMM2 +
+// finish took 16.9 / 15.3 / 14.7 / 14.4 / 14.5 ms with about 1024 / 2048 / 4096 /
+// 8192 / 16384 workgroups, two factors at nao=500 2.36 / 2.08 / 2.10 / 2.21 / 2.28.
+// Short contractions keep 384 rows a split (naux=103 at nao=1024) unless that
+// leaves CUs idle: then down to
+// kMinRows64 rows: nao=64, naux=256, nocc=16 GEMM2 + finish 0.054 -> 0.022 ms,
+// nao=128, naux=512, nocc=24 0.057 -> 0.030.
+// FP32: about 16384 workgroups, no split shorter than 384 rows and no running
+// sum longer than kMaxSum32 terms (the split partials are added in FP64).
+constexpr int64_t kMinRows64 = 48;
 void syrk_splits(int64_t nrows, int64_t ntl, bool f32, int64_t* nsplit_out, int64_t* kchunk_out) {
-    int64_t nsplit = cdiv(f32 ? 16384 : 8192, ntl);
-    if (f32 && nsplit < cdiv(nrows, kMaxSum32)) nsplit = cdiv(nrows, kMaxSum32);
-    const int64_t max_split = cdiv(nrows, 384);  // splits of at least 384 rows (short contractions)
-    if (nsplit > max_split) nsplit = max_split;
+    int64_t nsplit;
+    if (f32) {
+        nsplit = std::min(std::max(cdiv(16384, ntl), cdiv(nrows, kMaxSum32)), cdiv(nrows, 384));
+    } else {
+        nsplit = std::max(cdiv(4096, ntl), std::min(cdiv(8192, ntl), nrows / 2048));
+        nsplit = std::min(nsplit, std::max(cdiv(nrows, 384), std::min(cdiv(512, ntl), cdiv(nrows, kMinRows64))));
+    }
     if (nsplit < 1) nsplit = 1;
     const int64_t kchunk = cdiv(cdiv(nrows, nsplit), KC) * KC;
     *nsplit_out = cdiv(nrows, kchunk);
@@ -990,8 +966,9 @@ int k_build_t(dfjk_ctx* h, const double* C_in, int64_t ncol, const double* sign,
     h->prof.end(PH_K_SYRK, h->stream);
     DFJK_LAUNCH_CHECK("k_syrk");
     h->prof.begin(PH_K_FINISH, h->stream);
-    k_syrk_finish<T><<<dim3((unsigned)(ntl * kFinSub)), kThreads, 0, h->stream>>>(part, nsplit, ntl, h->nao,
-                                                                                   scale, K);
+    const int nsub = fin_sub(ntl);
+    k_syrk_finish<T><<<dim3((unsigned)(ntl * nsub)), kThreads, 0, h->stream>>>(part, nsplit, ntl, h->nao, scale,
+                                                                                nsub, K);
     h->prof.end(PH_K_FINISH, h->stream);
     h->prof.end(PH_K, h->stream);
     DFJK_LAUNCH_CHECK("k_syrk_finish");
@@ -1041,9 +1018,10 @@ int k_build_pair_t(dfjk_ctx* h, const double* L_in, const double* R_in, int64_t 
     h->prof.end(PH_K_SYRK, h->stream);
     DFJK_LAUNCH_CHECK("k_syrk (two factors)");
     h->prof.begin(PH_K_FINISH, h->stream);
+    const int nsub = fin_sub(ntl);
     if (sym)
-        k_syrk_finish<T><<<dim3((unsigned)(ntl * kFinSub)), kThreads, 0, h->stream>>>(part, nsplit, ntl,
-                                                                                       h->nao, scale, K);
+        k_syrk_finish<T><<<dim3((unsigned)(ntl * nsub)), kThreads, 0, h->stream>>>(part, nsplit, ntl, h->nao, scale,
+                                                                                    nsub, K);
     else
         k_pair_finish<T><<<dim3((unsigned)(ntl * kFinSub)), kThreads, 0, h->stream>>>(part, nsplit, nt, h->nao,
                                                                                        scale, K);
@@ -1064,32 +1042,31 @@ __device__ inline int find_mol_k(const int64_t* __restrict__ prefix, int n, int6
     return lo;
 }
 
-// 4 waves per SIMD, as the FP32 GEMM2 it runs (256 molecules: 69.2 -> 67.0 ms
-// per eager build)
-__global__ __launch_bounds__(kThreads, 4) void kb_kernel(int kind, const MolDesc* __restrict__ mols,
-                                                       PhaseList pl) {
-    // SYRK blocks are renumbered so runs of consecutive ids share an XCD
-    const int64_t b = kind == BP_SYRK ? xcd_logical(blockIdx.x, pl.nblk) : (int64_t)blockIdx.x;
+__global__ __launch_bounds__(kThreads) void kb_kernel(int kind, const MolDesc* __restrict__ mols, PhaseList pl) {
+    const int64_t b = blockIdx.x;
     const int j = find_mol_k(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
     const int64_t lid = b - pl.prefix[j];
-    switch (kind) {
-        case BP_CF32: {
-            const int64_t e = lid * kThreads + threadIdx.x;
-            if (e < d.nao * d.nocc) d.Cf[e / d.nocc * d.ldcf + e % d.nocc] = (float)d.C[e];
-            break;
-        }
-        case BP_SYRK:
-            k_syrk_body<float, SY_SYM, false>(lid, d.X, d.ldx, d.naux * d.nocc, d.nao, d.nocc, nullptr, d.kchunk,
-                                             d.ntl,
-                               d.kpart);
-            break;
-        case BP_KFIN:
-            k_syrk_finish_body<float>(lid, 0, SY_T * SY_T, d.kpart, d.nsplit, d.ntl, d.nao, 2.0, d.K);
-            break;
-        default:
-            break;
+    if (kind == BP_CF32) {
+        const int64_t e = lid * kThreads + threadIdx.x;
+        if (e < d.nao * d.nocc) as_global(d.Cf)[e / d.nocc * d.ldcf + e % d.nocc] = (float)as_global(d.C)[e];
+    } else if (kind == BP_KFIN) {
+        constexpr int per = SY_T * SY_T / kFinSub;
+        const int sub = (int)(lid % kFinSub);
+        k_syrk_finish_body<float>(lid / kFinSub, sub * per, (sub + 1) * per, as_global(d.kpart), d.nsplit, d.ntl,
+                                  d.nao, 2.0, as_global(d.K));
     }
+}
+
+// GEMM2 of every molecule: 4 waves per SIMD, as the single one.  Blocks are
+// renumbered so runs of consecutive ids share an XCD.  A kernel of its own:
+// beside the other phases its registers spilled.
+__global__ __launch_bounds__(kThreads, 4) void kb_syrk(const MolDesc* __restrict__ mols, PhaseList pl) {
+    const int64_t b = xcd_logical(blockIdx.x, pl.nblk);
+    const int j = find_mol_k(pl.prefix, pl.n, b);
+    const MolDesc& d = mols[pl.ids[j]];
+    k_syrk_body<float, SY_SYM, false>(b - pl.prefix[j], as_global(d.X), d.ldx, d.naux * d.nocc, d.nao, d.nocc,
+                                      nullptr, d.kchunk, d.ntl, as_global(d.kpart));
 }
 
 // Batched GEMM1 tiles with at most 8 accumulator blocks are held to 5 waves
@@ -1103,8 +1080,8 @@ __global__ __launch_bounds__(kThreads, (kb_g1_waves<NI, WM>())) void kb_gemm1(co
     const int64_t b = xcd_logical(blockIdx.x, pl.nblk);
     const int j = find_mol_k(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
-    k_gemm1_body<float, TS, NI, WM>(b - pl.prefix[j], static_cast<const TS*>(d.B), d.ldB, d.nao, d.Cf,
-                                        d.ldcf, d.nocc, d.X, d.ldx, d.g1_nib, d.g1_nmb);
+    k_gemm1_body<float, TS, NI, WM>(b - pl.prefix[j], as_global(static_cast<const TS*>(d.B)), d.ldB, d.nao,
+                                    as_global(d.Cf), d.ldcf, d.nocc, as_global(d.X), d.ldx, d.g1_nib, d.g1_nmb);
 }
 
 template <int NI, int WM>
@@ -1125,8 +1102,8 @@ __global__ __launch_bounds__(kThreads) void kb_gemm1w(const MolDesc* __restrict_
     const int64_t b = xcd_logical(blockIdx.x, pl.nblk);
     const int j = find_mol_k(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
-    k_gemm1w_body<TS, NJ, WJ>(b - pl.prefix[j], static_cast<const TS*>(d.B), d.ldB, d.nao, d.Cf, d.ldcf,
-                                 d.nocc, d.X, d.ldx, d.g1_nib, d.g1_nmb);
+    k_gemm1w_body<TS, NJ, WJ>(b - pl.prefix[j], as_global(static_cast<const TS*>(d.B)), d.ldB, d.nao,
+                              as_global(d.Cf), d.ldcf, d.nocc, as_global(d.X), d.ldx, d.g1_nib, d.g1_nmb);
 }
 
 template <int NJ, int WJ>
@@ -1147,7 +1124,8 @@ typedef int (*KbLaunch)(hipStream_t, int, const MolDesc*, const PhaseList&);
 const KbLaunch kKbTiles[] = {KBT(1, 2), KBT(2, 2), KBT(3, 2), KBT(4, 2), KBT(5, 2), KBT(6, 2),
                              KBT(7, 2), KBT(8, 2), KBT(13, 1), KBT(4, 4), KBT(7, 1), KBT(5, 1),
                              KBT(6, 1), KBT(3, 1), launch_kb_gemm1w<2, 1>, launch_kb_gemm1w<1, 2>,
-                             launch_kb_gemm1w<2, 2>};
+                             launch_kb_gemm1w<2, 2>, KBT(1, 1), KBT(2, 1), KBT(4, 1), KBT(8, 1), KBT(9, 1),
+                             KBT(10, 1), KBT(11, 1), KBT(12, 1)};
 #undef KBT
 static_assert(sizeof(kKbTiles) / sizeof(kKbTiles[0]) == kNumG1Tiles, "tile tables differ");
 
@@ -1156,7 +1134,10 @@ static_assert(sizeof(kKbTiles) / sizeof(kKbTiles[0]) == kNumG1Tiles, "tile table
 int k_batch_phase(hipStream_t st, int kind, int dtype, const MolDesc* mols, const PhaseList& pl) {
     (void)dtype;
     if (pl.nblk <= 0) return DFJK_OK;
-    kb_kernel<<<dim3((unsigned)pl.nblk), kThreads, 0, st>>>(kind, mols, pl);
+    if (kind == BP_SYRK)
+        kb_syrk<<<dim3((unsigned)pl.nblk), kThreads, 0, st>>>(mols, pl);
+    else
+        kb_kernel<<<dim3((unsigned)pl.nblk), kThreads, 0, st>>>(kind, mols, pl);
     DFJK_LAUNCH_CHECK("kb_kernel");
     return DFJK_OK;
 }
