@@ -75,40 +75,50 @@ __global__ __launch_bounds__(256) void gemm_kernel(int64_t M, int64_t N, int64_t
 
 // C = alpha A B + beta C for large row-major FP64 products (no transposes):
 // 128 x 128 tile per workgroup, 2 x 2 waves of 64 x 64 (4 x 4 steps of
-// 16 x 16 x 4 per wavefront, the accumulators in the matrix-core registers),
-// K in 16-deep chunks double-buffered in LDS with the next chunk loaded into
-// registers while the current one is multiplied.  Loads are pairs of
-// doubles (rows start 16-byte aligned when lda, ldb are even and A, B are
-// 16-byte aligned; otherwise element loads).  The k order of every sum is
-// that of gemm_kernel (4-deep steps in increasing k).
-constexpr int WT = 128, WK = 16;
-template <bool PAIRS>
+// 16 x 16 x 4 per wavefront), K in 16-deep chunks double-buffered in LDS.  The
+// matrix cores bound it (64 cycles a step), so a chunk holds only 8 16-byte
+// loads from uniform bases at 32-bit offsets that stay the same, their stores
+// and the products; a chunk is loaded a whole chunk of products before its
+// store; tiles and chunks at the edges take a path of their own.  LDS rows are
+// k, 144 doubles apart (16 modulo 32: the two rows a read serves at once use
+// different banks); A arrives along k and is stored transposed, column m of row
+// k at m ^ 2 (k / 2 % 8).  The k order of every sum is that of gemm_kernel
+// (4-deep steps in increasing k).  MI355X: rank-256 updates of 73920 columns
+// 38 TFLOP/s (C read and written in each), 26 with element-wise LDS stores and
+// bounds checks in the loop.
+constexpr int WT = 128, WK = 16, WP = WT + 16;
+__device__ inline int wide_swz(int k) { return 2 * ((k >> 1) & 7); }
+
 __global__ __launch_bounds__(256, 2) void gemm_nn_wide(int64_t M, int64_t N, int64_t K, double alpha,
                                                         const double* __restrict__ A, int64_t lda,
                                                         const double* __restrict__ B, int64_t ldb, double beta,
                                                         double* __restrict__ C, int64_t ldc) {
-    __shared__ double sA[2][WK][WT + 2];  // sA[k][m] = A[m0 + m][k0 + k]
-    __shared__ double sB[2][WK][WT + 2];  // sB[k][n] = B[k0 + k][n0 + n]
+    __shared__ __attribute__((aligned(16))) double sA[2][WK][WP];  // sA[k][m] = A[m0 + m][k0 + k]
+    __shared__ __attribute__((aligned(16))) double sB[2][WK][WP];  // sB[k][n] = B[k0 + k][n0 + n]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave >> 1, wn = wave & 1, lc = lane & 15;
     const int64_t m0 = (int64_t)blockIdx.y * WT, n0 = (int64_t)blockIdx.x * WT;
     // thread's pairs: A rows m0 + tid/8 + 32 j at k pair 2 (tid%8); B rows
     // tid/64 + 4 j at n pair 2 (tid%64)
     const int am = tid >> 3, akp = 2 * (tid & 7), bk = tid >> 6, bnp = 2 * (tid & 63);
     const bool full_mn = m0 + WT <= M && n0 + WT <= N;
     double ra[4][2], rb[4][2];
+    int64_t aoff[4], boff[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        aoff[j] = (am + 32 * j) * lda + akp;
+        boff[j] = (bk + 4 * j) * ldb + bnp;
+    }
     auto load = [&](int64_t k0) {
-        if (PAIRS && full_mn && k0 + WK <= K) {
+        const double *Ak = A + m0 * lda + k0, *Bk = B + k0 * ldb + n0;
+        if (__builtin_expect(full_mn && k0 + WK <= K, 1)) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const double2 va = *reinterpret_cast<const double2*>(A + (m0 + am + 32 * j) * lda + k0 + akp);
-                const double2 vb = *reinterpret_cast<const double2*>(B + (k0 + bk + 4 * j) * ldb + n0 + bnp);
-                ra[j][0] = va.x;
-                ra[j][1] = va.y;
-                rb[j][0] = vb.x;
-                rb[j][1] = vb.y;
+                __builtin_memcpy(ra[j], Ak + aoff[j], 16);
+                __builtin_memcpy(rb[j], Bk + boff[j], 16);
             }
         } else {
+            asm volatile("" ::: "memory");  // stays a branch
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -123,10 +133,9 @@ __global__ __launch_bounds__(256, 2) void gemm_nn_wide(int64_t M, int64_t N, int
     auto store = [&](int buf) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            sA[buf][akp][am + 32 * j] = ra[j][0];
-            sA[buf][akp + 1][am + 32 * j] = ra[j][1];
-            sB[buf][bk + 4 * j][bnp] = rb[j][0];
-            sB[buf][bk + 4 * j][bnp + 1] = rb[j][1];
+            sA[buf][akp][(am + 32 * j) ^ wide_swz(akp)] = ra[j][0];
+            sA[buf][akp + 1][(am + 32 * j) ^ wide_swz(akp)] = ra[j][1];
+            __builtin_memcpy(&sB[buf][bk + 4 * j][bnp], rb[j], 16);
         }
     };
     v4d acc[4][4];
@@ -134,44 +143,96 @@ __global__ __launch_bounds__(256, 2) void gemm_nn_wide(int64_t M, int64_t N, int
     for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
-    const int64_t nk = cdiv(K, WK);
+    const int nk = (int)cdiv(K, WK);
     load(0);
     store(0);
+    if (nk > 1) load(WK);
     __syncthreads();
-    for (int64_t kc = 0; kc < nk; ++kc) {
+    for (int kc = 0; kc < nk; ++kc) {
         const int buf = kc & 1;
-        const bool more = kc + 1 < nk;
-        if (more) load((kc + 1) * WK);
 #pragma unroll
         for (int kk = 0; kk < WK / 4; ++kk) {
-            const int kr = kk * 4 + (lane >> 4);
+            const int kr = kk * 4 + (lane >> 4), ca = lc ^ (4 * kk + 2 * (lane >> 5));
             double a[4], b[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                a[q] = sA[buf][kr][wm * 64 + q * 16 + (lane & 15)];
-                b[q] = sB[buf][kr][wn * 64 + q * 16 + (lane & 15)];
+                a[q] = sA[buf][kr][wm * 64 + q * 16 + ca];
+                b[q] = sB[buf][kr][wn * 64 + q * 16 + lc];
             }
 #pragma unroll
             for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
                 for (int tj = 0; tj < 4; ++tj) acc[ti][tj] = Mma<double>::step(a[ti], b[tj], acc[ti][tj]);
         }
-        if (more) store(buf ^ 1);
+        if (kc + 1 < nk) {
+            store(buf ^ 1);
+            if (kc + 2 < nk) load((int64_t)(kc + 2) * WK);
+        }
         __syncthreads();
     }
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
+    for (int tj = 0; tj < 4; ++tj) {
+        const int64_t gn = n0 + wn * 64 + tj * 16 + lc;
+        if (gn >= N) continue;
 #pragma unroll
-        for (int tj = 0; tj < 4; ++tj)
+        for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int64_t gm = m0 + wm * 64 + ti * 16 + Mma<double>::row(lane, r);
-                const int64_t gn = n0 + wn * 64 + tj * 16 + (lane & 15);
-                if (gm < M && gn < N) {
+                if (gm < M) {
                     const double old = beta == 0.0 ? 0.0 : beta * C[gm * ldc + gn];
                     C[gm * ldc + gn] = alpha * acc[ti][tj][r] + old;
                 }
             }
+    }
+}
+
+// C = alpha op(A) op(B) + beta C for small products (the SCF's nao x nao ones):
+// one 16 x 16 tile per workgroup, the contraction split over its four
+// wavefronts and added in order, operands straight from L2 into the
+// matrix-core layout.  Latency bounds these, so every load is independent and
+// there is one barrier: nao=128 4 us (the 64 and 128 tiles leave one to four
+// workgroups with a serial loop of staged chunks: 7 to 16 and 24 us).
+template <bool TA, bool TB>
+__global__ __launch_bounds__(256) void gemm_small(int M, int N, int K, double alpha, const double* __restrict__ A,
+                                                  int64_t lda, const double* __restrict__ B, int64_t ldb, double beta,
+                                                  double* __restrict__ C, int64_t ldc) {
+    __shared__ double red[4][16][17];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
+    const int gm = min(m0 + (lane & 15), M - 1), gn = min(n0 + (lane & 15), N - 1);
+    const int per = (int)cdiv(cdiv(K, 4), 4) * 4;  // contraction terms per wavefront, in whole steps
+    const int kb = wave * per, ke = min(kb + per, K);
+    const double *Ak = TA ? A + gm : A + gm * lda, *Bk = TB ? B + gn * ldb : B + gn;
+    const int64_t sa = TA ? lda : 1, sb = TB ? 1 : ldb;
+    v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
+    int k0 = kb;
+    for (; k0 + 32 <= ke; k0 += 32) {  // eight steps' loads in flight
+        double a[8], b[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int64_t k = k0 + 4 * j + (lane >> 4);
+            a[j] = Ak[k * sa];
+            b[j] = Bk[k * sb];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc = Mma<double>::step(a[j], b[j], acc);
+    }
+    for (; k0 < ke; k0 += 4) {
+        const int k = k0 + (lane >> 4);
+        double a = 0.0, b = 0.0;
+        if (k < ke) a = Ak[k * sa], b = Bk[k * sb];
+        acc = Mma<double>::step(a, b, acc);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wave][Mma<double>::row(lane, r)][lane & 15] = acc[r];
+    __syncthreads();
+    const int r = tid >> 4, c = tid & 15;
+    if (m0 + r < M && n0 + c < N) {
+        const double v = ((red[0][r][c] + red[1][r][c]) + red[2][r][c]) + red[3][r][c];
+        double* dst = C + (m0 + r) * ldc + n0 + c;
+        *dst = alpha * v + (beta == 0.0 ? 0.0 : beta * *dst);
+    }
 }
 
 // ---------------------------------------------------------------- network products
@@ -646,17 +707,33 @@ __global__ void symmetrize(const double* __restrict__ X, int64_t n, double* __re
 
 }  // namespace
 
+// Largest result edge of gemm_small.  Square products, us: 256: 5 small, 41 wide
+// (A B^T: 6, 11); 448: 18, 80 (6, 20); 640: 41, 98 (15, 24).  Each
+// operand is read from L2 once per 16 rows or columns, not 64 or 128, so its lead
+// shrinks with size; not measured beyond 640.
+constexpr int64_t kSmallN = 640;
+
 int dgemm(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha,
           const double* A, int64_t lda, const double* B, int64_t ldb, double beta, double* C,
           int64_t ldc) {
+    // small results: the larger tiles would leave most CUs idle
+    if (M <= kSmallN && N <= kSmallN && K <= 4 * kSmallN) {
+        const dim3 grid((unsigned)cdiv(N, 16), (unsigned)cdiv(M, 16));
+        const int m = (int)M, n = (int)N, k = (int)K;
+        if (!ta && !tb)
+            gemm_small<false, false><<<grid, 256, 0, st>>>(m, n, k, alpha, A, lda, B, ldb, beta, C, ldc);
+        else if (ta && !tb)
+            gemm_small<true, false><<<grid, 256, 0, st>>>(m, n, k, alpha, A, lda, B, ldb, beta, C, ldc);
+        else if (!ta && tb)
+            gemm_small<false, true><<<grid, 256, 0, st>>>(m, n, k, alpha, A, lda, B, ldb, beta, C, ldc);
+        else
+            gemm_small<true, true><<<grid, 256, 0, st>>>(m, n, k, alpha, A, lda, B, ldb, beta, C, ldc);
+        DFJK_LAUNCH_CHECK("gemm_small");
+        return DFJK_OK;
+    }
     if (!ta && !tb && M >= WT && N >= WT && K >= WK) {
         const dim3 grid((unsigned)cdiv(N, WT), (unsigned)cdiv(M, WT));
-        const bool pairs = lda % 2 == 0 && ldb % 2 == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0 &&
-                           (reinterpret_cast<uintptr_t>(B) & 15) == 0;
-        if (pairs)
-            gemm_nn_wide<true><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-        else
-            gemm_nn_wide<false><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
+        gemm_nn_wide<<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
         DFJK_LAUNCH_CHECK("gemm_nn_wide");
         return DFJK_OK;
     }
