@@ -903,7 +903,7 @@ int run_gemm1(dfjk_ctx* h, const void* C, int64_t ncol, void* X, int64_t ldx, bo
 // FP32: about 16384 workgroups, no split shorter than 384 rows and no running
 // sum longer than kMaxSum32 terms (the split partials are added in FP64).
 constexpr int64_t kMinRows64 = 48;
-void syrk_splits(int64_t nrows, int64_t ntl, bool f32, int64_t* nsplit_out, int64_t* kchunk_out) {
+int64_t syrk_max_splits(int64_t nrows, int64_t ntl, bool f32) {  // never falls as nrows grows
     int64_t nsplit;
     if (f32) {
         nsplit = std::min(std::max(cdiv(16384, ntl), cdiv(nrows, kMaxSum32)), cdiv(nrows, 384));
@@ -911,7 +911,10 @@ void syrk_splits(int64_t nrows, int64_t ntl, bool f32, int64_t* nsplit_out, int6
         nsplit = std::max(cdiv(4096, ntl), std::min(cdiv(8192, ntl), nrows / 2048));
         nsplit = std::min(nsplit, std::max(cdiv(nrows, 384), std::min(cdiv(512, ntl), cdiv(nrows, kMinRows64))));
     }
-    if (nsplit < 1) nsplit = 1;
+    return std::max<int64_t>(nsplit, 1);
+}
+void syrk_splits(int64_t nrows, int64_t ntl, bool f32, int64_t* nsplit_out, int64_t* kchunk_out) {
+    const int64_t nsplit = syrk_max_splits(nrows, ntl, f32);
     const int64_t kchunk = cdiv(cdiv(nrows, nsplit), KC) * KC;
     *nsplit_out = cdiv(nrows, kchunk);
     *kchunk_out = kchunk;
@@ -1185,9 +1188,13 @@ int k_reserve(dfjk_ctx* h, int64_t max_ncol) {
     // half of the rows over every tile)
     const KBytes a = k_bytes(h, elem, n1, n1, lower);
     const KBytes b = k_bytes(h, elem, 2 * half, 2 * half, lower);
-    const KBytes c = k_bytes(h, elem, 2 * half, half, nt * nt);
-    size_t kp = a.kpart > b.kpart ? a.kpart : b.kpart;
-    kp = kp > c.kpart ? kp : c.kpart;
+    // the partials by the splits aimed at, not those that whole chunks leave: a
+    // call of fewer columns may be cut into more of them (24600 rows into 385,
+    // 24576 into 512)
+    const auto partials = [&](int64_t nrows, int64_t ntl) {
+        return elem * (size_t)(syrk_max_splits(nrows, ntl, elem == 4) * ntl) * SY_T * SY_T;
+    };
+    const size_t kp = std::max({partials(n1, lower), partials(2 * half, lower), partials(half, nt * nt)});
     int rc;
     if ((rc = h->X.ensure(a.X > b.X ? a.X : b.X))) return rc;
     if ((rc = h->kpart.ensure(kp))) return rc;
