@@ -15,7 +15,7 @@
 #include <new>
 #include <vector>
 
-#include "internal.h"
+#include "dense.h"
 
 namespace dfjk {
 namespace {
@@ -58,9 +58,13 @@ struct dfjk_batch_ctx {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     // SCF iterations over the batch: one handle per molecule without B (its
-    // DIIS history and eigensolver state), and worker streams for the
-    // molecules' dense steps
+    // DIIS history and eigensolver state).  The dense steps of the molecules
+    // whose eigensolver runs in LDS (scf_small) are launches over all of them;
+    // the others (scf_large) take theirs to worker streams.
     std::vector<dfjk_ctx*> scf;
+    bool scf_ok = false;
+    std::vector<int> scf_small, scf_large;
+    dfjk::DevBuf d_scf, scf_rec;  // descriptors of scf_small; records by molecule
     std::vector<hipStream_t> workers;
     std::vector<hipEvent_t> worker_done;
     hipEvent_t built = nullptr;
@@ -230,25 +234,31 @@ int time_tiles(dfjk_batch_ctx* b, int reps, double* best_ms) {
     return rc;
 }
 
-// Per-molecule SCF handles and worker streams, made on first use.
-int scf_setup(dfjk_batch b) {
-    if (!b->scf.empty()) return DFJK_OK;
-    const int nw = std::min(b->nmol, 8);
-    for (int w = 0; w < nw; ++w) {
-        hipStream_t s = nullptr;
-        hipEvent_t e = nullptr;
-        DFJK_HIP_TRY(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
-        b->workers.push_back(s);
-        DFJK_HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-        b->worker_done.push_back(e);
-    }
-    DFJK_HIP_TRY(hipEventCreateWithFlags(&b->built, hipEventDisableTiming));
+void scf_drop(dfjk_batch b) {
+    for (hipStream_t s : b->workers) (void)hipStreamSynchronize(s);
+    for (dfjk_ctx* h : b->scf) dfjk_destroy(h);
+    for (hipEvent_t e : b->worker_done) (void)hipEventDestroy(e);
+    for (hipStream_t s : b->workers) (void)hipStreamDestroy(s);
+    if (b->built) (void)hipEventDestroy(b->built);
+    b->built = nullptr;
+    b->scf.clear();
+    b->workers.clear();
+    b->worker_done.clear();
+    b->scf_small.clear();
+    b->scf_large.clear();
+    b->d_scf.release();
+    b->scf_rec.release();
+}
+
+// Per-molecule SCF handles, and worker streams where one needs them
+int scf_make(dfjk_batch b) {
     for (int i = 0; i < b->nmol; ++i) {
         dfjk_ctx* h = new (std::nothrow) dfjk_ctx();
         if (!h) {
             ::dfjk::set_error("dfjk_batch_scf: host allocation failed");
             return DFJK_E_OOM;
         }
+        b->scf.push_back(h);
         const MolDesc& d = b->mols[i];
         h->device = b->device;
         h->nao = d.nao;
@@ -256,21 +266,78 @@ int scf_setup(dfjk_batch b) {
         h->npair = d.npair;
         h->dtype = b->dtype;
         dfjk_default_options(&h->opts);
-        b->scf.push_back(h);
+        h->stream = b->stream;
     }
-    // molecules longest first, dealt round-robin to the worker streams
-    for (int j = 0; j < b->nmol; ++j) b->scf[b->order[j]]->stream = b->workers[j % nw];
+    // longest first, as in every phase
+    for (int i : b->order) (b->mols[i].nao <= kEigLdsN ? b->scf_small : b->scf_large).push_back(i);
+    if (!b->scf_large.empty()) {
+        const int nw = std::min((int)b->scf_large.size(), 8);
+        for (int w = 0; w < nw; ++w) {
+            hipStream_t s = nullptr;
+            hipEvent_t e = nullptr;
+            DFJK_HIP_TRY(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
+            b->workers.push_back(s);
+            DFJK_HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+            b->worker_done.push_back(e);
+        }
+        DFJK_HIP_TRY(hipEventCreateWithFlags(&b->built, hipEventDisableTiming));
+        // dealt round-robin to the worker streams
+        for (size_t j = 0; j < b->scf_large.size(); ++j) b->scf[b->scf_large[j]]->stream = b->workers[j % nw];
+    }
+    int rc;
+    if ((rc = b->scf_rec.ensure(sizeof(ScfRecord) * (size_t)b->nmol))) return rc;
+    if (b->scf_small.empty()) return DFJK_OK;
+    std::vector<ScfMol> desc(b->scf_small.size());
+    for (size_t j = 0; j < desc.size(); ++j) {
+        const int i = b->scf_small[j];
+        const MolDesc& d = b->mols[i];
+        if ((rc = scf_describe(b->scf[i], const_cast<double*>(d.D), const_cast<double*>(d.C), d.nocc, d.J, d.K,
+                               static_cast<ScfRecord*>(b->scf_rec.ptr) + i, &desc[j])))
+            return rc;
+    }
+    if ((rc = b->d_scf.ensure(sizeof(ScfMol) * desc.size()))) return rc;
+    DFJK_HIP_TRY(hipMemcpy(b->d_scf.ptr, desc.data(), sizeof(ScfMol) * desc.size(), hipMemcpyHostToDevice));
     return DFJK_OK;
 }
 
-// Fork the worker streams off the batch stream, run fn(i) for every molecule
-// on its worker stream, and join them back.
+int scf_setup(dfjk_batch b) {
+    if (b->scf_ok) return DFJK_OK;
+    const int rc = scf_make(b);
+    if (rc)
+        scf_drop(b);
+    else
+        b->scf_ok = true;
+    return rc;
+}
+
+// fn(descriptors, handles, pointers of the call, count) over the small molecules,
+// kMolChunk at a time
 template <typename F>
-int on_workers(dfjk_batch b, F fn) {
+int on_small(dfjk_batch b, const double* const* list, F fn) {
+    dfjk_ctx* h[kMolChunk];
+    const double* p[kMolChunk];
+    for (size_t j0 = 0; j0 < b->scf_small.size(); j0 += kMolChunk) {
+        const int n = (int)std::min<size_t>(kMolChunk, b->scf_small.size() - j0);
+        for (int j = 0; j < n; ++j) {
+            const int i = b->scf_small[j0 + j];
+            h[j] = b->scf[i];
+            p[j] = list[i];
+        }
+        if (int rc = fn(static_cast<const ScfMol*>(b->d_scf.ptr) + j0, h, p, n)) return rc;
+    }
+    return DFJK_OK;
+}
+
+// Fork the worker streams off the batch stream, run small() on the batch stream
+// and fn(i) for every large molecule on its worker stream, and join them back.
+template <typename S, typename F>
+int on_workers(dfjk_batch b, S small, F fn) {
+    if (b->scf_large.empty()) return small();
     DFJK_HIP_TRY(hipEventRecord(b->built, b->stream));
     for (hipStream_t s : b->workers) DFJK_HIP_TRY(hipStreamWaitEvent(s, b->built, 0));
     int rc = DFJK_OK;
-    for (int j = 0; j < b->nmol && !rc; ++j) rc = fn(b->order[j]);
+    for (size_t j = 0; j < b->scf_large.size() && !rc; ++j) rc = fn(b->scf_large[j]);
+    if (!rc) rc = small();
     for (size_t w = 0; w < b->workers.size(); ++w) {
         DFJK_HIP_TRY(hipEventRecord(b->worker_done[w], b->workers[w]));
         DFJK_HIP_TRY(hipStreamWaitEvent(b->stream, b->worker_done[w], 0));
@@ -624,9 +691,14 @@ int dfjk_batch_scf_guess(dfjk_batch b, const double* const* H_list) {
         }
     int rc;
     if ((rc = scf_setup(b))) return rc;
-    return on_workers(b, [&](int i) {
+    for (dfjk_ctx* h : b->scf) scf_reset(h);
+    const auto small = [&] {
+        return on_small(b, H_list, [&](const ScfMol* m, dfjk_ctx* const* h, const double* const* p, int n) {
+            return aufbau_many(b->stream, m, h, p, n);
+        });
+    };
+    return on_workers(b, small, [&](int i) {
         const MolDesc& d = b->mols[i];
-        scf_reset(b->scf[i]);
         return aufbau(b->scf[i], H_list[i], d.nocc, const_cast<double*>(d.C), const_cast<double*>(d.D));
     });
 }
@@ -657,15 +729,23 @@ int dfjk_batch_scf_step(dfjk_batch b, const double* const* H_list, dfjk_scf_info
     if ((rc = scf_setup(b))) return rc;
     // J(D) and K(Cocc) of every molecule, the batch's phases on its stream
     if ((rc = run_all(b, b->stream))) return rc;
-    std::vector<const void*> rec((size_t)b->nmol, nullptr);
-    rc = on_workers(b, [&](int i) {
+    const auto small = [&] {
+        return on_small(b, H_list, [&](const ScfMol* m, dfjk_ctx* const* h, const double* const* p, int n) {
+            return scf_tail_many(b->stream, m, h, p, n);
+        });
+    };
+    ScfRecord* recs = static_cast<ScfRecord*>(b->scf_rec.ptr);
+    rc = on_workers(b, small, [&](int i) -> int {
         const MolDesc& d = b->mols[i];
-        return scf_tail(b->scf[i], H_list[i], const_cast<double*>(d.D), const_cast<double*>(d.C), d.nocc, d.J,
-                        d.K, &rec[i]);
+        const void* rec = nullptr;
+        if (int e = scf_tail(b->scf[i], H_list[i], const_cast<double*>(d.D), const_cast<double*>(d.C), d.nocc, d.J,
+                             d.K, &rec))
+            return e;
+        DFJK_HIP_TRY(hipMemcpyAsync(recs + i, rec, sizeof(ScfRecord), hipMemcpyDeviceToDevice, b->scf[i]->stream));
+        return DFJK_OK;
     });
     if (rc || !info) return rc;
-    for (int i = 0; i < b->nmol; ++i)
-        DFJK_HIP_TRY(hipMemcpyAsync(&info[i], rec[i], sizeof(dfjk_scf_info), hipMemcpyDeviceToHost, b->stream));
+    DFJK_HIP_TRY(hipMemcpyAsync(info, recs, sizeof(ScfRecord) * (size_t)b->nmol, hipMemcpyDeviceToHost, b->stream));
     DFJK_HIP_TRY(hipStreamSynchronize(b->stream));
     bool all = true;
     for (int i = 0; i < b->nmol; ++i) {
@@ -681,11 +761,7 @@ int dfjk_batch_scf_step(dfjk_batch b, const double* const* H_list, dfjk_scf_info
 void dfjk_batch_destroy(dfjk_batch b) {
     if (!b) return;
     (void)hipStreamSynchronize(b->stream);
-    for (hipStream_t s : b->workers) (void)hipStreamSynchronize(s);
-    for (dfjk_ctx* h : b->scf) dfjk_destroy(h);
-    for (hipEvent_t e : b->worker_done) (void)hipEventDestroy(e);
-    for (hipStream_t s : b->workers) (void)hipStreamDestroy(s);
-    if (b->built) (void)hipEventDestroy(b->built);
+    scf_drop(b);
     drop_graph(b);
     if (b->cap) (void)hipStreamDestroy(b->cap);
     b->work.release();

@@ -1,5 +1,5 @@
-// Dense FP64 helpers (dense.hip): matrix product, deterministic dot
-// products, symmetric eigensolver.
+// Dense helpers (dense.hip, eigen.hip): matrix products and the symmetric
+// eigensolver.
 #pragma once
 
 #include "internal.h"
@@ -7,13 +7,13 @@
 namespace dfjk {
 
 constexpr int kMaxEighN = 4096;
-constexpr int kMaxDots = 16;
 
-// Up to kMaxDots dot products of length n, passed by value to the kernel.
-struct DotList {
-    const double* a[kMaxDots];
-    const double* b[kMaxDots];
-};
+// Largest edge of a result that 16 x 16 tiles take (gemm_tile.h).  Square products, us:
+// 256: 5 with them, 41 with the wide tiles (A B^T: 6, 11 with 64 x 64 tiles);
+// 448: 18, 80 (6, 20); 640: 41, 98 (15, 24).  Each operand is read from L2 once
+// per 16 rows or columns, not 64 or 128, so their lead shrinks with size; not
+// measured beyond 640.
+constexpr int64_t kSmallN = 640;
 
 // C = alpha op(A) op(B) + beta C (row-major; op = transpose when ta / tb).
 int dgemm(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha,
@@ -35,11 +35,6 @@ struct GemmEpi {
 int net_gemm(hipStream_t st, bool bf16, bool ta, bool tb, int64_t M, int64_t N, int64_t K, const float* A,
              int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int64_t kslab = 0,
              int epi = EPI_NONE, GemmEpi e = GemmEpi());
-
-// out[t] = a_t . b_t for t < nd, summed in a fixed order (bitwise reproducible).
-// part needs dots_part_elems(nd) doubles.
-int dots(hipStream_t st, const DotList& list, int nd, int64_t n, double* part, double* out);
-size_t dots_part_elems(int nd);
 
 // Workspace of the eigensolver for n x n matrices, carved from one buffer.
 constexpr int kEigLdsN = 198;       // largest n solved in LDS (eigen.hip)
@@ -71,5 +66,43 @@ int eigh_cols(hipStream_t st, const double* X, double* V, int n, bool v_identity
 // The form for n <= kEigLdsN (eigen.hip).
 int eig_lds(hipStream_t st, const double* X, double* V, int n, bool v_identity, const EigWork& ws, int ncol,
             int mode, double* out, double* sign);
+
+// ---- one molecule's SCF step (scf.hip): what its kernels read from the device
+struct ScfRecord {  // mirrors dfjk_scf_info
+    double e_tot, e_1e, e_j, e_k, err_norm, d_e;
+    int iter, converged;
+};
+struct ScfMol {
+    int n, nocc;
+    const double *J, *K;
+    double *D, *C;
+    double *V, *F, *G, *Fx;        // eigenbasis (rows), Fock matrix, scratch, extrapolated Fock matrix
+    double *Fh, *Eh;               // DIIS history
+    double *gram, *coef, *part, *e_prev, *first;
+    ScfRecord* rec;
+    EigWork eig;
+};
+// A launch over molecules takes the pointers that a call brings for up to
+// kMolChunk of them by value.
+constexpr int kMolChunk = 64;
+struct MolPtrs {
+    const double* p[kMolChunk];
+};
+
+// Eigenvectors of up to kMolChunk molecules with n <= kEigLdsN in one launch
+// each for rotations and vectors: of X.p[i], V then starting as the identity,
+// or, without X, of each one's Fx in the basis V.
+// max_n: the largest n, lds_n: the one that takes the most LDS.
+int eig_lds_many(hipStream_t st, const ScfMol* mols, const MolPtrs* X, bool v_identity, int nmol, int max_n,
+                 int lds_n);
+size_t eig_lds_bytes(int n);
+
+// The SCF step after J and K, and the aufbau of a given F, of up to kMolChunk
+// molecules (scf.hip): mols on the device, h their handles, all at the same
+// iteration.  scf_describe fills one entry; its record goes to rec.
+int scf_describe(dfjk_ctx* h, double* D, double* C, int64_t nocc, const double* J, const double* K, void* rec,
+                 ScfMol* out);
+int scf_tail_many(hipStream_t st, const ScfMol* mols, dfjk_ctx* const* h, const double* const* H, int nmol);
+int aufbau_many(hipStream_t st, const ScfMol* mols, dfjk_ctx* const* h, const double* const* F, int nmol);
 
 }  // namespace dfjk

@@ -1,9 +1,8 @@
-// Dense FP64 helpers for the SCF step and the density path of K:
-// a general matrix product on the FP64 matrix cores, deterministic
-// reductions, and the eigensolver for matrices too large for LDS.
+// Dense helpers: the general matrix product on the FP64 matrix cores, the
+// network's products, and the eigensolver for matrices too large for LDS.
 #include "dense.h"
 
-#include "mma.h"
+#include "gemm_tile.h"
 #include "numerics.h"
 
 namespace dfjk {
@@ -187,52 +186,12 @@ __global__ __launch_bounds__(256, 2) void gemm_nn_wide(int64_t M, int64_t N, int
     }
 }
 
-// C = alpha op(A) op(B) + beta C for small products (the SCF's nao x nao ones):
-// one 16 x 16 tile per workgroup, the contraction split over its four
-// wavefronts and added in order, operands straight from L2 into the
-// matrix-core layout.  Latency bounds these, so every load is independent and
-// there is one barrier: nao=128 4 us (the 64 and 128 tiles leave one to four
-// workgroups with a serial loop of staged chunks: 7 to 16 and 24 us).
+// C = alpha op(A) op(B) + beta C for small products: gemm_tile16 in every workgroup
 template <bool TA, bool TB>
 __global__ __launch_bounds__(256) void gemm_small(int M, int N, int K, double alpha, const double* __restrict__ A,
                                                   int64_t lda, const double* __restrict__ B, int64_t ldb, double beta,
                                                   double* __restrict__ C, int64_t ldc) {
-    __shared__ double red[4][16][17];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
-    const int gm = min(m0 + (lane & 15), M - 1), gn = min(n0 + (lane & 15), N - 1);
-    const int per = (int)cdiv(cdiv(K, 4), 4) * 4;  // contraction terms per wavefront, in whole steps
-    const int kb = wave * per, ke = min(kb + per, K);
-    const double *Ak = TA ? A + gm : A + gm * lda, *Bk = TB ? B + gn * ldb : B + gn;
-    const int64_t sa = TA ? lda : 1, sb = TB ? 1 : ldb;
-    v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
-    int k0 = kb;
-    for (; k0 + 32 <= ke; k0 += 32) {  // eight steps' loads in flight
-        double a[8], b[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int64_t k = k0 + 4 * j + (lane >> 4);
-            a[j] = Ak[k * sa];
-            b[j] = Bk[k * sb];
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc = Mma<double>::step(a[j], b[j], acc);
-    }
-    for (; k0 < ke; k0 += 4) {
-        const int k = k0 + (lane >> 4);
-        double a = 0.0, b = 0.0;
-        if (k < ke) a = Ak[k * sa], b = Bk[k * sb];
-        acc = Mma<double>::step(a, b, acc);
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) red[wave][Mma<double>::row(lane, r)][lane & 15] = acc[r];
-    __syncthreads();
-    const int r = tid >> 4, c = tid & 15;
-    if (m0 + r < M && n0 + c < N) {
-        const double v = ((red[0][r][c] + red[1][r][c]) + red[2][r][c]) + red[3][r][c];
-        double* dst = C + (m0 + r) * ldc + n0 + c;
-        *dst = alpha * v + (beta == 0.0 ? 0.0 : beta * *dst);
-    }
+    gemm_tile16<TA, TB>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
 }
 
 // ---------------------------------------------------------------- network products
@@ -488,37 +447,6 @@ __global__ __launch_bounds__(256, 2) void bgemm_net(int64_t M, int64_t N, int64_
     net_store<EPI>(acc, m0, n0, wm, wn, lane, M, N, C, ldc, e);
 }
 
-// ---------------------------------------------------------------- reductions
-// part[t * nblk + b] = sum over this block's slice of a_t . b_t
-constexpr int RT = 256, RBLK = 128;
-
-__global__ __launch_bounds__(RT) void dots_partial(DotList list, int64_t n, double* __restrict__ part) {
-    __shared__ double lds[RT / 64];
-    const double* __restrict__ da = list.a[blockIdx.y];
-    const double* __restrict__ db = list.b[blockIdx.y];
-    const int64_t per = cdiv(n, RBLK);
-    const int64_t beg = (int64_t)blockIdx.x * per;
-    const int64_t end = beg + per < n ? beg + per : n;
-    double s = 0.0;
-    for (int64_t i = beg + threadIdx.x; i < end; i += RT) s = fma(da[i], db[i], s);
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int w = 0; w < RT / 64; ++w) t += lds[w];
-        part[blockIdx.y * RBLK + blockIdx.x] = t;
-    }
-}
-
-__global__ void dots_finish(const double* __restrict__ part, int nd, double* __restrict__ out) {
-    const int t = threadIdx.x;
-    if (t >= nd) return;
-    double s = 0.0;
-    for (int b = 0; b < RBLK; ++b) s += part[t * RBLK + b];
-    out[t] = s;
-}
-
 // ---------------------------------------------------------------- Jacobi
 // n > kEigLdsN (smaller matrices: eigen.hip).
 // Parallel cyclic Jacobi in one workgroup on a symmetric n x n matrix A (overwritten; the
@@ -707,12 +635,6 @@ __global__ void symmetrize(const double* __restrict__ X, int64_t n, double* __re
 
 }  // namespace
 
-// Largest result edge of gemm_small.  Square products, us: 256: 5 small, 41 wide
-// (A B^T: 6, 11); 448: 18, 80 (6, 20); 640: 41, 98 (15, 24).  Each
-// operand is read from L2 once per 16 rows or columns, not 64 or 128, so its lead
-// shrinks with size; not measured beyond 640.
-constexpr int64_t kSmallN = 640;
-
 int dgemm(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha,
           const double* A, int64_t lda, const double* B, int64_t ldb, double beta, double* C,
           int64_t ldc) {
@@ -778,20 +700,6 @@ int net_gemm(hipStream_t st, bool bf16, bool ta, bool tb, int64_t M, int64_t N, 
     DFJK_LAUNCH_CHECK("net_gemm");
     return DFJK_OK;
 }
-
-int dots(hipStream_t st, const DotList& list, int nd, int64_t n, double* part, double* out) {
-    if (nd < 1 || nd > kMaxDots) {
-        set_error("dots: %d products outside [1, %d]", nd, kMaxDots);
-        return DFJK_E_INVALID;
-    }
-    dots_partial<<<dim3(RBLK, (unsigned)nd), RT, 0, st>>>(list, n, part);
-    DFJK_LAUNCH_CHECK("dots_partial");
-    dots_finish<<<1, 64, 0, st>>>(part, nd, out);
-    DFJK_LAUNCH_CHECK("dots_finish");
-    return DFJK_OK;
-}
-
-size_t dots_part_elems(int nd) { return (size_t)nd * RBLK; }
 
 int eigh_cols(hipStream_t st, const double* X, double* V, int n, bool v_identity, const EigWork& ws, int ncol,
               int mode, double* out, double* sign) {

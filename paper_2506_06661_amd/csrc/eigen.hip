@@ -167,11 +167,9 @@ __device__ inline void store_column(double* __restrict__ V, int n, int j, const 
 // the log of rotations.  NB blocks per thread; DB: two copies of the matrix in
 // LDS.
 template <int NB, bool DB>
-__global__ __launch_bounds__(kEigThreads) void jacobi_lds(const double* __restrict__ X, int n,
-                                                          double2* __restrict__ log,
-                                                          int* __restrict__ iwork, double* __restrict__ w) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ double red[2][kEigThreads / 64];
+__device__ __forceinline__ void jacobi_solve(const double* __restrict__ X, int n, double2* __restrict__ log,
+                                    int* __restrict__ iwork, double* __restrict__ w, char* smem,
+                                    double (&red)[2][kEigThreads / 64]) {
     const int m = n + (n & 1), h = m / 2, nblk = h * (h + 1) / 2;
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int na = 64 * (int)cdiv(h, 64);  // threads of the rotation wavefronts
@@ -345,14 +343,22 @@ __global__ __launch_bounds__(kEigThreads) void jacobi_lds(const double* __restri
     }
 }
 
+template <int NB, bool DB>
+__global__ __launch_bounds__(kEigThreads) void jacobi_lds(const double* __restrict__ X, int n,
+                                                          double2* __restrict__ log, int* __restrict__ iwork,
+                                                          double* __restrict__ w) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    __shared__ double red[2][kEigThreads / 64];
+    jacobi_solve<NB, DB>(X, n, log, iwork, w, smem, red);
+}
+
 // V^T <- J^T V^T with the logged rotations, one column per wavefront, and the
 // ncol lowest eigenvectors as columns of out (mode 1: scaled by sqrt|w|, the
 // signs of w to sign).
 template <int R>
-__global__ __launch_bounds__(256) void jacobi_apply(const double2* __restrict__ log, const int* __restrict__ iwork,
-                                                    int n, int v_identity, double* __restrict__ V,
-                                                    const double* __restrict__ w, int ncol, int mode, double* __restrict__ out,
-                                                    double* __restrict__ sign) {
+__device__ __forceinline__ void apply_log(const double2* __restrict__ log, const int* __restrict__ iwork, int n,
+                                 int v_identity, double* __restrict__ V, const double* __restrict__ w, int ncol,
+                                 int mode, double* __restrict__ out, double* __restrict__ sign) {
     const int col = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (col >= n) return;
     const int h = (n + 1) / 2;
@@ -373,34 +379,96 @@ __global__ __launch_bounds__(256) void jacobi_apply(const double2* __restrict__ 
     }
 }
 
+template <int R>
+__global__ __launch_bounds__(256) void jacobi_apply(const double2* __restrict__ log, const int* __restrict__ iwork,
+                                                    int n, int v_identity, double* __restrict__ V,
+                                                    const double* __restrict__ w, int ncol, int mode,
+                                                    double* __restrict__ out, double* __restrict__ sign) {
+    apply_log<R>(log, iwork, n, v_identity, V, w, ncol, mode, out, sign);
+}
+
+// The forms of jacobi_lds: one block per thread while the blocks fit a workgroup
+// (fewer wavefronts to wait for), else three with two copies of the matrix in LDS, else six with one.
+struct EigForm {
+    int h, nblk, na, nb, threads;
+    size_t lds;
+    __host__ __device__ explicit EigForm(int n) {
+        h = (n + 1) / 2;
+        nblk = h * (h + 1) / 2;
+        na = 64 * (int)cdiv(h, 64);
+        const bool db = h <= kEigDoubleH;
+        nb = nblk <= kEigThreads - na ? 1 : db ? 3 : 6;
+        threads = nb == 1 ? na + 64 * (int)cdiv(nblk, 64) : kEigThreads;
+        lds = 2 * sizeof(double2) * (size_t)h + (db ? 2 : 1) * 4 * sizeof(double) * (size_t)nblk;
+    }
+};
+
+// One workgroup per molecule
+__global__ __launch_bounds__(kEigThreads) void jacobi_many(const ScfMol* __restrict__ mols, MolPtrs X, int given) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    __shared__ double red[2][kEigThreads / 64];
+    const ScfMol& d = mols[blockIdx.x];
+    const int n = d.n, nb = EigForm(n).nb;
+    const double* x = as_global(given ? X.p[blockIdx.x] : d.Fx);
+    double2* log = as_global(reinterpret_cast<double2*>(d.eig.log));
+    int* iwork = as_global(d.eig.iwork);
+    double* w = as_global(d.eig.w);
+    if (nb == 1)
+        jacobi_solve<1, true>(x, n, log, iwork, w, smem, red);
+    else if (nb == 3)
+        jacobi_solve<3, true>(x, n, log, iwork, w, smem, red);
+    else
+        jacobi_solve<6, false>(x, n, log, iwork, w, smem, red);
+}
+
+__global__ __launch_bounds__(256) void jacobi_apply_many(const ScfMol* __restrict__ mols, int v_identity) {
+    const ScfMol& d = mols[blockIdx.y];
+    const double2* log = as_global(reinterpret_cast<const double2*>(d.eig.log));
+    const int* iwork = as_global(d.eig.iwork);
+    if (d.n <= 128)
+        apply_log<1>(log, iwork, d.n, v_identity, as_global(d.V), d.eig.w, d.nocc, 0, as_global(d.C), nullptr);
+    else
+        apply_log<2>(log, iwork, d.n, v_identity, as_global(d.V), d.eig.w, d.nocc, 0, as_global(d.C), nullptr);
+}
+
 }  // namespace
 
 int eig_lds(hipStream_t st, const double* X, double* V, int n, bool v_identity, const EigWork& ws, int ncol,
             int mode, double* out, double* sign) {
-    const int h = (n + 1) / 2, nblk = h * (h + 1) / 2, na = 64 * (int)cdiv(h, 64);
-    const bool db = h <= kEigDoubleH;
-    const size_t bytes = 2 * sizeof(double2) * (size_t)h + (db ? 2 : 1) * 4 * sizeof(double) * (size_t)nblk;
-    // one block per thread while they fit a workgroup: fewer wavefronts to wait for
-    const int nb = nblk <= kEigThreads - na ? 1 : db ? 3 : 6;
-    const int threads = nb == 1 ? na + 64 * (int)cdiv(nblk, 64) : kEigThreads;
+    const EigForm f(n);
     double2* log = reinterpret_cast<double2*>(ws.log);
     auto launch = [&](auto kernel) -> int {
         // above 64 KB of dynamic LDS a kernel has to be told so
         DFJK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, kEigLdsBytes));
-        kernel<<<1, threads, bytes, st>>>(X, n, log, ws.iwork, ws.w);
+        kernel<<<1, f.threads, f.lds, st>>>(X, n, log, ws.iwork, ws.w);
         DFJK_LAUNCH_CHECK("jacobi_lds");
         return DFJK_OK;
     };
-    int rc = nb == 1 ? launch(jacobi_lds<1, true>) : nb == 3 ? launch(jacobi_lds<3, true>) : launch(jacobi_lds<6, false>);
+    int rc = f.nb == 1 ? launch(jacobi_lds<1, true>) : f.nb == 3 ? launch(jacobi_lds<3, true>) : launch(jacobi_lds<6, false>);
     if (rc) return rc;
     const dim3 grid((unsigned)cdiv(n, 4));
-    if (h <= 64)
+    if (f.h <= 64)
         jacobi_apply<1><<<grid, 256, 0, st>>>(log, ws.iwork, n, v_identity ? 1 : 0, V, ws.w, ncol, mode, out, sign);
     else
         jacobi_apply<2><<<grid, 256, 0, st>>>(log, ws.iwork, n, v_identity ? 1 : 0, V, ws.w, ncol, mode, out, sign);
     DFJK_LAUNCH_CHECK("jacobi_apply");
     return DFJK_OK;
 }
+
+int eig_lds_many(hipStream_t st, const ScfMol* mols, const MolPtrs* X, bool v_identity, int nmol, int max_n,
+                 int lds_n) {
+    // one launch holds all sizes, so its LDS is the most any of them takes (at lds_n)
+    DFJK_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(jacobi_many),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kEigLdsBytes));
+    const MolPtrs none{};
+    jacobi_many<<<(unsigned)nmol, EigForm(max_n).threads, EigForm(lds_n).lds, st>>>(mols, X ? *X : none, X ? 1 : 0);
+    DFJK_LAUNCH_CHECK("jacobi_many");
+    jacobi_apply_many<<<dim3((unsigned)cdiv(max_n, 4), (unsigned)nmol), 256, 0, st>>>(mols, v_identity ? 1 : 0);
+    DFJK_LAUNCH_CHECK("jacobi_apply_many");
+    return DFJK_OK;
+}
+
+size_t eig_lds_bytes(int n) { return EigForm(n).lds; }
 
 }  // namespace dfjk
