@@ -202,35 +202,63 @@ void launch_j_out(bool vec, dim3 g, hipStream_t st, const double* B, int64_t ldB
     }
 }
 
+// v[0] + v[stride] + ... (n terms, in order), 16 loads in flight
+__device__ inline double sum_strided(const double* __restrict__ v, int64_t stride, int n) {
+    double s = 0.0;
+    int i = 0;
+    for (; i + 16 <= n; i += 16, v += 16 * stride) {
+        double t[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) t[j] = v[j * stride];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) s += t[j];
+    }
+    for (; i < n; ++i, v += stride) s += *v;
+    return s;
+}
+
 // diag[p] = sum_s dpart[s][p], splits in order
 __global__ __launch_bounds__(256) void diag_finish(const double* __restrict__ dpart, int64_t npair, int nsplit,
                                                    double* __restrict__ diag) {
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (p >= npair) return;
-    double v = 0.0;
-    for (int s = 0; s < nsplit; ++s) v += dpart[(int64_t)s * npair + p];
-    diag[p] = v;
+    if (p < npair) diag[p] = sum_strided(dpart + p, npair, nsplit);
 }
 
 constexpr int kJOutU[] = {2, 4, 8, 16};
 constexpr int kNumJOut = 4;
 
-// J[nu,mu] = J[mu,nu] = sum_s jpart[s][p(mu,nu)]; one block per packed row nu.
-__device__ __attribute__((always_inline)) inline void j_finish_body(int64_t nu, const double* __restrict__ jpart, int64_t npair,
-                                     int nsplit, int64_t nao, double* __restrict__ J) {
+// J[nu,mu] = J[mu,nu] = sum_s jpart[s][p(mu,nu)] for the 64-wide column blocks
+// block0, block0 + nblock, ... of packed row nu: four wavefronts take a quarter of
+// the splits each, added in order.  Latency bounds it (up to 128 splits, few
+// columns at small nao), so loads are issued 16 at a time: 128 splits at nao=64
+// 4 us, 17 at nao=701 48 us (33 and 113 with one thread adding a column's splits
+// one by one).
+__device__ __attribute__((always_inline)) inline void j_finish_body(int64_t nu, int block0, int nblock,
+                                                                    const double* __restrict__ jpart, int64_t npair,
+                                                                    int nsplit, int64_t nao, double* __restrict__ J) {
+    __shared__ double red[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int per = (nsplit + 3) / 4, s0 = min(wave * per, nsplit), s1 = min(s0 + per, nsplit);
     const int64_t base = nu * (nu + 1) / 2;
-    for (int64_t mu = threadIdx.x; mu <= nu; mu += kThreads) {
-        double v = 0.0;
-        for (int s = 0; s < nsplit; ++s) v += jpart[(int64_t)s * npair + base + mu];
-        J[nu * nao + mu] = v;
-        J[mu * nao + nu] = v;
+    for (int64_t mu0 = 64 * (int64_t)block0; mu0 <= nu; mu0 += 64 * (int64_t)nblock) {
+        const int64_t mu = mu0 + lane;
+        red[wave][lane] = mu <= nu ? sum_strided(jpart + s0 * npair + base + mu, npair, s1 - s0) : 0.0;
+        __syncthreads();
+        if (wave == 0 && mu <= nu) {
+            const double v = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+            J[nu * nao + mu] = v;
+            J[mu * nao + nu] = v;
+        }
+        __syncthreads();
     }
 }
 
 __global__ __launch_bounds__(kThreads) void j_finish(const double* __restrict__ jpart, int64_t npair,
                                                       int nsplit, int64_t nao, double* __restrict__ J) {
-    j_finish_body(blockIdx.x, jpart, npair, nsplit, nao, J);
+    j_finish_body(blockIdx.x, blockIdx.y, gridDim.y, jpart, npair, nsplit, nao, J);
 }
+// column blocks of a row shared by this many workgroups
+inline unsigned j_finish_blocks(int64_t nao) { return (unsigned)std::min<int64_t>((nao + 63) / 64, 64); }
 
 __host__ __device__ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -488,7 +516,7 @@ int j_build_red_t(dfjk_ctx* h, double* J, double* rho_out, double* diag) {
                                                            vec, jpart, nullptr);
     h->prof.end(PH_J_OUT, st);
     DFJK_LAUNCH_CHECK("j_out_red");
-    j_finish<<<dim3((unsigned)h->nao), kThreads, 0, st>>>(jpart, h->npair, h->j_splits, h->nao, J);
+    j_finish<<<dim3((unsigned)h->nao, j_finish_blocks(h->nao)), kThreads, 0, st>>>(jpart, h->npair, h->j_splits, h->nao, J);
     DFJK_LAUNCH_CHECK("j_finish");
     if (dpart) {
         diag_finish<<<dim3((unsigned)cdiv(h->npair, 256)), 256, 0, st>>>(dpart, h->npair, h->j_splits, diag);
@@ -550,7 +578,7 @@ __global__ __launch_bounds__(kThreads) void jb_kernel(int kind, const MolDesc* _
             break;
         }
         case BP_JFIN:
-            j_finish_body(lid, as_global(d.jpart), d.npair, (int)d.j_splits, d.nao, as_global(d.J));
+            j_finish_body(lid, 0, 1, as_global(d.jpart), d.npair, (int)d.j_splits, d.nao, as_global(d.J));
             break;
         default:
             break;
@@ -712,7 +740,7 @@ __global__ __launch_bounds__(kThreads) void j_out_f64m(const double* __restrict_
 __global__ __launch_bounds__(kThreads) void j_finish_m(const double* __restrict__ jpart, int64_t npair,
                                                         int nsplit, int64_t nao, double* __restrict__ J) {
     const int64_t m = blockIdx.y;
-    j_finish_body(blockIdx.x, jpart + m * nsplit * npair, npair, nsplit, nao, J + m * nao * nao);
+    j_finish_body(blockIdx.x, blockIdx.z, gridDim.z, jpart + m * nsplit * npair, npair, nsplit, nao, J + m * nao * nao);
 }
 
 template <int M>
@@ -875,7 +903,7 @@ int j_build(dfjk_ctx* h, const double* D, double* J, double* rho_out, double* di
     }
     h->prof.end(PH_J_OUT, st);
     DFJK_LAUNCH_CHECK("j_out_f64");
-    j_finish<<<dim3((unsigned)h->nao), kThreads, 0, st>>>(jpart, h->npair, (int)splits, h->nao, J);
+    j_finish<<<dim3((unsigned)h->nao, j_finish_blocks(h->nao)), kThreads, 0, st>>>(jpart, h->npair, (int)splits, h->nao, J);
     DFJK_LAUNCH_CHECK("j_finish");
     if (dpart) {
         diag_finish<<<dim3((unsigned)cdiv(h->npair, 256)), 256, 0, st>>>(dpart, h->npair, (int)splits, diag);
@@ -964,7 +992,7 @@ int j_build_multi(dfjk_ctx* h, int64_t ndm, const double* D, double* J, double* 
                          nsplit, jpart, false);
         h->prof.end(PH_J_OUT, st);
         DFJK_LAUNCH_CHECK("j_out_f64m");
-        j_finish_m<<<dim3((unsigned)nao, (unsigned)M), kThreads, 0, st>>>(jpart, npair, (int)nsplit, nao,
+        j_finish_m<<<dim3((unsigned)nao, (unsigned)M, j_finish_blocks(nao)), kThreads, 0, st>>>(jpart, npair, (int)nsplit, nao,
                                                                            J + m0 * nao * nao);
         DFJK_LAUNCH_CHECK("j_finish_m");
     }
