@@ -47,7 +47,9 @@ struct Mma16<uint16_t> {  // bfloat16 bits
         __builtin_memcpy(&bv, &b, 16);
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
     }
-    __device__ static uint16_t from_float(float f) { return float_to_bf16_rne(f); }
+    // RNE on the conversion unit; the bit arithmetic of float_to_bf16_rne, with its
+    // branch for NaN, was a fifth of GEMM1's time
+    __device__ static uint16_t from_float(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
     __device__ static uint16_t from_double(double x) { return float_to_bf16_rne(to_float_round_odd(x)); }
 };
 template <>
@@ -612,63 +614,67 @@ __device__ inline int st_row(int t) {
 // i.e. a 128 x 32*NI output tile per P; with 32*NI >= the padded orbital
 // count every element of Bd_P is read from memory once.  Per 64-deep chunk
 // the 128 rows of Bd_P and the 32*NI rows of Ct are staged in LDS (128-byte
-// rows, piece p of row r at p ^ (r & 7)), double-buffered, the next chunk
-// loaded into registers while the current one is multiplied on
+// rows, piece p of row r at p ^ (r & 7)), double-buffered, multiplied on
 // 16 x 16 x 32 steps (2 x NI result blocks per wavefront).
+// One workgroup fills a CU, so nothing else runs while it waits: Bd_P is loaded two
+// chunks ahead (8 registers each), Ct, which the L2 holds, one; addresses are
+// uniform bases with constant 32-bit offsets; rows outside the operands read the
+// last row (they only feed outputs that are not written), so a chunk has no
+// branch and its stores and loads stand between the second step's products.
+// nao=2048, naux=4096, nocc=400 (BF16): 18.3 -> 15.4 ms, 0.93 PFLOP/s counting the
+// padding (1.0 ms of it from conversions without branches and 4-byte stores of X, 1.9
+// from the order; four chunks ahead measured the same as two).
 constexpr int kT8 = 512;
-constexpr int GW_M = 128;
+constexpr int GW_M = 128, GW_RING = 2;
 
-template <int NI>
-struct GwStage {
-    static constexpr int NP = (GW_M + 32 * NI) * 8;        // 16-byte pieces per chunk
-    static constexpr int PER = (NP + kT8 - 1) / kT8;       // per thread
-    u4 v[PER];
-};
-
-template <typename H, int NI, bool PRE, bool SCHED = false>
+template <typename H, int NI>
 __global__ __launch_bounds__(kT8, 1) void g1_w(const H* __restrict__ Bd, int64_t ldd, int64_t rs, int64_t nao,
                                                 const H* __restrict__ Ct, int64_t ncol, int64_t ncp,
                                                 H* __restrict__ X, int64_t nib, int64_t nmb, int64_t nblk) {
-    constexpr int BI = 32 * NI, ROWS = GW_M + BI;
-    __shared__ uint16_t sT[2][ROWS][LROW64];  // rows 0..127: Bd_P; rows 128..: Ct
+    constexpr int BI = 32 * NI;
+    constexpr int NA = GW_M * 8 / kT8, NB = (BI * 8 + kT8 - 1) / kT8;  // pieces per thread
+    constexpr int ROWS = GW_M + 64 * NB;  // whole passes of the workgroup: no store needs a check
+    // rows 0..127: Bd_P; rows 128..: Ct; two arrays, so that a store to one is known
+    // not to touch what is read from the other
+    __shared__ __attribute__((aligned(16))) uint16_t s0[ROWS][LROW64], s1[ROWS][LROW64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave & 3, wn = wave >> 2;
-    const int64_t lid = xcd_lid(blockIdx.x, nblk);
-    const int64_t ib = lid % nib, mb = (lid / nib) % nmb, P = lid / (nib * nmb);
-    const int64_t i0 = ib * BI, mu0 = mb * GW_M;
-    const uint16_t* A = reinterpret_cast<const uint16_t*>(Bd) + P * ldd * rs;
-    const uint16_t* Bt = reinterpret_cast<const uint16_t*>(Ct);
-    using St = GwStage<NI>;
-    // piece e = tid + j*512: row e>>3, piece e&7 of the 64-deep chunk
-    const uint16_t* src[St::PER];
-    bool ok[St::PER];
+    const uint32_t lid = (uint32_t)xcd_lid(blockIdx.x, nblk);  // nblk is a grid: below 2^31
+    const uint32_t ib = lid % (uint32_t)nib, q = lid / (uint32_t)nib, mb = q % (uint32_t)nmb, P = q / (uint32_t)nmb;
+    const int64_t i0 = ib * (int64_t)BI, mu0 = mb * (int64_t)GW_M;
+    const uint16_t* Ak = reinterpret_cast<const uint16_t*>(Bd) + (P * ldd + mu0) * rs;
+    const uint16_t* Bk = reinterpret_cast<const uint16_t*>(Ct) + i0 * rs;
+    // piece tid % 8 of rows tid / 8 + 64 j of either operand
+    const int pr = tid >> 3;
+    uint32_t aoff[NA], boff[NB];
 #pragma unroll
-    for (int j = 0; j < St::PER; ++j) {
-        const int e = tid + j * kT8, r = e >> 3;
-        if (r < GW_M) {
-            const int64_t row = mu0 + r;
-            ok[j] = e < St::NP && row < ldd;
-            src[j] = A + (ok[j] ? row : 0) * rs + 8 * (e & 7);
-        } else {
-            const int64_t row = i0 + (r - GW_M);
-            ok[j] = e < St::NP && row < ncp;
-            src[j] = Bt + (ok[j] ? row : 0) * rs + 8 * (e & 7);
-        }
+    for (int j = 0; j < NA; ++j) {
+        const int64_t last = ldd - 1 - mu0;
+        aoff[j] = (uint32_t)((pr + 64 * j < last ? pr + 64 * j : last) * rs + 8 * (tid & 7));
     }
-    const u4 z4 = u4{0u, 0u, 0u, 0u};
-    St st;
-    // loads always read a valid address (row 0 stands in for rows outside the
-    // operands); the pieces of such rows are replaced by zeros when stored
-    auto load = [&](int64_t k0) {
 #pragma unroll
-        for (int j = 0; j < St::PER; ++j) st.v[j] = *reinterpret_cast<const u4*>(src[j] + k0);
+    for (int j = 0; j < NB; ++j) {
+        const int64_t last = ncp - 1 - i0 < BI - 1 ? ncp - 1 - i0 : BI - 1;
+        boff[j] = (uint32_t)((pr + 64 * j < last ? pr + 64 * j : last) * rs + 8 * (tid & 7));
+    }
+    u4 ra[GW_RING][NA], rb[NB];
+    auto load_a = [&](u4 (&v)[NA], int64_t kc) {
+        const uint16_t* p = Ak + kc * KC16;
+#pragma unroll
+        for (int j = 0; j < NA; ++j) v[j] = *reinterpret_cast<const u4*>(p + aoff[j]);
     };
-    auto store = [&](int buf) {
+    auto load_b = [&](int64_t kc) {
+        const uint16_t* p = Bk + kc * KC16;
 #pragma unroll
-        for (int j = 0; j < St::PER; ++j) {
-            const int e = tid + j * kT8;
-            if (e < St::NP) *reinterpret_cast<u4*>(&sT[buf][e >> 3][swz(e >> 3, e & 7)]) = ok[j] ? st.v[j] : z4;
-        }
+        for (int j = 0; j < NB; ++j) rb[j] = *reinterpret_cast<const u4*>(p + boff[j]);
+    };
+    // the row of every piece has the same r & 7
+    auto store = [&](const u4 (&v)[NA], int buf) {
+        uint16_t* d = &(buf ? s1 : s0)[pr][swz(pr, tid & 7)];
+#pragma unroll
+        for (int j = 0; j < NA; ++j) *reinterpret_cast<u4*>(d + 64 * j * LROW64) = v[j];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) *reinterpret_cast<u4*>(d + (GW_M + 64 * j) * LROW64) = rb[j];
     };
     v4f acc[2][NI];
 #pragma unroll
@@ -676,71 +682,78 @@ __global__ __launch_bounds__(kT8, 1) void g1_w(const H* __restrict__ Bd, int64_t
 #pragma unroll
         for (int b = 0; b < NI; ++b) acc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
     const int64_t nk = ldd / KC16;  // ldd is a multiple of 64
-    load(0);
-    store(0);
-    __syncthreads();
-    for (int64_t kc = 0; kc < nk; ++kc) {
-        const int buf = kc & 1;
-        const bool more = kc + 1 < nk;
-        if (more) load((kc + 1) * KC16);
+    // chunk kc: its products, chunk kc + 1 (ring place u1) to the other buffer, Bd_P of
+    // chunk kc + 1 + GW_RING and Ct of chunk kc + 2 to its registers (past the end
+    // the last chunk again, for nothing: no branch inside a chunk)
+    auto chunk = [&](int64_t kc, int buf, int u1) {
+        u4 a[2][2], b[2][NI];
 #pragma unroll
-        for (int ks = 0; ks < KC16 / KS; ++ks) {
+        for (int ks = 0; ks < 2; ++ks) {
             const int pc = ks * (KS / 8) + (lane >> 4);
-            u4 a[2];
+            const uint16_t* pa = &(buf ? s1 : s0)[wm * 32 + (lane & 15)][swz(lane & 15, pc)];
+            const uint16_t* pb = &(buf ? s1 : s0)[GW_M + wn * 16 * NI + (lane & 15)][swz(lane & 15, pc)];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int r = wm * 32 + t * 16 + (lane & 15);
-                a[t] = *reinterpret_cast<const u4*>(&sT[buf][r][swz(r, pc)]);
-            }
-            if constexpr (PRE) {
-                // every operand piece of the step is requested before the first
-                // product, so the LDS latency is paid once per step
-                u4 b[NI];
+            for (int t = 0; t < 2; ++t) a[ks][t] = *reinterpret_cast<const u4*>(pa + 16 * t * LROW64);
 #pragma unroll
-                for (int n = 0; n < NI; ++n) {
-                    const int r = GW_M + wn * 16 * NI + n * 16 + (lane & 15);
-                    b[n] = *reinterpret_cast<const u4*>(&sT[buf][r][swz(r, pc)]);
-                }
+            for (int n = 0; n < NI; ++n) b[ks][n] = *reinterpret_cast<const u4*>(pb + 16 * n * LROW64);
 #pragma unroll
-                for (int n = 0; n < NI; ++n)
+            for (int n = 0; n < NI; ++n)
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) acc[t][n] = Mma16<H>::step(a[t], b[n], acc[t][n]);
-                if constexpr (SCHED) {
-                    // keep several operand reads in flight ahead of the products:
-                    // 6 reads, then (2 products, 1 read) until the reads run out
-                    constexpr int R0 = 6 < NI + 2 ? 6 : NI + 2;
-                    __builtin_amdgcn_sched_group_barrier(0x100, R0, 0);
+                for (int t = 0; t < 2; ++t) acc[t][n] = Mma16<H>::step(a[ks][t], b[ks][n], acc[t][n]);
+        }
+        store(ra[u1], buf ^ 1);
+        load_a(ra[u1], kc + 1 + GW_RING < nk ? kc + 1 + GW_RING : nk - 1);
+        load_b(kc + 2 < nk ? kc + 2 : nk - 1);
+        // operand reads six ahead of the products, and between the second step's
+        // products each store to LDS with the load that refills its register
+        constexpr int R0 = 6, R = 2 * (NI + 2) - R0, S = NA + NB;
+        static_assert(R <= 2 * NI && S <= R - NI, "schedule");
+        __builtin_amdgcn_sched_group_barrier(0x100, R0, 0);
 #pragma unroll
-                    for (int g = 0; g < NI + 2 - R0; ++g) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                    }
-                    __builtin_amdgcn_sched_group_barrier(0x008, 2 * NI - 2 * (NI + 2 - R0), 0);
-                }
-            } else {
-#pragma unroll
-                for (int n = 0; n < NI; ++n) {
-                    const int r = GW_M + wn * 16 * NI + n * 16 + (lane & 15);
-                    const u4 b = *reinterpret_cast<const u4*>(&sT[buf][r][swz(r, pc)]);
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) acc[t][n] = Mma16<H>::step(a[t], b, acc[t][n]);
-                }
+        for (int g = 0; g < 2 * NI; ++g) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+            if (g < R) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            if (g >= NI && g < NI + S) {
+                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
             }
         }
-        if (more) store(buf ^ 1);
         __syncthreads();
+    };
+#pragma unroll
+    for (int u = 0; u < GW_RING; ++u) load_a(ra[u], u < nk ? u : nk - 1);
+    load_b(0);
+    store(ra[0], 0);
+    load_a(ra[0], GW_RING < nk ? GW_RING : nk - 1);
+    load_b(1 < nk ? 1 : 0);
+    __syncthreads();
+    for (int64_t kc = 0; kc < nk; kc += GW_RING) {
+#pragma unroll
+        for (int u = 0; u < GW_RING; ++u) {
+            if (kc + u >= nk) break;
+            chunk(kc + u, u & 1, (u + 1) % GW_RING);
+        }
     }
+    // two columns of one row per 4-byte store (ncp is even): lanes 2k and 2k + 1
+    // exchange, the even one keeping row r, the odd one row r + 1
+    const int odd = lane & 1;
+    H* Xw = X + (int64_t)P * nao * ncp;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int n = 0; n < NI; ++n) {
+        const int64_t i = i0 + wn * 16 * NI + n * 16 + (lane & 15);
+        const bool on = i < ncol;
 #pragma unroll
-        for (int n = 0; n < NI; ++n)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t mu = mu0 + wm * 32 + t * 16 + 4 * (lane >> 4) + r;
-                const int64_t i = i0 + wn * 16 * NI + n * 16 + (lane & 15);
-                if (mu < nao && i < ncp)
-                    X[(P * nao + mu) * ncp + i] = Mma16<H>::from_float(i < ncol ? acc[t][n][r] : 0.f);
+            for (int r = 0; r < 4; r += 2) {
+                const uint32_t lo = __builtin_bit_cast(uint16_t, Mma16<H>::from_float(on ? acc[t][n][r] : 0.f));
+                const uint32_t hi = __builtin_bit_cast(uint16_t, Mma16<H>::from_float(on ? acc[t][n][r + 1] : 0.f));
+                const uint32_t own = lo | (hi << 16), other = __builtin_amdgcn_mov_dpp(own, 0xb1, 0xf, 0xf, true);
+                const uint32_t w = odd ? (other >> 16) | (own & 0xffff0000u) : (own & 0xffffu) | (other << 16);
+                const int64_t mu = mu0 + wm * 32 + t * 16 + 4 * (lane >> 4) + r + odd;
+                if (mu < nao && i < ncp) __builtin_memcpy(Xw + mu * ncp + (i - odd), &w, 4);
             }
+    }
 }
 
 // ---------------------------------------------------------------- GEMM1 on the packed triangle
@@ -1180,12 +1193,12 @@ void launch_g1d(hipStream_t st, const H* Bd, int64_t ldd, int64_t rs, int64_t na
     g1_16d<H, TM, NI><<<dim3((unsigned)nblk), kT, 0, st>>>(Bd, ldd, rs, nao, Ct, ncol, ncp, X, nib, nmb, nblk);
 }
 
-template <typename H, int NI, bool PRE = true, bool SCHED = false>
+template <typename H, int NI>
 void launch_gw(hipStream_t st, const H* Bd, int64_t ldd, int64_t rs, int64_t nao, const H* Ct, int64_t ncol,
                int64_t ncp, H* X, int64_t naux) {
     const int64_t nib = cdiv(ncp, 32 * NI), nmb = cdiv(nao, GW_M);
     const int64_t nblk = nib * nmb * naux;
-    g1_w<H, NI, PRE, SCHED><<<dim3((unsigned)nblk), kT8, 0, st>>>(Bd, ldd, rs, nao, Ct, ncol, ncp, X, nib, nmb, nblk);
+    g1_w<H, NI><<<dim3((unsigned)nblk), kT8, 0, st>>>(Bd, ldd, rs, nao, Ct, ncol, ncp, X, nib, nmb, nblk);
 }
 
 template <typename H, int WM, int WN, int FM, int FN>
@@ -1270,7 +1283,7 @@ void launch_g16(int t, hipStream_t st, const H* Bd, int64_t ldd, const H* Bp, in
         case 4: launch_g1d<H, 2, 13>(st, Bd, ldd, rs, nao, Ct, ncol, ncp, X, naux); break;
         case 5: launch_g1d<H, 4, 8>(st, Bd, ldd, rs, nao, Ct, ncol, ncp, X, naux); break;
         case 6: launch_g1d<H, 4, 4>(st, Bd, ldd, rs, nao, Ct, ncol, ncp, X, naux); break;
-        default: launch_gw<H, 13, true, true>(st, Bd, ldd, rs, nao, Ct, ncol, ncp, X, naux); break;
+        default: launch_gw<H, 13>(st, Bd, ldd, rs, nao, Ct, ncol, ncp, X, naux); break;
     }
 }
 
