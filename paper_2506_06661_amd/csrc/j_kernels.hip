@@ -536,16 +536,6 @@ int j_build_red(dfjk_ctx* h, double* J, double* rho_out, double* diag) {
 }
 
 // ---------------------------------------------------------------- batched
-__device__ inline int find_mol(const int64_t* __restrict__ prefix, int n, int64_t b) {
-    int lo = 0, hi = n - 1;  // largest j with prefix[j] <= b
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (prefix[mid] <= b) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 constexpr int kBatchR = 8;
 
 template <typename TB>

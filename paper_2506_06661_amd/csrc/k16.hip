@@ -1397,20 +1397,10 @@ int k16_t(dfjk_ctx* h, const double* C, int64_t ncol, double scale, double* K) {
 // The 16-bit exchange over many molecules: every phase is one launch over
 // all molecules' blocks; a block finds its molecule by binary search in the
 // phase's prefix table (molecules longest first).
-__device__ inline int find_mol16(const int64_t* __restrict__ prefix, int n, int64_t b) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (prefix[mid] <= b) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 template <typename H>
 __global__ __launch_bounds__(kT) void kb16_kernel(int kind, const MolDesc* __restrict__ mols, PhaseList pl) {
-    const int64_t b = kind == BP_SYRK16 ? xcd_lid(blockIdx.x, pl.nblk) : (int64_t)blockIdx.x;
-    const int j = find_mol16(pl.prefix, pl.n, b);
+    const int64_t b = kind == BP_SYRK16 ? xcd_runs(blockIdx.x, pl.nblk) : (int64_t)blockIdx.x;
+    const int j = find_mol(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
     const int64_t lid = b - pl.prefix[j];
     if (kind == BP_CT16) {
@@ -1434,8 +1424,8 @@ constexpr int kG16WM = 2;
 template <typename H, int FN>
 __global__ __launch_bounds__(128 * kG16WM, 4) void kb16_gemm1(const MolDesc* __restrict__ mols, PhaseList pl) {
     using G = G1P<kG16WM, 2, 2, FN>;
-    const int64_t b = xcd_lid(blockIdx.x, pl.nblk);
-    const int j = find_mol16(pl.prefix, pl.n, b);
+    const int64_t b = xcd_runs(blockIdx.x, pl.nblk);
+    const int j = find_mol(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
     g1p_body<H, kG16WM, 2, 2, FN>(b - pl.prefix[j], as_global(static_cast<const H*>(d.B)), d.ldB, d.nao,
                                   as_global(static_cast<const H*>(d.Ct16)), d.rs16, d.nocc, d.ncp16,

@@ -1035,19 +1035,9 @@ int k_build_pair_t(dfjk_ctx* h, const double* L_in, const double* R_in, int64_t 
 }
 
 // ---------------------------------------------------------------- batched
-__device__ inline int find_mol_k(const int64_t* __restrict__ prefix, int n, int64_t b) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (prefix[mid] <= b) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 __global__ __launch_bounds__(kThreads) void kb_kernel(int kind, const MolDesc* __restrict__ mols, PhaseList pl) {
     const int64_t b = blockIdx.x;
-    const int j = find_mol_k(pl.prefix, pl.n, b);
+    const int j = find_mol(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
     const int64_t lid = b - pl.prefix[j];
     if (kind == BP_CF32) {
@@ -1061,12 +1051,11 @@ __global__ __launch_bounds__(kThreads) void kb_kernel(int kind, const MolDesc* _
     }
 }
 
-// GEMM2 of every molecule: 4 waves per SIMD, as the single one.  Blocks are
-// renumbered so runs of consecutive ids share an XCD.  A kernel of its own:
-// beside the other phases its registers spilled.
+// GEMM2 of every molecule: 4 waves per SIMD, as the single one.  A kernel of its
+// own: beside the other phases its registers spilled.
 __global__ __launch_bounds__(kThreads, 4) void kb_syrk(const MolDesc* __restrict__ mols, PhaseList pl) {
-    const int64_t b = xcd_logical(blockIdx.x, pl.nblk);
-    const int j = find_mol_k(pl.prefix, pl.n, b);
+    const int64_t b = xcd_runs(blockIdx.x, pl.nblk);
+    const int j = find_mol(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
     k_syrk_body<float, SY_SYM, false>(b - pl.prefix[j], as_global(d.X), d.ldx, d.naux * d.nocc, d.nao, d.nocc,
                                       nullptr, d.kchunk, d.ntl, as_global(d.kpart));
@@ -1080,8 +1069,8 @@ constexpr int kb_g1_waves() { return NI * WM <= 8 ? 5 : 1; }
 template <typename TS, int NI, int WM>
 __global__ __launch_bounds__(kThreads, (kb_g1_waves<NI, WM>())) void kb_gemm1(const MolDesc* __restrict__ mols,
                                                                              PhaseList pl) {
-    const int64_t b = xcd_logical(blockIdx.x, pl.nblk);
-    const int j = find_mol_k(pl.prefix, pl.n, b);
+    const int64_t b = xcd_runs(blockIdx.x, pl.nblk);
+    const int j = find_mol(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
     k_gemm1_body<float, TS, NI, WM>(b - pl.prefix[j], as_global(static_cast<const TS*>(d.B)), d.ldB, d.nao,
                                     as_global(d.Cf), d.ldcf, d.nocc, as_global(d.X), d.ldx, d.g1_nib, d.g1_nmb);
@@ -1102,8 +1091,8 @@ int launch_kb_gemm1(hipStream_t st, int dtype, const MolDesc* mols, const PhaseL
 
 template <typename TS, int NJ, int WJ>
 __global__ __launch_bounds__(kThreads) void kb_gemm1w(const MolDesc* __restrict__ mols, PhaseList pl) {
-    const int64_t b = xcd_logical(blockIdx.x, pl.nblk);
-    const int j = find_mol_k(pl.prefix, pl.n, b);
+    const int64_t b = xcd_runs(blockIdx.x, pl.nblk);
+    const int j = find_mol(pl.prefix, pl.n, b);
     const MolDesc& d = mols[pl.ids[j]];
     k_gemm1w_body<TS, NJ, WJ>(b - pl.prefix[j], as_global(static_cast<const TS*>(d.B)), d.ldB, d.nao,
                               as_global(d.Cf), d.ldcf, d.nocc, as_global(d.X), d.ldx, d.g1_nib, d.g1_nmb);
