@@ -207,11 +207,10 @@ int dfjk_build_J_diag(dfjk_handle h, const double* D_dev, double* J_dev, double*
  *                     (nao x nocc, 1 <= nocc <= nao), i.e. K for D = 2 C C^T.
  *   Cocc_dev == NULL: K = sum_P B_P D B_P for the symmetric D_dev (paper
  *                     Sec. IV.A.1: a guess density need not be idempotent),
- *                     through the signed eigen-factors of D for nao < 256
- *                     or a reserved workspace (max_ncol > 0), else as the
- *                     two-factor form of dfjk_build_K_pair with L = D,
- *                     R = I, sym = 1, scale 1/2 (workspace: X for
- *                     2 * naux * nao rows).
+ *                     from the rows of B_P D and of B_P (workspace: X for
+ *                     2 * naux * nao rows); through the signed eigen-factors
+ *                     of D with a reserved workspace (max_ncol > 0) and, for
+ *                     reduced-precision B, for nao < 256.
  * Deterministic.
  */
 int dfjk_build_K(dfjk_handle h, const double* Cocc_dev, int64_t nocc, const double* D_dev,
@@ -237,7 +236,7 @@ enum { DFJK_SCF_C_VALID = 1 };
  * (paper Sec. IV.A: a mean-field run starts from a guess density, which need
  * not be idempotent; Sec. IV.B: Pulay DIIS is the default accelerator):
  *   J, K of D (K through Cocc when flags has DFJK_SCF_C_VALID, else through
- *   the eigen-factors of D); F = H + J - K/2; E = tr(D(H+F))/2;
+ *   D itself as in dfjk_build_K); F = H + J - K/2; E = tr(D(H+F))/2;
  *   e = FD - DF; DIIS over the last diis_space (F, e) pairs (the oldest
  *   dropped for good while the Gram matrix of the error vectors has a
  *   condition number above 1e12); aufbau on the
@@ -309,9 +308,8 @@ int dfjk_profile_read(dfjk_handle h, double* total_ms, int* counts, int nphase);
 /*
  * Tile shapes (for autotuning).  DFJK_TILE_GEMM1 selects the X = B_P C
  * kernel's workgroup tile: dfjk_tile_info gives (p0, p1) = (row tiles of 16
- * occupied orbitals, column tiles of 16 basis functions per wavefront); the
- * last three run on the FP32 32 x 32 x 2 matrix-core steps and have no FP64
- * form (dfjk_set_tile returns DFJK_E_DTYPE for them on an FP64 handle).
+ * occupied orbitals, column tiles of 16 basis functions per wavefront); 14 to
+ * 16 run on the FP32 32 x 32 x 2 matrix-core steps and have no FP64 form (dfjk_set_tile returns DFJK_E_DTYPE for them on an FP64 handle).
  * DFJK_TILE_J_OUT selects the FP64 J pass-2 column width: (p0, p1) =
  * (packed columns per workgroup, 0).  DFJK_TILE_K16 selects the 16-bit
  * exchange's GEMM1 tile: (p0, p1) = (occupied orbitals, basis functions) per
@@ -401,10 +399,12 @@ void dfjk_batch_destroy(dfjk_batch b);
  *           (dfjk_scf_step's criteria and defaults), DFJK_E_NONFINITE for a
  *           non-finite energy.
  *   dfjk_batch_scf_reset  forget the SCF histories.
- * The molecules' dense steps run on up to 8 worker streams forked from and
- * joined back to the batch stream (not graph-capturable); each molecule keeps
- * its own DIIS history and eigensolver workspace (about (5 + 2 * 8) nao^2
- * doubles), allocated on first use.  nao <= 4096 per molecule.
+ * The dense steps of molecules with nao <= 198 are launches over all of them
+ * on the batch stream; larger ones run on up to 8 worker streams forked from and
+ * joined back to it (not graph-capturable).  Each molecule keeps its own DIIS
+ * history and eigensolver workspace (about (8 + 2 * 8) nao^2 doubles, and 40
+ * nao^2 more for the eigensolver's rotations where nao <= 198), allocated on
+ * first use.  nao <= 4096 per molecule.
  */
 int dfjk_batch_scf_guess(dfjk_batch b, const double* const* H_list);
 int dfjk_batch_scf_step(dfjk_batch b, const double* const* H_list, dfjk_scf_info* info);

@@ -4,8 +4,8 @@
 // Iteration k with density D_k (paper Sec. IV.A: a mean-field run takes a
 // guess density dm0, which need not be idempotent; Sec. IV.B: DIIS is the
 // default accelerator):
-//   J, K from D_k (K through C when D_k = 2 C C^T, else through the signed
-//   eigen-factors of D_k); F = H + J - K/2;
+//   J, K from D_k (K through C when D_k = 2 C C^T, else from D_k itself or its
+//   signed eigen-factors); F = H + J - K/2;
 //   E_k = tr(D H) + tr(D J)/2 - tr(D K)/4 = tr(D (H + F))/2;
 //   e = F D - D F = G - G^T with G = F D (F, D symmetric);
 //   Pulay DIIS over the last `diis_space` (F, e): minimise |sum c_i e_i| with
@@ -38,11 +38,6 @@ namespace dfjk {
 namespace {
 
 __host__ __device__ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
-
-__global__ void identity_kernel(int64_t n, double* __restrict__ Y) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n * n) Y[i] = (i / n == i % n) ? 1.0 : 0.0;
-}
 
 __global__ void symmetrize_kernel(const double* __restrict__ X, int64_t n, double* __restrict__ Y) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -382,9 +377,10 @@ static int scf_ws(dfjk_ctx* h, bool scf, ScfWs& ws) {
     return DFJK_OK;
 }
 
-// From this nao on, K of a density goes through the two factors (D, I)
-// instead of D's eigen-factors.
-constexpr int64_t kPairFromD = 256;
+// K of a density from D itself instead of D's eigen-factors: always with FP64 B (the
+// eigensolver alone takes 1 ms at nao=128), from this nao on with FP32 compute,
+// where the two differ by the FP32 sums.
+constexpr int64_t kDensityF32 = 256;
 
 int k_build_from_D(dfjk_ctx* h, const double* D, double* K) {
     const int64_t n = h->nao;
@@ -398,16 +394,12 @@ int k_build_from_D(dfjk_ctx* h, const double* D, double* K) {
     int rc = scf_ws(h, h->scf_ready, ws);
     if (rc) return rc;
     const hipStream_t st = h->stream;
-    if (n >= kPairFromD && h->opts.max_ncol == 0) {
-        // K = 1/2 sum_P [(B_P D)(B_P I)^T + (B_P I)(B_P D)^T]: two factors of
-        // nao columns each, no eigensolver (whose one-workgroup sweeps take
-        // seconds from nao ~ 500 on); a reserved workspace (at most nao
-        // columns) keeps the eigen-factor path, which fits it
+    if (h->opts.max_ncol == 0 && (h->dtype == DFJK_F64 || n >= kDensityF32)) {
+        // K = sum_P B_P D B_P; a reserved workspace (at most nao columns) keeps the
+        // eigen-factor path, which fits it
         symmetrize_kernel<<<dim3((unsigned)cdiv(n * n, 256)), 256, 0, st>>>(D, n, ws.eig.A);
         DFJK_LAUNCH_CHECK("symmetrize_kernel");
-        identity_kernel<<<dim3((unsigned)cdiv(n * n, 256)), 256, 0, st>>>(n, ws.V);
-        DFJK_LAUNCH_CHECK("identity_kernel");
-        return k_build_pair(h, ws.eig.A, ws.V, n, 1, 0.5, K);
+        return k_build_density(h, ws.eig.A, K);
     }
     // D = sum_c w_c v_c v_c^T = sum_c sign_c (sqrt|w_c| v_c)(sqrt|w_c| v_c)^T
     if ((rc = eigh_cols(st, D, ws.V, (int)n, true, ws.eig, (int)n, 1, ws.Cf, ws.sign))) return rc;
