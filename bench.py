@@ -939,8 +939,7 @@ def main():
         "phase_ms": {"J": j_ms, "J_rho": jr_ms, "J_out": jo_ms, "K": k_ms, "K_gemm1": g1_ms,
                      "K_syrk": sy_ms, "K_finish": avg("K_finish")},
         "roofline": {
-            "kernel": ("k_gemm1_f64" if args.dtype == "f64" else "k_gemm1_f32") + " (GEMM1 phase; the orbital "
-                      "columns may be covered by two launches of different tiles)",
+            "kernel": ("k_gemm1_f64" if args.dtype == "f64" else "k_gemm1_f32") + " (GEMM1 phase)",
             "bound": "mfma",
             "achieved": g1_flops / g1_ms / 1e9,
             "peak": peak,
@@ -1027,9 +1026,11 @@ def main():
         e1.record()
         torch.cuda.synchronize()
         kd_ms = e0.elapsed_time(e1)
-        kd_flops = 2 * 2.0 * cfg.naux * cfg.nao ** 3 + 2.0 * cfg.naux * cfg.nao * cfg.nao * (cfg.nao + 1)
+        # B_P D, then its rows with those of B_P over the lower triangle; reduced B takes both orders
+        kd_flops = 2.0 * cfg.naux * cfg.nao ** 3 + (1.0 if args.dtype == "f64" else 2.0) * (
+            cfg.naux * cfg.nao * cfg.nao * (cfg.nao + 1))
         res["k_from_density"] = {"ms": kd_ms, "tflops": kd_flops / kd_ms / 1e9, "ratio_to_k_occ": kd_ms / k_ms,
-                                 "form": "two factors (D, I): sum_P B_P D B_P"}
+                                 "form": "rows of B_P D with those of B_P: sum_P B_P D B_P"}
         del A, Dg, Kg
     res["measured_mfma_ceiling_tflops"] = {
         "f64_16x16x4": pkg.dfjk_probe_mfma(pkg.DFJK_F64), "f32_16x16x4": pkg.dfjk_probe_mfma(pkg.DFJK_F32),

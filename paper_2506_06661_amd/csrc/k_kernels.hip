@@ -421,6 +421,12 @@ __global__ __launch_bounds__(kThreads, (g1_waves<T, TS, NI, WM>())) void k_gemm1
 // where the sum is symmetric by itself.
 enum { SY_SYM = 0, SY_PAIR_LOWER = 1, SY_PAIR_FULL = 2 };
 
+// Edge of a partial tile's slot: where one lower tile holds all of K, no more than
+// its 16-wide blocks.
+__host__ __device__ inline int sy_slot(int64_t nao, bool full) {
+    return !full && nao < SY_T ? (int)(nao + 15) / 16 * 16 : SY_T;
+}
+
 // Staging of one KC-deep chunk of a 128-wide operand panel: 16-byte loads (rows
 // of X start 16-byte aligned: ldx is a multiple of V), 8 elements per thread.
 // Addresses are a uniform base plus a 32-bit offset that stays the same for
@@ -594,12 +600,12 @@ __device__ __attribute__((always_inline)) inline void k_syrk_body(int64_t lid, c
     }
     const int64_t mu0 = I * SY_T, nu0 = J * SY_T;
     const int64_t kbeg = s * kchunk, kend = kbeg + kchunk < nrows ? kbeg + kchunk : nrows;
-    T* out = part + (s * ntl + t) * (int64_t)(SY_T * SY_T);
     const int nbr = nao - mu0 < SY_T ? (int)cdiv(nao - mu0, 16) : SY_T / 16;  // block rows below nao
     const int lc = lane & 15;
-    auto put = [&](const typename Mma<T>::acc_t& a, int br, int bc) {
+    auto put = [&](const typename Mma<T>::acc_t& a, int br, int bc, int edge = SY_T) {
+        T* out = part + (s * ntl + t) * (int64_t)(edge * edge);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) out[(br * 16 + Mma<T>::row(lane, r)) * SY_T + bc * 16 + lc] = a[r];
+        for (int r = 0; r < 4; ++r) out[(br * 16 + Mma<T>::row(lane, r)) * edge + bc * 16 + lc] = a[r];
     };
     if (MODE != SY_PAIR_FULL && I == J) {
         constexpr int NB = 9;
@@ -633,9 +639,10 @@ __device__ __attribute__((always_inline)) inline void k_syrk_body(int64_t lid, c
                         if (q < mine) acc[q] = Mma<T>::step(a[q], b[q], acc[q]);
                 }
             });
+        const int slot = sy_slot(nao, false);
 #pragma unroll
         for (int q = 0; q < NB; ++q)
-            if (q < mine) put(acc[q], br[q], bc[q]);
+            if (q < mine) put(acc[q], br[q], bc[q], slot);
     } else if (nbr < SY_T / 16) {
         typename Mma<T>::acc_t acc[8][2];
 #pragma unroll
@@ -700,20 +707,22 @@ __global__ __launch_bounds__(kThreads, (sizeof(T) == 4 ? 4 : 2)) void k_syrk(con
 // K[mu][nu] = K[nu][mu] = scale * sum_s partial[s][t][m][n] over the lower
 // triangle (on diagonal tiles only m >= n is used, so K is exactly symmetric).
 template <typename T>
-__device__ __attribute__((always_inline)) inline void k_syrk_finish_body(int64_t t, int e0, int e1, const T* __restrict__ part,
+__device__ __attribute__((always_inline)) inline void k_syrk_finish_body(int64_t t, int sub, int nsub, const T* __restrict__ part,
                                           int64_t nsplit, int64_t ntl, int64_t nao, double scale,
                                           double* __restrict__ K) {
     int64_t I = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
     while (I * (I + 1) / 2 > t) --I;
     while ((I + 1) * (I + 2) / 2 <= t) ++I;
     const int64_t J = t - I * (I + 1) / 2;
-    const int64_t stride = ntl * (int64_t)(SY_T * SY_T);
-    for (int e = e0 + (int)threadIdx.x; e < e1; e += kThreads) {
-        const int m = e / SY_T, n = e % SY_T;
+    const int slot = sy_slot(nao, false), n2 = slot * slot, per = (n2 + nsub - 1) / nsub;
+    const int64_t stride = ntl * n2;
+    const int e1 = min((sub + 1) * per, n2);
+    for (int e = sub * per + (int)threadIdx.x; e < e1; e += kThreads) {
+        const int m = slot == SY_T ? e / SY_T : e / slot, n = e - m * slot;
         const int64_t mu = I * SY_T + m, nu = J * SY_T + n;
         if (mu >= nao || nu >= nao) continue;
         if (I == J && m < n) continue;
-        const T* p = part + t * (int64_t)(SY_T * SY_T) + e;
+        const T* p = part + t * n2 + e;
         double v = 0.0;
 #pragma unroll 8
         for (int64_t s = 0; s < nsplit; ++s) v += (double)p[s * stride];  // fixed order
@@ -733,9 +742,7 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void k_syrk_finish(const T* __restrict__ part, int64_t nsplit,
                                                            int64_t ntl, int64_t nao, double scale, int nsub,
                                                            double* __restrict__ K) {
-    const int per = SY_T * SY_T / nsub;
-    const int sub = (int)(blockIdx.x % nsub);
-    k_syrk_finish_body<T>(blockIdx.x / nsub, sub * per, (sub + 1) * per, part, nsplit, ntl, nao, scale, K);
+    k_syrk_finish_body<T>(blockIdx.x / nsub, (int)(blockIdx.x % nsub), nsub, part, nsplit, ntl, nao, scale, K);
 }
 
 // Full-tile finish (two factors, no symmetry): K[mu][nu] = scale * sum_s
@@ -900,23 +907,29 @@ int run_gemm1(dfjk_ctx* h, const void* C, int64_t ncol, void* X, int64_t ldx, bo
 // 8192 / 16384 workgroups, two factors at nao=500 2.36 / 2.08 / 2.10 / 2.21 / 2.28.
 // Short contractions keep 384 rows a split (naux=103 at nao=1024) unless that
 // leaves CUs idle: then down to
-// kMinRows64 rows: nao=64, naux=256, nocc=16 GEMM2 + finish 0.054 -> 0.022 ms,
+// kMinRows64 rows: nao=64, naux=256, nocc=16 GEMM2 + finish 0.054 -> 0.018 ms,
 // nao=128, naux=512, nocc=24 0.057 -> 0.030.
 // FP32: about 16384 workgroups, no split shorter than 384 rows and no running
 // sum longer than kMaxSum32 terms (the split partials are added in FP64).
-constexpr int64_t kMinRows64 = 48;
-int64_t syrk_max_splits(int64_t nrows, int64_t ntl, bool f32) {  // never falls as nrows grows
+// Partials that fit kSmallPart with 384 rows a split stay within it: a
+// buffer above 2 MiB takes the driver 0.25 ms on a handle's first call, one below 1 to
+// 40 us.
+constexpr int64_t kMinRows64 = 48, kSmallPart = 2 << 20;
+int64_t syrk_max_splits(int64_t nrows, int64_t ntl, int64_t slot, bool f32) {  // never falls as nrows grows
     int64_t nsplit;
     if (f32) {
         nsplit = std::min(std::max(cdiv(16384, ntl), cdiv(nrows, kMaxSum32)), cdiv(nrows, 384));
     } else {
         nsplit = std::max(cdiv(4096, ntl), std::min(cdiv(8192, ntl), nrows / 2048));
-        nsplit = std::min(nsplit, std::max(cdiv(nrows, 384), std::min(cdiv(512, ntl), cdiv(nrows, kMinRows64))));
+        const int64_t base = cdiv(nrows, 384), fit = kSmallPart / (8 * slot * slot * ntl);
+        int64_t more = std::min(cdiv(512, ntl), cdiv(nrows, kMinRows64));
+        if (base <= fit) more = std::min(more, fit);
+        nsplit = std::min(nsplit, std::max(base, more));
     }
     return std::max<int64_t>(nsplit, 1);
 }
-void syrk_splits(int64_t nrows, int64_t ntl, bool f32, int64_t* nsplit_out, int64_t* kchunk_out) {
-    const int64_t nsplit = syrk_max_splits(nrows, ntl, f32);
+void syrk_splits(int64_t nrows, int64_t ntl, int64_t slot, bool f32, int64_t* nsplit_out, int64_t* kchunk_out) {
+    const int64_t nsplit = syrk_max_splits(nrows, ntl, slot, f32);
     const int64_t kchunk = cdiv(cdiv(nrows, nsplit), KC) * KC;
     *nsplit_out = cdiv(nrows, kchunk);
     *kchunk_out = kchunk;
@@ -932,10 +945,11 @@ int64_t x_stride(const dfjk_ctx* h, size_t elem) {
     const int64_t V = 16 / (int64_t)elem;
     return cdiv(h->nao, V) * V;
 }
-KBytes k_bytes(const dfjk_ctx* h, size_t elem, int64_t xrows, int64_t nrows, int64_t ntl) {
+KBytes k_bytes(const dfjk_ctx* h, size_t elem, int64_t xrows, int64_t nrows, int64_t ntl, bool full = false) {
     int64_t nsplit, kchunk;
-    syrk_splits(nrows, ntl, elem == 4, &nsplit, &kchunk);
-    return KBytes{elem * (size_t)xrows * (size_t)x_stride(h, elem), elem * (size_t)(nsplit * ntl) * SY_T * SY_T};
+    const size_t slot = (size_t)sy_slot(h->nao, full);
+    syrk_splits(nrows, ntl, (int64_t)slot, elem == 4, &nsplit, &kchunk);
+    return KBytes{elem * (size_t)xrows * (size_t)x_stride(h, elem), elem * (size_t)(nsplit * ntl) * slot * slot};
 }
 
 template <typename T>
@@ -959,7 +973,7 @@ int k_build_t(dfjk_ctx* h, const double* C_in, int64_t ncol, const double* sign,
     if (rc) return rc;
 
     int64_t nsplit, kchunk;
-    syrk_splits(nrows, ntl, sizeof(T) == 4, &nsplit, &kchunk);
+    syrk_splits(nrows, ntl, sy_slot(h->nao, false), sizeof(T) == 4, &nsplit, &kchunk);
     T* part = static_cast<T*>(h->kpart.ptr);
     h->prof.begin(PH_K_SYRK, h->stream);
     if (sign)
@@ -991,7 +1005,7 @@ int k_build_pair_t(dfjk_ctx* h, const double* L_in, const double* R_in, int64_t 
     const int64_t nt = cdiv(h->nao, SY_T);
     const int64_t ntl = sym ? nt * (nt + 1) / 2 : nt * nt;
     const int64_t nrows = sym ? 2 * n1 : n1;  // contraction length
-    const KBytes need = k_bytes(h, sizeof(T), 2 * n1, nrows, ntl);
+    const KBytes need = k_bytes(h, sizeof(T), 2 * n1, nrows, ntl, !sym);
     int rc;
     if ((rc = h->X.ensure(need.X)) || (rc = h->kpart.ensure(need.kpart)) || (rc = h->Cw.ensure(c_bytes(h, ncol, 2))))
         return rc;
@@ -1010,7 +1024,7 @@ int k_build_pair_t(dfjk_ctx* h, const double* L_in, const double* R_in, int64_t 
     if (rc) return rc;
 
     int64_t nsplit, kchunk;
-    syrk_splits(nrows, ntl, sizeof(T) == 4, &nsplit, &kchunk);
+    syrk_splits(nrows, ntl, sy_slot(h->nao, !sym), sizeof(T) == 4, &nsplit, &kchunk);
     T* part = static_cast<T*>(h->kpart.ptr);
     const dim3 grid((unsigned)(ntl * nsplit));
     h->prof.begin(PH_K_SYRK, h->stream);
@@ -1118,7 +1132,7 @@ int k_build_density_t(dfjk_ctx* h, const double* D, double* K) {
     if (rc) return rc;
     DFJK_LAUNCH_CHECK("unpack_rows");
     int64_t nsplit, kchunk;
-    syrk_splits(nrows, ntl, f32, &nsplit, &kchunk);
+    syrk_splits(nrows, ntl, sy_slot(nao, false), f32, &nsplit, &kchunk);
     T* part = static_cast<T*>(h->kpart.ptr);
     h->prof.begin(PH_K_SYRK, st);
     k_syrk<T, SY_PAIR_LOWER><<<dim3((unsigned)(ntl * nsplit)), kThreads, 0, st>>>(X, ldx, nrows, nao, nao, nullptr,
@@ -1145,9 +1159,7 @@ __global__ __launch_bounds__(kThreads) void kb_kernel(int kind, const MolDesc* _
         const int64_t e = lid * kThreads + threadIdx.x;
         if (e < d.nao * d.nocc) as_global(d.Cf)[e / d.nocc * d.ldcf + e % d.nocc] = (float)as_global(d.C)[e];
     } else if (kind == BP_KFIN) {
-        constexpr int per = SY_T * SY_T / kFinSub;
-        const int sub = (int)(lid % kFinSub);
-        k_syrk_finish_body<float>(lid / kFinSub, sub * per, (sub + 1) * per, as_global(d.kpart), d.nsplit, d.ntl,
+        k_syrk_finish_body<float>(lid / kFinSub, (int)(lid % kFinSub), kFinSub, as_global(d.kpart), d.nsplit, d.ntl,
                                   d.nao, 2.0, as_global(d.K));
     }
 }
@@ -1285,10 +1297,12 @@ int k_reserve(dfjk_ctx* h, int64_t max_ncol) {
     // the partials by the splits aimed at, not those that whole chunks leave: a
     // call of fewer columns may be cut into more of them (24600 rows into 385,
     // 24576 into 512)
-    const auto partials = [&](int64_t nrows, int64_t ntl) {
-        return elem * (size_t)(syrk_max_splits(nrows, ntl, elem == 4) * ntl) * SY_T * SY_T;
+    const auto partials = [&](int64_t nrows, int64_t ntl, bool full) {
+        const size_t slot = (size_t)sy_slot(h->nao, full);
+        return elem * (size_t)(syrk_max_splits(nrows, ntl, (int64_t)slot, elem == 4) * ntl) * slot * slot;
     };
-    const size_t kp = std::max({partials(n1, lower), partials(2 * half, lower), partials(half, nt * nt)});
+    const size_t kp =
+        std::max({partials(n1, lower, false), partials(2 * half, lower, false), partials(half, nt * nt, true)});
     int rc;
     if ((rc = h->X.ensure(a.X > b.X ? a.X : b.X))) return rc;
     if ((rc = h->kpart.ensure(kp))) return rc;
