@@ -912,7 +912,7 @@ int run_gemm1(dfjk_ctx* h, const void* C, int64_t ncol, void* X, int64_t ldx, bo
 // FP32: about 16384 workgroups, no split shorter than 384 rows and no running
 // sum longer than kMaxSum32 terms (the split partials are added in FP64).
 // Partials that fit kSmallPart with 384 rows a split stay within it: a
-// buffer above 2 MiB takes the driver 0.25 ms on a handle's first call, one below 1 to
+// buffer above 2 MiB takes 0.25 ms to allocate on a handle's first call, one below 1 to
 // 40 us.
 constexpr int64_t kMinRows64 = 48, kSmallPart = 2 << 20;
 int64_t syrk_max_splits(int64_t nrows, int64_t ntl, int64_t slot, bool f32) {  // never falls as nrows grows
