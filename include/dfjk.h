@@ -256,7 +256,8 @@ int dfjk_scf_step(dfjk_handle h, const double* H_dev, double* D_dev, double* Coc
  * Aufbau occupation of a symmetric nao x nao matrix F (e.g. the core
  * Hamiltonian for the core guess): Cocc <- eigenvectors of the nocc lowest
  * eigenvalues (nao x nocc), and, if D_dev is not NULL, D <- 2 C C^T.  Uses
- * the handle's eigensolver workspace and stream (nao <= 4096).
+ * the handle's eigensolver workspace and stream (nao <= 4096).  An infinity or
+ * a NaN anywhere in F makes all of C and D NaN.
  */
 int dfjk_aufbau(dfjk_handle h, const double* F_dev, int64_t nocc, double* Cocc_dev, double* D_dev);
 

@@ -59,7 +59,7 @@ struct EigWork {
 // v_identity V is taken as the identity and need not be set), on exit row k of
 // V is an eigenvector of F.  out (n x ncol) = eigenvector columns of the ncol
 // smallest eigenvalues; mode 1 scales column c by sqrt|w_c| and writes
-// sign(w_c) to sign.
+// sign(w_c) to sign.  A non-finite entry in X: w and out are NaN, V is as on entry.
 int eigh_cols(hipStream_t st, const double* X, double* V, int n, bool v_identity, const EigWork& ws, int ncol,
               int mode, double* out, double* sign);
 

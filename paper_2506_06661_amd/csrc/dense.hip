@@ -452,7 +452,8 @@ __global__ __launch_bounds__(256, 2) void bgemm_net(int64_t M, int64_t N, int64_
 // Parallel cyclic Jacobi in one workgroup on a symmetric n x n matrix A (overwritten; the
 // eigenvalues end on its diagonal).  Vt (n x n) holds the basis as ROWS: it
 // starts as the caller's basis (rows orthonormal) and its row k ends as the
-// eigenvector of diagonal entry k.  Each sweep visits every pair (p,q) once in
+// eigenvector of diagonal entry k.  A matrix with an infinity or a NaN is left
+// alone and reported as -1 sweeps.  Each sweep visits every pair (p,q) once in
 // the round-robin (circle) order: n-1 rounds of n/2 disjoint pairs (a dummy
 // index when n is odd).  Rotations follow the symmetric Schur step of Golub &
 // Van Loan (Matrix Computations, 8.5.2): with J[p][p] = J[q][q] = c,
@@ -494,6 +495,18 @@ __global__ __launch_bounds__(JT) void jacobi_kernel(double* __restrict__ A, doub
     const int half = m / 2;
     double* cc = cs;
     double* ss = cs + half;
+    uint32_t top = 0;  // of the largest entry
+    for (int64_t e = threadIdx.x; e < (int64_t)n * n; e += JT) top = max(top, top_bits(A[e]));
+    top = wave_max(top);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = (double)top;
+    __syncthreads();
+    double topd = 0.0;
+    for (int w = 0; w < JT / 64; ++w) topd = fmax(topd, red[w]);
+    __syncthreads();
+    if (!(topd < (double)kNotFinite)) {
+        if (threadIdx.x == 0) *sweeps_done = -1;
+        return;
+    }
     int sweep = 0;
     for (; sweep < max_sweeps; ++sweep) {
         // convergence test: off-diagonal norm against the full norm
@@ -592,11 +605,17 @@ __global__ __launch_bounds__(JT) void jacobi_kernel(double* __restrict__ A, doub
     if (threadIdx.x == 0) *sweeps_done = sweep;
 }
 
-// Ascending order of the diagonal of A (ties by index): rank[i] = position.
-__global__ void eig_rank(const double* __restrict__ A, int n, int* __restrict__ pos_of_rank,
-                         double* __restrict__ w) {
+// Ascending order of the diagonal of A (ties by index): rank[i] = position.  Without a
+// solution (sweeps < 0) the index and NaN: every place of the order is written.
+__global__ void eig_rank(const double* __restrict__ A, int n, const int* __restrict__ sweeps,
+                         int* __restrict__ pos_of_rank, double* __restrict__ w) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
+    if (*sweeps < 0) {
+        pos_of_rank[i] = i;
+        w[i] = __builtin_nan("");
+        return;
+    }
     const double ai = A[(int64_t)i * n + i];
     int rank = 0;
     for (int j = 0; j < n; ++j) {
@@ -616,6 +635,7 @@ __global__ void gather_cols(const double* __restrict__ Vt, int n, const int* __r
     const int r = (int)(e / ncol), c = (int)(e % ncol);
     double f = 1.0;
     if (mode == 1) f = sqrt(fabs(w[c]));  // signed square-root factor
+    if (w[c] != w[c]) f = w[c];           // no solution
     out[e] = f * Vt[(int64_t)pos_of_rank[c] * n + r];
     if (sign && r == 0) sign[c] = w[c] < 0.0 ? -1.0 : 1.0;
 }
@@ -721,7 +741,7 @@ int eigh_cols(hipStream_t st, const double* X, double* V, int n, bool v_identity
     // then never met)
     jacobi_kernel<<<1, JT, 0, st>>>(ws.A, V, n, ws.work, 40, 1e-13, ws.iwork);
     DFJK_LAUNCH_CHECK("jacobi_kernel");
-    eig_rank<<<dim3((unsigned)cdiv(n, 256)), 256, 0, st>>>(ws.A, n, ws.iwork + 1, ws.w);
+    eig_rank<<<dim3((unsigned)cdiv(n, 256)), 256, 0, st>>>(ws.A, n, ws.iwork, ws.iwork + 1, ws.w);
     DFJK_LAUNCH_CHECK("eig_rank");
     gather_cols<<<dim3((unsigned)cdiv((int64_t)n * ncol, 256)), 256, 0, st>>>(V, n, ws.iwork + 1, ncol, ws.w, mode,
                                                                                out, sign);

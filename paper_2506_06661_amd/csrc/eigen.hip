@@ -209,6 +209,7 @@ __device__ __forceinline__ void jacobi_solve(const double* __restrict__ X, int n
     // blocks of this thread (negative: none) and where their results go
     int kk2[NB];  // k | kk << 16
     uint32_t to[NB][2];
+    uint32_t top = 0;  // of the largest entry
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         const int b = self(j);
@@ -223,7 +224,9 @@ __device__ __forceinline__ void jacobi_solve(const double* __restrict__ X, int n
             for (int e = 0; e < 4; ++e) {
                 const int i = 2 * k + (e >> 1), q = 2 * kk + (e & 1);
                 p[e] = h > 1 ? (uint32_t)place_of(next_pos(i, h), next_pos(q, h), h, nblk) : (uint32_t)(e * nblk + b);
-                Abuf[0][e * nblk + b] = elem(i, q);
+                const double x = elem(i, q);
+                top = max(top, top_bits(x));
+                Abuf[0][e * nblk + b] = x;
             }
             to[j][0] = p[0] | (p[1] << 16);
             to[j][1] = p[2] | (p[3] << 16);
@@ -237,7 +240,12 @@ __device__ __forceinline__ void jacobi_solve(const double* __restrict__ X, int n
     const int lo = ku < kv ? ku : kv, hi = ku < kv ? kv : ku;
     const int bu = blk_of(ku, ku, h), bv = blk_of(kv, kv, h), bx = blk_of(lo, hi, h);
     const bool rot_thread = tid < h;
+    top = wave_max(top);
+    if ((tid & 63) == 0) red[0][tid >> 6] = (double)top;
     __syncthreads();
+    double topd = 0.0;
+    for (int q = 0; q < nthr / 64; ++q) topd = fmax(topd, red[0][q]);
+    const bool finite = topd < (double)kNotFinite;  // else there is nothing to solve: no sweep, NaN results
     double c = 1.0, s = 0.0;  // rotation thread: the rotation of the round to come
     if (rot_thread) {
         const int b = blk_of(ak, ak, h);
@@ -247,7 +255,7 @@ __device__ __forceinline__ void jacobi_solve(const double* __restrict__ X, int n
     }
     int cur = 0, par = 0, sweep = 0, logged = 0;
     __syncthreads();
-    for (; sweep < kEigMaxSweeps; ++sweep) {
+    for (; finite && sweep < kEigMaxSweeps; ++sweep) {
         // off-diagonal norm against the full norm
         double off = 0.0, dia = 0.0;
 #pragma unroll
@@ -343,8 +351,7 @@ __device__ __forceinline__ void jacobi_solve(const double* __restrict__ X, int n
             if (DB) cur ^= 1;
         }
     }
-    // ascending order of the diagonal (ties by index; a NaN sorts nowhere, but
-    // every rank stays in range)
+    // ascending order of the diagonal (ties by index); where it has none, the index
     __syncthreads();
     double* dg = reinterpret_cast<double*>(smem);  // overwrites cs, not the blocks
     double di = 0.0;
@@ -357,13 +364,17 @@ __device__ __forceinline__ void jacobi_solve(const double* __restrict__ X, int n
     if (tid < n) {
         int rank = 0;
         for (int j = 0; j < n; ++j) rank += (dg[j] < di || (dg[j] == di && j < tid)) ? 1 : 0;
+        if (!finite) {
+            rank = tid;
+            di = __builtin_nan("");
+        }
         iwork[1 + rank] = tid;
         iwork[EigWork::rank_at(n) + tid] = rank;
         w[rank] = di;
     }
     if (tid == 0) {
         iwork[0] = sweep;
-        iwork[EigWork::rounds_at(n)] = logged;
+        iwork[EigWork::rounds_at(n)] = finite ? logged : -1;
     }
 }
 
@@ -388,7 +399,8 @@ __device__ __forceinline__ void apply_log(const double2* __restrict__ log, const
     const int h = (n + 1) / 2;
     double xt[R], xb[R];
     load_column<R>(V, v_identity != 0, n, col, xt, xb);
-    apply_rounds<R, 8>(log, iwork[EigWork::rounds_at(n)], h, xt, xb);
+    const int rounds = iwork[EigWork::rounds_at(n)];  // negative: no eigenvectors
+    apply_rounds<R, 8>(log, rounds, h, xt, xb);
     store_column<R>(V, n, col, xt, xb);
 #pragma unroll
     for (int q = 0; q < 2 * R; ++q) {
@@ -397,7 +409,7 @@ __device__ __forceinline__ void apply_log(const double2* __restrict__ log, const
         const int c = iwork[EigWork::rank_at(n) + i];
         if (c >= ncol) continue;
         const double x = (q & 1) ? xb[q >> 1] : xt[q >> 1];
-        const double f = mode == 1 ? sqrt(fabs(w[c])) : 1.0;
+        const double f = rounds < 0 ? __builtin_nan("") : mode == 1 ? sqrt(fabs(w[c])) : 1.0;
         out[(int64_t)col * ncol + c] = f * x;
         if (sign && col == 0) sign[c] = w[c] < 0.0 ? -1.0 : 1.0;
     }

@@ -18,6 +18,21 @@ __device__ inline float wave_sum(float v) {
     return v;
 }
 
+// Largest value of the 64 lanes, in every lane
+__device__ inline uint32_t wave_max(uint32_t v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const uint32_t o = (uint32_t)__shfl_xor((int)v, off, 64);
+        v = o > v ? o : v;
+    }
+    return v;
+}
+
+// Exponent and leading mantissa bits of |x|: they order as |x| does, with every
+// infinity and NaN at or above kNotFinite.
+constexpr uint32_t kNotFinite = 0x7ff00000u;
+__device__ inline uint32_t top_bits(double x) { return (uint32_t)__double2hiint(x) & 0x7fffffffu; }
+
 // Knuth's TwoSum: s + e == a + b exactly (round-to-nearest, no overflow).
 __device__ inline void two_sum(float a, float b, float& s, float& e) {
     s = a + b;
