@@ -507,6 +507,11 @@ __global__ __launch_bounds__(JT) void jacobi_kernel(double* __restrict__ A, doub
         if (threadIdx.x == 0) *sweeps_done = -1;
         return;
     }
+    const int ex = eig_exponent((uint32_t)topd);
+    if (ex != 0) {  // scaled by 2^-ex: exact
+        for (int64_t e = threadIdx.x; e < (int64_t)n * n; e += JT) A[e] *= pow2(-ex);
+        __syncthreads();
+    }
     int sweep = 0;
     for (; sweep < max_sweeps; ++sweep) {
         // convergence test: off-diagonal norm against the full norm
@@ -602,6 +607,8 @@ __global__ __launch_bounds__(JT) void jacobi_kernel(double* __restrict__ A, doub
             __syncthreads();
         }
     }
+    if (ex != 0)
+        for (int i = threadIdx.x; i < n; i += JT) A[(int64_t)i * n + i] *= pow2(ex);
     if (threadIdx.x == 0) *sweeps_done = sweep;
 }
 

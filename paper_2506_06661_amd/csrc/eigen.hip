@@ -246,6 +246,15 @@ __device__ __forceinline__ void jacobi_solve(const double* __restrict__ X, int n
     double topd = 0.0;
     for (int q = 0; q < nthr / 64; ++q) topd = fmax(topd, red[0][q]);
     const bool finite = topd < (double)kNotFinite;  // else there is nothing to solve: no sweep, NaN results
+    const int ex = eig_exponent((uint32_t)topd);
+    if (ex != 0) {  // scaled by 2^-ex: exact
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+            if (kk2[j] >= 0)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) Abuf[0][e * nblk + self(j)] *= pow2(-ex);
+        __syncthreads();
+    }
     double c = 1.0, s = 0.0;  // rotation thread: the rotation of the round to come
     if (rot_thread) {
         const int b = blk_of(ak, ak, h);
@@ -370,7 +379,7 @@ __device__ __forceinline__ void jacobi_solve(const double* __restrict__ X, int n
         }
         iwork[1 + rank] = tid;
         iwork[EigWork::rank_at(n) + tid] = rank;
-        w[rank] = di;
+        w[rank] = di * pow2(ex);
     }
     if (tid == 0) {
         iwork[0] = sweep;

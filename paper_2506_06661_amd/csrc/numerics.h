@@ -33,6 +33,18 @@ __device__ inline uint32_t wave_max(uint32_t v) {
 constexpr uint32_t kNotFinite = 0x7ff00000u;
 __device__ inline uint32_t top_bits(double x) { return (uint32_t)__double2hiint(x) & 0x7fffffffu; }
 
+// Exponent e of the power of two that the eigensolvers divide a matrix by, from the
+// top bits of its largest entry: 0, so the matrix as it is, while the squares of its
+// entries and their sum are far from the ends of the range; else that entry's own
+// exponent (1000 at most, so that 2^e and 2^-e are normal).  Without it the norms
+// overflowed from about 1e154 / n on and vanished below 1e-162, and the sweeps
+// stopped before the first one.
+__device__ inline int eig_exponent(uint32_t top) {
+    const int e = (int)(top >> 20) - 1023;
+    return e > 400 || e < -400 ? (e < -1000 ? -1000 : e > 1000 ? 1000 : e) : 0;
+}
+__device__ inline double pow2(int e) { return __hiloint2double((e + 1023) << 20, 0); }
+
 // Knuth's TwoSum: s + e == a + b exactly (round-to-nearest, no overflow).
 __device__ inline void two_sum(float a, float b, float& s, float& e) {
     s = a + b;
