@@ -136,7 +136,8 @@ __global__ __launch_bounds__(256) void head_grad(const float* __restrict__ Z2, c
 #pragma unroll
         for (int q = 0; q < 4; ++q) gw[c][q] = gb[c][q] = 0.f;
     }
-    float loss = 0.f, sgy = 0.f;
+    float sgy = 0.f;
+    double loss = 0.0;  // one value per row for the whole wavefront: FP64 costs nothing here
     float zn[NC][4];  // the next row, loaded while this one is worked on
     auto load = [&](int64_t i) {
 #pragma unroll
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(256) void head_grad(const float* __restrict__ Z2, c
         s = wave_sum(s);
         const float d = (s + b0) - t[i];
         const float gy = two_n * d;
-        loss = __builtin_fmaf(d, d, loss);
+        loss = fma((double)d, (double)d, loss);
         sgy += gy;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(256) void head_grad(const float* __restrict__ Z2, c
         emit(gb[c], out, c * 256, h);
         emit(gw[c], out + h, c * 256, h);
     }
-    const float last[4] = {sgy, loss, 0.f, 0.f};  // lane 0's columns
+    const float last[4] = {sgy, (float)loss, 0.f, 0.f};  // lane 0's columns
     emit(last, out + 2 * h, 0, 2);
 }
 
@@ -240,26 +241,26 @@ __global__ __launch_bounds__(256) void layer1_grad(const float* __restrict__ G, 
     }
 }
 
-// out[c] = sum_p part[p * ld + c] for c < cols, in a fixed order: a workgroup
-// adds 64 columns, its four wavefronts a quarter of the parts each.  With
+// out[c] = sum_p part[p * ld + c] for c < cols, in FP64 and a fixed order: a
+// workgroup adds 64 columns, its four wavefronts a quarter of the parts each.  With
 // loss, the column past them is the sum of squares: loss = inv_n times it.
 __global__ __launch_bounds__(256) void sum_parts(const float* __restrict__ part, int64_t np, int64_t ld,
                                                  int64_t cols, float* __restrict__ out, float* __restrict__ loss,
-                                                 float inv_n) {
-    __shared__ float red[4][64];
+                                                 double inv_n) {
+    __shared__ double red[4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t c = (int64_t)blockIdx.x * 64 + lane;
     const int64_t q = (np + 3) / 4, p0 = wave * q, p1 = p0 + q < np ? p0 + q : np;
-    float s = 0.f;
+    double s = 0.0;
     if (c < cols + (loss ? 1 : 0)) {
 #pragma unroll 8
-        for (int64_t p = p0; p < p1; ++p) s += part[p * ld + c];
+        for (int64_t p = p0; p < p1; ++p) s += (double)part[p * ld + c];
     }
     red[wave][lane] = s;
     __syncthreads();
-    const float v = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
-    if (wave == 0 && c < cols) out[c] = v;
-    if (wave == 0 && c == cols && loss) loss[0] = v * inv_n;
+    const double v = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    if (wave == 0 && c < cols) out[c] = (float)v;
+    if (wave == 0 && c == cols && loss) loss[0] = (float)(v * inv_n);
 }
 
 __global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
@@ -426,7 +427,7 @@ int hidden_layers(dfjk_mlp_ctx* m, const float* X, int64_t n, Act& a, bool keep)
 }
 
 int add_parts(dfjk_mlp_ctx* m, const float* part, int64_t np, int64_t ld, int64_t cols, float* out,
-              float* loss = nullptr, float inv_n = 0.f) {
+              float* loss = nullptr, double inv_n = 0.0) {
     sum_parts<<<dim3((unsigned)cdiv(cols + 1, 64)), 256, 0, m->stream>>>(part, np, ld, cols, out, loss, inv_n);
     DFJK_LAUNCH_CHECK("sum_parts");
     return DFJK_OK;
@@ -566,7 +567,7 @@ int dfjk_mlp_loss_grad(dfjk_mlp m, const float* X, const float* t, int64_t n, fl
         head_grad<4><<<dim3((unsigned)nrow), 256, 0, st>>>(a.Z2, P + m->oW3, P + m->ob3, t, n, H, per, a.gZ2, part);
     DFJK_LAUNCH_CHECK("head_grad");
     // b2, W3 and b3 lie one after the other in the parameters, as in the parts
-    if ((rc = add_parts(m, part, nrow, 2 * H + 2, 2 * H + 1, G + m->ob2, a.loss, 1.f / (float)n))) return rc;
+    if ((rc = add_parts(m, part, nrow, 2 * H + 2, 2 * H + 1, G + m->ob2, a.loss, 1.0 / (double)n))) return rc;
     // layer 2
     const int64_t slab = slab_of(n);
     if ((rc = net_gemm(st, bf, true, false, H, H, n, a.gZ2, H, a.A1, H, part, H, slab))) return rc;
