@@ -367,11 +367,16 @@ __global__ void gather_rows(const float* __restrict__ X, const int64_t* __restri
     Y[e] = X[idx[r] * d + (e - r * d)];
 }
 
-// Batch rows per partial sum: at least kSlab, and at most kMaxSlabs partials
-// (a 256 x 256 weight gradient then has 4 x 128 workgroups at 65536 rows, two
-// per CU, and its partials stay below 64 MB whatever the batch).
-constexpr int64_t kSlab = 512, kMaxSlabs = 256;
-inline int64_t slab_of(int64_t n) { return std::max(kSlab, cdiv(cdiv(n, kMaxSlabs), 16) * 16); }
+// Batch rows per partial sum of the weight gradient: at least kSlab and, while no FP32
+// running sum gets longer than kMaxSlab rows for it, at most kMaxSlabs partials (a
+// 256 x 256 gradient then has 4 x 128 workgroups at 65536 rows, two per CU, and
+// 64 MB of partials up to 524288 rows).
+constexpr int64_t kSlab = 512, kMaxSlab = 2048, kMaxSlabs = 256;
+inline int64_t slab_of(int64_t n) {
+    return std::min(std::max(kSlab, cdiv(cdiv(n, kMaxSlabs), 16) * 16), kMaxSlab);
+}
+// Most partials that any batch of up to n rows takes
+inline int64_t max_slabs(int64_t n) { return std::max(std::min(cdiv(n, kSlab), kMaxSlabs), cdiv(n, kMaxSlab)); }
 // Rows per workgroup of the row passes (head_grad, layer1_grad): about 1024
 // workgroups, four per CU
 constexpr int64_t kRowParts = 1024;
@@ -483,7 +488,7 @@ int dfjk_mlp_init(dfjk_mlp* out, int d_in, int hidden, int64_t max_batch, void* 
     const size_t pb = sizeof(float) * (size_t)m->nparam;
     // partial sums: weight-gradient slabs, then the row passes' workgroups
     // (every batch up to max_batch takes at most as many)
-    const int64_t nslab = std::min(cdiv(max_batch, kSlab), kMaxSlabs);
+    const int64_t nslab = max_slabs(max_batch);
     const int64_t nrow = std::min<int64_t>(cdiv(max_batch, 16), kRowParts);
     int rc;
     if ((rc = m->params.ensure(pb)) || (rc = m->grads.ensure(pb)) || (rc = m->m1.ensure(pb)) ||

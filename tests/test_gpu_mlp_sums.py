@@ -37,3 +37,23 @@ def test_loss(t):
     loss, _ = step(params, 0.5, t)
     ref = float(np.float32(t)) ** 2
     assert abs(loss - ref) <= 8 * U * ref
+
+
+def test_gradient():
+    """No FP32 running sum is longer than 2048 rows in the hidden weights' gradient
+    and 4096 in the others (a wavefront's rows); their partials are added in FP64.  64 u
+    more for the elementwise steps, relative to the sums of absolute values."""
+    import oracle
+    print(f"gradient of {ROWS} rows", flush=True)
+    rng = np.random.default_rng(5)
+    params = [rng.uniform(0.1, 1.0, s).astype(np.float32) for s in ((16, 1), 16, (16, 16), 16, (1, 16), 1)]
+    x, t = 0.7, 0.3
+    p64 = [p.astype(np.float64) for p in params]
+    # one row; every weight and activation is positive, so no sum cancels
+    L, g = oracle.mlp_loss_grad(p64, np.array([[float(np.float32(x))]]), np.array([float(np.float32(t))]))
+    loss, got = step(params, x, t)
+    for k, (a, b) in enumerate(zip(got, g)):
+        rel = np.abs(a.reshape(b.shape) - b) / np.abs(b)
+        print(k, rel.max() / U, flush=True)
+        assert rel.max() <= ((2048 if k == 2 else 4096) + 64) * U, (k, rel.max() / U)
+    assert abs(loss - L) <= 200 * U * L
