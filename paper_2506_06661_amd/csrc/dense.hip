@@ -196,24 +196,26 @@ __global__ __launch_bounds__(256) void gemm_small(int M, int N, int K, double al
 
 // ---------------------------------------------------------------- network products
 // The FP32 and BF16 products of the perceptron: activations (n x hidden),
-// the input gradient and the weight gradient.  128 x 128 tile per workgroup,
-// 2 x 2 wavefronts of 64 x 64 (16 accumulator blocks of 16 x 16 each), the
-// contraction in chunks staged through registers into two LDS buffers.  The
+// the input gradient and the weight gradient.  128 x 128 tile per workgroup (64 x 64
+// where those are few, see kNetTiles), 2 x 2 wavefronts of a quarter of it each (16 or 4
+// accumulator blocks of 16 x 16), the contraction in chunks staged through
+// registers into two LDS buffers.  The
 // products are bound by the FP32 matrix cores (256 x 256 weights: 64 flop per
 // byte of activation), so each operand element read from LDS is used four
-// times and the chunk loop holds nothing but loads, LDS moves and products.
+// times (twice in the small tiles) and the chunk loop holds nothing but loads, LDS moves
+// and products.
 // The weight gradient contracts over the batch rows: its slabs are the third
 // grid dimension of ONE launch.  Measured at 65536 rows, 256 x 256 weights:
 // 32 launches of 16 workgroups each, on 64 x 64 tiles without prefetch, took
 // 10.9 ms; one launch of 4 x 128 workgroups takes 0.091 ms (94 TFLOP/s).
 //
 // Operand panels are kept as rows of the contraction index k.  FP32 rows are
-// 144 floats apart (16 modulo 64 banks, so the 4 rows of an operand read use
+// 144 or 80 floats apart (16 modulo 64 banks, so the 4 rows of an operand read use
 // disjoint banks) and row k keeps column m at m ^ 16 (k / 4 % 4): a thread
 // that holds 4 consecutive k of one column (operand contiguous along k)
 // stores them to 4 rows without bank conflicts, and the reads, whose k / 4 is
 // the step number, only see their 16-column groups renumbered.
-constexpr int NT_M = 128, NT_K = 16, NT_P = NT_M + 16;
+constexpr int NT_M = 128, NT_K = 16;
 
 // 4 consecutive floats from any float address; elements at or past lim are 0
 __device__ inline void load4(float (&v)[4], const float* __restrict__ p, int64_t lim) {
@@ -230,19 +232,19 @@ __device__ inline float dsilu_f(float z) {
     return s * (1.f + z * (1.f - s));
 }
 
-template <int EPI>
-__device__ __attribute__((always_inline)) inline void net_store(const v4f (&acc)[4][4], int64_t m0, int64_t n0, int wm, int wn, int lane,
+template <int EPI, int R>
+__device__ __attribute__((always_inline)) inline void net_store(const v4f (&acc)[R][R], int64_t m0, int64_t n0, int wm, int wn, int lane,
                                  int64_t M, int64_t N, float* __restrict__ C, int64_t ldc, const GemmEpi& e) {
 #pragma unroll
-    for (int tj = 0; tj < 4; ++tj) {
-        const int64_t gn = n0 + wn * 64 + tj * 16 + (lane & 15);
+    for (int tj = 0; tj < R; ++tj) {
+        const int64_t gn = n0 + wn * (16 * R) + tj * 16 + (lane & 15);
         if (gn >= N) continue;
         const float bias = EPI == EPI_BIAS ? e.bias[gn] : 0.f;
 #pragma unroll
-        for (int ti = 0; ti < 4; ++ti)
+        for (int ti = 0; ti < R; ++ti)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int64_t gm = m0 + wm * 64 + ti * 16 + 4 * (lane >> 4) + r;
+                const int64_t gm = m0 + wm * (16 * R) + ti * 16 + 4 * (lane >> 4) + r;
                 if (gm >= M) continue;
                 float v = acc[ti][tj][r];
                 if (EPI == EPI_BIAS) v += bias;
@@ -255,39 +257,43 @@ __device__ __attribute__((always_inline)) inline void net_store(const v4f (&acc)
 // Tile and slab of this workgroup.  Workgroups go round-robin to the 8 XCDs;
 // those that read the same rows (the column tiles of 128 rows, or all tiles
 // of one slab) are numbered 8 apart, so one XCD's L2 fetches the rows once.
+template <int NT>
 __device__ inline bool net_tile(int64_t M, int64_t N, int64_t K, int64_t kslab, int64_t& m0, int64_t& n0,
                                 int64_t& slab) {
-    const int64_t nbn = cdiv(N, NT_M), nbm = cdiv(M, NT_M);
+    const int64_t nbn = cdiv(N, NT), nbm = cdiv(M, NT);
     const int64_t inner = kslab ? nbm * nbn : nbn, q = blockIdx.x >> 3;
     const int64_t unit = q / inner * 8 + (blockIdx.x & 7), t = q % inner;
-    n0 = t % nbn * NT_M;
-    m0 = (kslab ? t / nbn : unit) * NT_M;
+    n0 = t % nbn * NT;
+    m0 = (kslab ? t / nbn : unit) * NT;
     slab = kslab ? unit : 0;
     return unit < (kslab ? cdiv(K, kslab) : nbm);
 }
 
-template <bool TA, bool TB, int EPI>
+// NT: edge of the tile
+template <int NT, bool TA, bool TB, int EPI>
 __global__ __launch_bounds__(256, 3) void sgemm_net(int64_t M, int64_t N, int64_t K, const float* __restrict__ A,
                                                      int64_t lda, const float* __restrict__ B, int64_t ldb,
                                                      float* __restrict__ C, int64_t ldc, int64_t kslab, GemmEpi e) {
-    __shared__ __attribute__((aligned(16))) float sA[2][NT_K][NT_P];
-    __shared__ __attribute__((aligned(16))) float sB[2][NT_K][NT_P];
+    constexpr int P = NT + 16, R = NT / 32;                   // LDS pitch; 16 x 16 blocks per wavefront and edge
+    constexpr int NL = NT / 64, TR = NT / 4, RR = 256 / TR;   // loads per operand; row-contiguous: threads per row, rows per load
+    __shared__ __attribute__((aligned(16))) float sA[2][NT_K][P];
+    __shared__ __attribute__((aligned(16))) float sB[2][NT_K][P];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     int64_t m0, n0, slab;
-    if (!net_tile(M, N, K, kslab, m0, n0, slab)) return;
+    if (!net_tile<NT>(M, N, K, kslab, m0, n0, slab)) return;
     const int64_t kbeg = slab * kslab;
     const int64_t kend = kslab && kbeg + kslab < K ? kbeg + kslab : K;
-    // k-contiguous operand: thread holds k quad tid % 4 of rows tid / 4 and
-    // tid / 4 + 64; row-contiguous: quad tid % 32 of k rows tid / 32 and + 8
-    const int cr = tid >> 2, cq = 4 * (tid & 3), rr = tid >> 5, rq = 4 * (tid & 31);
-    float ra[2][4], rb[2][4];
-    auto load1 = [&](float (&v)[2][4], const float* __restrict__ S, int64_t ld, bool rows, int64_t lim, int64_t o0,
+    // k-contiguous operand: thread holds k quad tid % 4 of rows tid / 4 + 64 j;
+    // row-contiguous: quad tid % TR of k rows tid / TR + RR j
+    const int cr = tid >> 2, cq = 4 * (tid & 3), rr = tid / TR, rq = 4 * (tid % TR);
+    float ra[NL][4], rb[NL][4];
+    auto load1 = [&](float (&v)[NL][4], const float* __restrict__ S, int64_t ld, bool rows, int64_t lim, int64_t o0,
                      int64_t k0) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NL; ++j) {
             if (rows) {  // S[k][o]
-                const int64_t k = k0 + rr + 8 * j;
+                const int64_t k = k0 + rr + RR * j;
                 load4(v[j], S + k * ld + o0 + rq, k < kend ? lim - (o0 + rq) : 0);
             } else {  // S[o][k]
                 const int64_t o = o0 + cr + 64 * j;
@@ -295,11 +301,11 @@ __global__ __launch_bounds__(256, 3) void sgemm_net(int64_t M, int64_t N, int64_
             }
         }
     };
-    auto store1 = [&](const float (&v)[2][4], float (*S)[NT_P], bool rows) {
+    auto store1 = [&](const float (&v)[NL][4], float (*S)[P], bool rows) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NL; ++j) {
             if (rows) {
-                const int k = rr + 8 * j;
+                const int k = rr + RR * j;
                 __builtin_memcpy(&S[k][rq ^ (16 * ((k >> 2) & 3))], v[j], 16);
             } else {
                 const int o = (cr + 64 * j) ^ (16 * (cq >> 2));
@@ -308,11 +314,11 @@ __global__ __launch_bounds__(256, 3) void sgemm_net(int64_t M, int64_t N, int64_
             }
         }
     };
-    v4f acc[4][4];
+    v4f acc[R][R];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < R; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < R; ++b) acc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
     load1(ra, A, lda, TA, M, m0, kbeg);
     load1(rb, B, ldb, !TB, N, n0, kbeg);
     store1(ra, sA[0], TA);
@@ -328,16 +334,16 @@ __global__ __launch_bounds__(256, 3) void sgemm_net(int64_t M, int64_t N, int64_
 #pragma unroll
         for (int kk = 0; kk < NT_K / 4; ++kk) {
             const int kr = kk * 4 + (lane >> 4);
-            float a[4], b[4];
+            float a[R], b[R];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                a[q] = sA[buf][kr][wm * 64 + (q ^ kk) * 16 + (lane & 15)];
-                b[q] = sB[buf][kr][wn * 64 + (q ^ kk) * 16 + (lane & 15)];
+            for (int q = 0; q < R; ++q) {
+                a[q] = sA[buf][kr][(wm ^ (kk / R)) * (16 * R) + ((q ^ kk) & (R - 1)) * 16 + (lane & 15)];
+                b[q] = sB[buf][kr][(wn ^ (kk / R)) * (16 * R) + ((q ^ kk) & (R - 1)) * 16 + (lane & 15)];
             }
 #pragma unroll
-            for (int ti = 0; ti < 4; ++ti)
+            for (int ti = 0; ti < R; ++ti)
 #pragma unroll
-                for (int tj = 0; tj < 4; ++tj) acc[ti][tj] = Mma<float>::step(a[ti], b[tj], acc[ti][tj]);
+                for (int tj = 0; tj < R; ++tj) acc[ti][tj] = Mma<float>::step(a[ti], b[tj], acc[ti][tj]);
         }
         if (more) {
             store1(ra, sA[buf ^ 1], TA);
@@ -361,31 +367,32 @@ __device__ inline uint32_t pack_bf16(float lo, float hi) {
     return (uint32_t)float_to_bf16_rne(lo) | ((uint32_t)float_to_bf16_rne(hi) << 16);
 }
 
-template <bool TA, bool TB, int EPI>
+template <int NT, bool TA, bool TB, int EPI>
 __global__ __launch_bounds__(256, 2) void bgemm_net(int64_t M, int64_t N, int64_t K, const float* __restrict__ A,
                                                      int64_t lda, const float* __restrict__ B, int64_t ldb,
                                                      float* __restrict__ C, int64_t ldc, int64_t kslab, GemmEpi e) {
-    __shared__ __attribute__((aligned(16))) uint16_t sA[2][NT_M][BROW];
-    __shared__ __attribute__((aligned(16))) uint16_t sB[2][NT_M][BROW];
+    constexpr int R = NT / 32, NL = NT / 64, TR = NT / 4, RR = 2 * 256 / TR;
+    __shared__ __attribute__((aligned(16))) uint16_t sA[2][NT][BROW];
+    __shared__ __attribute__((aligned(16))) uint16_t sB[2][NT][BROW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     int64_t m0, n0, slab;
-    if (!net_tile(M, N, K, kslab, m0, n0, slab)) return;
+    if (!net_tile<NT>(M, N, K, kslab, m0, n0, slab)) return;
     const int64_t kbeg = slab * kslab;
     const int64_t kend = kslab && kbeg + kslab < K ? kbeg + kslab : K;
-    // k-contiguous operand: 8 k at 8 (tid % 4) of rows tid / 4 and + 64;
-    // row-contiguous: the k pair 2 (tid / 32) (and + 16) of columns 4 (tid % 32)
-    const int cr = tid >> 2, cq = 8 * (tid & 3), rr = 2 * (tid >> 5), rq = 4 * (tid & 31);
-    float ra[2][8], rb[2][8];
-    auto load1 = [&](float (&v)[2][8], const float* __restrict__ S, int64_t ld, bool rows, int64_t lim, int64_t o0,
+    // k-contiguous operand: 8 k at 8 (tid % 4) of rows tid / 4 + 64 j;
+    // row-contiguous: the k pair 2 (tid / TR) + RR j of columns 4 (tid % TR)
+    const int cr = tid >> 2, cq = 8 * (tid & 3), rr = 2 * (tid / TR), rq = 4 * (tid % TR);
+    float ra[NL][8], rb[NL][8];
+    auto load1 = [&](float (&v)[NL][8], const float* __restrict__ S, int64_t ld, bool rows, int64_t lim, int64_t o0,
                      int64_t k0) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NL; ++j)
 #pragma unroll
             for (int d = 0; d < 2; ++d) {
                 float w[4];
                 if (rows) {
-                    const int64_t k = k0 + rr + 16 * j + d;
+                    const int64_t k = k0 + rr + RR * j + d;
                     load4(w, S + k * ld + o0 + rq, k < kend ? lim - (o0 + rq) : 0);
                 } else {
                     const int64_t o = o0 + cr + 64 * j, k = k0 + cq + 4 * d;
@@ -395,13 +402,13 @@ __global__ __launch_bounds__(256, 2) void bgemm_net(int64_t M, int64_t N, int64_
                 for (int q = 0; q < 4; ++q) v[j][4 * d + q] = w[q];
             }
     };
-    auto store1 = [&](const float (&v)[2][8], uint16_t (*S)[BROW], bool rows) {
+    auto store1 = [&](const float (&v)[NL][8], uint16_t (*S)[BROW], bool rows) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NL; ++j) {
             if (rows) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<uint32_t*>(&S[rq + q][rr + 16 * j]) = pack_bf16(v[j][q], v[j][4 + q]);
+                    *reinterpret_cast<uint32_t*>(&S[rq + q][rr + RR * j]) = pack_bf16(v[j][q], v[j][4 + q]);
             } else {
                 const u4_d w = u4_d{pack_bf16(v[j][0], v[j][1]), pack_bf16(v[j][2], v[j][3]),
                                     pack_bf16(v[j][4], v[j][5]), pack_bf16(v[j][6], v[j][7])};
@@ -409,11 +416,11 @@ __global__ __launch_bounds__(256, 2) void bgemm_net(int64_t M, int64_t N, int64_
             }
         }
     };
-    v4f acc[4][4];
+    v4f acc[R][R];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < R; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < R; ++b) acc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
     load1(ra, A, lda, TA, M, m0, kbeg);
     load1(rb, B, ldb, !TB, N, n0, kbeg);
     store1(ra, sA[0], TA);
@@ -426,16 +433,16 @@ __global__ __launch_bounds__(256, 2) void bgemm_net(int64_t M, int64_t N, int64_
             load1(ra, A, lda, TA, M, m0, k0 + BK);
             load1(rb, B, ldb, !TB, N, n0, k0 + BK);
         }
-        v8bf_d a[4], b[4];
+        v8bf_d a[R], b[R];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            __builtin_memcpy(&a[q], &sA[buf][wm * 64 + q * 16 + (lane & 15)][8 * (lane >> 4)], 16);
-            __builtin_memcpy(&b[q], &sB[buf][wn * 64 + q * 16 + (lane & 15)][8 * (lane >> 4)], 16);
+        for (int q = 0; q < R; ++q) {
+            __builtin_memcpy(&a[q], &sA[buf][wm * (16 * R) + q * 16 + (lane & 15)][8 * (lane >> 4)], 16);
+            __builtin_memcpy(&b[q], &sB[buf][wn * (16 * R) + q * 16 + (lane & 15)][8 * (lane >> 4)], 16);
         }
 #pragma unroll
-        for (int ti = 0; ti < 4; ++ti)
+        for (int ti = 0; ti < R; ++ti)
 #pragma unroll
-            for (int tj = 0; tj < 4; ++tj)
+            for (int tj = 0; tj < R; ++tj)
                 acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ti], b[tj], acc[ti][tj], 0, 0, 0);
         if (more) {
             store1(ra, sA[buf ^ 1], TA);
@@ -699,27 +706,41 @@ int dgemm(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, dou
     return DFJK_OK;
 }
 
+// Edge of the tile: 128 reads each operand half as often, 64 gives four times the
+// workgroups, each with a quarter of the products in its chain of chunks.  The line is
+// where the 128-wide tiles are two per CU.  Forward pass of n rows, us, 64 and 128
+// (in brackets the number of 128-wide tiles):
+//   FP32, 256 hidden: n=100 27, 45 (2); 8192 37, 52 (128); 20000 62, 76 (314)
+//   FP32, 1024 hidden: n=100 96, 153 (8); 6000 233, 265 (376); 8192 294, 292 (512); 12000 434, 421 (752)
+//   BF16, 1024 hidden: n=100 90, 115; 6000 167, 173; 8192 216, 199; 12000 303, 276
+constexpr int64_t kNetTiles = 512;
+
 template <bool TA, bool TB, int EPI>
-void launch_net(hipStream_t st, bool bf16, dim3 grid, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
+void launch_net(hipStream_t st, bool bf16, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
                 const float* B, int64_t ldb, float* C, int64_t ldc, int64_t kslab, const GemmEpi& e) {
-    if (bf16)
-        bgemm_net<TA, TB, EPI><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
+    const bool small = cdiv(M, NT_M) * cdiv(N, NT_M) * (kslab ? cdiv(K, kslab) : 1) < kNetTiles;
+    const int64_t edge = small ? 64 : NT_M, nbn = cdiv(N, edge), nbm = cdiv(M, edge);
+    const int64_t units = kslab ? cdiv(K, kslab) : nbm, inner = kslab ? nbm * nbn : nbn;
+    const dim3 grid((unsigned)(cdiv(units, 8) * 8 * inner));
+    if (bf16 && small)
+        bgemm_net<64, TA, TB, EPI><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
+    else if (bf16)
+        bgemm_net<NT_M, TA, TB, EPI><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
+    else if (small)
+        sgemm_net<64, TA, TB, EPI><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
     else
-        sgemm_net<TA, TB, EPI><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
+        sgemm_net<NT_M, TA, TB, EPI><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
 }
 
 int net_gemm(hipStream_t st, bool bf16, bool ta, bool tb, int64_t M, int64_t N, int64_t K, const float* A,
              int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int64_t kslab, int epi, GemmEpi e) {
-    const int64_t nbn = cdiv(N, NT_M), nbm = cdiv(M, NT_M);
-    const int64_t units = kslab ? cdiv(K, kslab) : nbm, inner = kslab ? nbm * nbn : nbn;
-    const dim3 grid((unsigned)(cdiv(units, 8) * 8 * inner));
     // the three forms the network uses
     if (!ta && tb && epi == EPI_BIAS)
-        launch_net<false, true, EPI_BIAS>(st, bf16, grid, M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
+        launch_net<false, true, EPI_BIAS>(st, bf16, M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
     else if (!ta && !tb && epi == EPI_DSILU)
-        launch_net<false, false, EPI_DSILU>(st, bf16, grid, M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
+        launch_net<false, false, EPI_DSILU>(st, bf16, M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
     else if (ta && !tb && epi == EPI_NONE)
-        launch_net<true, false, EPI_NONE>(st, bf16, grid, M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
+        launch_net<true, false, EPI_NONE>(st, bf16, M, N, K, A, lda, B, ldb, C, ldc, kslab, e);
     else {
         set_error("net_gemm: form not provided");
         return DFJK_E_INVALID;
