@@ -502,7 +502,16 @@ __device__ __attribute__((always_inline)) inline void sy_loop(const T* __restric
     int rows = (int)(kend - kbeg);       // rows from there on
     int64_t left = boff - kbeg;          // rows from there on below boff (pairs)
     int klive = KC;                      // rows of the chunk in the panels
-    double sg[S::NP];
+    // signs: their upper halves, and the column of each row staged, moved on by a chunk
+    // at a time (whole values spilled, and a remainder of 64-bit numbers per load took
+    // longer than a short chunk's products)
+    uint32_t sg[S::NP];
+    int scol[S::NP];
+    const int sstep = SIGN ? KC % (int)ncol : 0;
+    if (SIGN) {
+#pragma unroll
+        for (int p = 0; p < S::NP; ++p) scol[p] = (int)((kbeg + tid / S::TPR + S::RPP * p) % ncol);
+    }
     auto load = [&]() {
         klive = min(rows, KC);
         if (__builtin_expect(klive < KC, 0)) {
@@ -523,11 +532,11 @@ __device__ __attribute__((always_inline)) inline void sy_loop(const T* __restric
             }
         }
         if (SIGN) {
-            const int64_t row0 = kend - rows;
 #pragma unroll
             for (int p = 0; p < S::NP; ++p) {
-                const int64_t row = row0 + min(tid / S::TPR + S::RPP * p, klive - 1);
-                sg[p] = sign[row % ncol];
+                sg[p] = reinterpret_cast<const uint32_t*>(sign)[2 * scol[p] + 1];  // (rows past the last are zeroed whatever their sign)
+                scol[p] += sstep;
+                if (scol[p] >= (int)ncol) scol[p] -= (int)ncol;
             }
         }
         base += KC * ldx;
@@ -541,7 +550,7 @@ __device__ __attribute__((always_inline)) inline void sy_loop(const T* __restric
 #pragma unroll
             for (int p = 0; p < S::NP; ++p)
 #pragma unroll
-                for (int e = 0; e < S::V; ++e) pb.v[p][e] = sg[p] < 0 ? -pb.v[p][e] : pb.v[p][e];
+                for (int e = 0; e < S::V; ++e) pb.v[p][e] = sg[p] > 0x80000000u ? -pb.v[p][e] : pb.v[p][e];
         }
         pb.store(sB[buf], klive, tid);
     };
@@ -693,8 +702,14 @@ __device__ __attribute__((always_inline)) inline void k_syrk_body(int64_t lid, c
     }
 }
 
+// Waves per SIMD the registers are held to.  FP32 pairs on the lower tiles and signed
+// rows carry a second panel, row offsets or signs more than the plain form: at 4 they
+// spilled 36 and 87 registers (nao=128, naux=512, 24 columns: K 98 and 85 us; 76 and 54 at 3).
+template <typename T, int MODE, bool SIGN>
+constexpr int sy_waves() { return sizeof(T) == 8 ? 2 : MODE == SY_PAIR_LOWER || SIGN ? 3 : 4; }
+
 template <typename T, int MODE, bool SIGN = false>
-__global__ __launch_bounds__(kThreads, (sizeof(T) == 4 ? 4 : 2)) void k_syrk(const T* __restrict__ X, int64_t ldx, int64_t nrows,
+__global__ __launch_bounds__(kThreads, (sy_waves<T, MODE, SIGN>())) void k_syrk(const T* __restrict__ X, int64_t ldx, int64_t nrows,
                                                     int64_t nao, int64_t ncol,
                                                     const double* __restrict__ sign, int64_t kchunk,
                                                     int64_t ntl, int64_t nblk, T* __restrict__ part,
