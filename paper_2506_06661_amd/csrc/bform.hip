@@ -205,7 +205,9 @@ __global__ __launch_bounds__(kT) void chol_panel(double* __restrict__ P, int64_t
 }
 
 // Trailing update C_ij -= P_i P_j^T of the lower block triangle (64 x 64 tiles,
-// P: n rows of 64)
+// P: n rows of 64).  The 64 terms are summed by themselves and then subtracted once:
+// each has a fraction of C's size, and rounding the running result at every one of them
+// made L's error four times as large (naux=1024: 3.6e-16 -> 1.4e-15).
 __global__ __launch_bounds__(kT) void chol_update(const double* __restrict__ P, double* __restrict__ C, int64_t lda,
                                                   int64_t n) {
     __shared__ __attribute__((aligned(16))) double sA[NB][TP], sB[NB][TP];
@@ -219,7 +221,7 @@ __global__ __launch_bounds__(kT) void chol_update(const double* __restrict__ P, 
     Block64<kT> ba, bb;
     ba.load(P + m0 * lda, lda, nr, tid);
     bb.load(P + n0 * lda, lda, nc, tid);
-    v4d acc[2][2];
+    v4d acc[2][2], old[2][2];
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -227,7 +229,8 @@ __global__ __launch_bounds__(kT) void chol_update(const double* __restrict__ P, 
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = wm * 32 + x * 16 + Mma<double>::row(lane, r), col = wn * 32 + y * 16 + (lane & 15);
-                acc[x][y][r] = row < nr && col < nc ? C[(m0 + row) * lda + n0 + col] : 0.0;
+                old[x][y][r] = row < nr && col < nc ? C[(m0 + row) * lda + n0 + col] : 0.0;
+                acc[x][y][r] = 0.0;
             }
     ba.store(sA, nr, true, tid);
     bb.store(sB, nc, false, tid);
@@ -248,7 +251,7 @@ __global__ __launch_bounds__(kT) void chol_update(const double* __restrict__ P, 
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = wm * 32 + x * 16 + Mma<double>::row(lane, r), col = wn * 32 + y * 16 + (lane & 15);
-                if (row < nr && col < nc) C[(m0 + row) * lda + n0 + col] = acc[x][y][r];
+                if (row < nr && col < nc) C[(m0 + row) * lda + n0 + col] = old[x][y][r] + acc[x][y][r];
             }
 }
 
@@ -261,14 +264,17 @@ __global__ void zero_upper(double* __restrict__ M, int64_t n, int64_t i0) {
 // Q <- L^-1 Q, one launch: a workgroup owns 64 columns and takes the rows in
 // panels of 256, so nothing crosses workgroups.  A wavefront holds 16 columns of
 // all the panel's rows in registers, as accumulators: first
-// Q_panel -= L[panel, above] Q[above], in 16-deep chunks (L staged in LDS one
+// -L[panel, above] Q[above], in 16-deep chunks (L staged in LDS one
 // chunk ahead for the four wavefronts, each one's columns of Q straight from
 // global memory into operand registers), then the triangle inside the panel, 64
 // rows at a time: the FP64 result layout (row 4 r + lane / 16 of a 16 x 16 block)
 // is the operand layout of the 4-deep step r, so Q_k <- Linv_k Q_k feeds
-// Q_i -= L_ik Q_k without leaving the registers.  Q is written once and
-// the matrix cores bound it.  naux=1536, 73920 columns: 4.1 ms, 42 TFLOP/s
-// (1155 workgroups in 512 slots: the third round is a quarter full); with an update
+// Q_i -= L_ik Q_k without leaving the registers.  Sums start at zero and are added to
+// Q per 256 rows above and per 64 inside the panel: a running result that starts as Q
+// rounds all of it at every term (error of B at naux=1536 1.2e-15, 5.1e-15 together with
+// the same in chol_update).  The matrix cores bound it.
+// naux=1536, 73920 columns: 4.28 ms, 41 TFLOP/s (1155 workgroups in 512 slots: the third
+// round is a quarter full; 4.07 with running results); with an update
 // of all rows below after each panel (Q rewritten 5 times) 5.0 ms, with one
 // product, one copy and one update per 64 rows 7.6 ms.
 constexpr int SK = 16, SP = NB2 + 16;  // chunk depth; LDS pitch (16 modulo 32)
@@ -293,16 +299,45 @@ __global__ __launch_bounds__(kT, 2) void solve(const double* __restrict__ L, int
         const double* Lp = L + K0 * ld;
         double* Qp = Qc + K0 * ldQ;
         double q[4][16];  // block k, element e: row K0 + 64 k + 4 e + lane / 16
-        if (nrow == NB2) {
-            const double* p = Qp;
+        // q <- Q_panel + q; with `keep` not in the registers but in Q_panel, q <- 0
+        auto fold = [&](bool keep) {
+            double* p = Qp;
+            int row = (t & 63) >> 4;
+            if (nrow == NB2) {
 #pragma unroll
-            for (int e = 0; e < 64; ++e, p += step) q[e >> 4][e & 15] = *p;
-        } else {
-            const double* p = Qp;
-            asm volatile("" ::: "memory");  // stays a branch
+                for (int g = 0; g < 8; ++g) {
+                    asm volatile("" : "+v"(p));  // one group's addresses at a time
+                    double v[8];
 #pragma unroll
-            for (int e = 0; e < 64; ++e, p += step) q[e >> 4][e & 15] = 4 * e + (lane >> 4) < nrow ? *p : 0.0;
-        }
+                    for (int e = 0; e < 8; ++e) v[e] = p[e * step];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        double& x = q[g >> 1][8 * (g & 1) + e];
+                        x += v[e];
+                        if (keep) {
+                            if (live) p[e * step] = x;
+                            x = 0.0;
+                        }
+                    }
+                    p += 8 * step;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 64; ++e) {
+                    asm volatile("" : "+v"(p), "+v"(row) : : "memory");
+                    double& x = q[e >> 4][e & 15];
+                    if (row < nrow) {
+                        x += *p;
+                        if (keep && live) *p = x;
+                    }
+                    if (keep) x = 0.0;
+                    p += step;
+                    row += 4;
+                }
+            }
+        };
+#pragma unroll
+        for (int e = 0; e < 64; ++e) q[e >> 4][e & 15] = 0.0;
         // ---- rows above the panel
         if (K0 > 0) {
             const int ar = t >> 3, akp = 2 * (t & 7);  // staged pairs: row ar + 32 j at k = akp
@@ -330,7 +365,7 @@ __global__ __launch_bounds__(kT, 2) void solve(const double* __restrict__ L, int
                 }
             };
             auto load_b = [&](int64_t kc) {
-const double* Qk = Qc + kc * ldQ;
+                const double* Qk = Qc + kc * ldQ;
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) rb[kk] = Qk[kk * step];
             };
@@ -368,8 +403,10 @@ const double* Qk = Qc + kc * ldQ;
                 }
                 buf ^= 1;
                 __syncthreads();
+                if ((kc + SK) % NB2 == 0 && kc + SK < K0) fold(true);
             }
         }
+        fold(false);
         // ---- the panel's own triangle
         const double *Lt = Lp + K0, *Li = Linv + K0 * NB;
         Block64<kT> st;
@@ -409,15 +446,18 @@ const double* Qk = Qc + kc * ldQ;
 #pragma unroll
                         for (int r = 0; r < 4; ++r) q[k][4 * b + r] = acc[b][r];
                 } else {
+                    v4d acc[4];
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) acc[b] = Mma<double>::zero();
 #pragma unroll
                     for (int kk = 0; kk < 16; ++kk)
 #pragma unroll
-                        for (int b = 0; b < 4; ++b) {
-                            v4d u = {q[i][4 * b], q[i][4 * b + 1], q[i][4 * b + 2], q[i][4 * b + 3]};
-                            u = Mma<double>::step(oper(S[buf], b, kk, lane), q[k][kk], u);
+                        for (int b = 0; b < 4; ++b)
+                            acc[b] = Mma<double>::step(oper(S[buf], b, kk, lane), q[k][kk], acc[b]);
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) q[i][4 * b + r] = u[r];
-                        }
+                    for (int b = 0; b < 4; ++b)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) q[i][4 * b + r] += acc[b][r];
                 }
                 if (more) st.store(S[buf ^ 1], rows, neg, t);
                 buf ^= 1;
