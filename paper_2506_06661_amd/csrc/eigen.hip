@@ -66,9 +66,14 @@ __host__ __device__ inline int place_of(int i, int j, int h, int nblk) {
 }
 
 // 1 / sqrt(x) and 1 / x to the last places for normal x well inside the range: the
-// hardware's start (relative error below 2^-23) and one third-order step.
+// hardware's start (relative error below 2^-23) and one third-order step.  The residual
+// 1 - x y^2 takes the rounding of x y along: without it the cosines were off to one
+// side, and the norms of the vectors, which gather that over a thousand rotations,
+// drifted: mean of |v|^2 - 1 at n=198 4.7e-14, with correctly rounded roots and
+// divisions 3.2e-14, so -6e-16.
 __device__ inline double rsqrt_near(double x) {
-    const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
+    const double y = __builtin_amdgcn_rsq(x), p = x * y;
+    const double e = fma(-fma(x, y, -p), y, fma(-p, y, 1.0));
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 __device__ inline double rcp_near(double x) {
