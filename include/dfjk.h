@@ -404,9 +404,9 @@ void dfjk_batch_destroy(dfjk_batch b);
  * The dense steps of molecules with nao <= 198 are launches over all of them
  * on the batch stream; larger ones run on up to 8 worker streams forked from and
  * joined back to it (not graph-capturable).  Each molecule keeps its own DIIS
- * history and eigensolver workspace (about (8 + 2 * 8) nao^2 doubles, and 40
- * nao^2 more for the eigensolver's rotations where nao <= 198), allocated on
- * first use.  nao <= 4096 per molecule.
+ * history and eigensolver workspace (about (8 + 2 * 8) nao^2 doubles), and the
+ * molecules of nao <= 198 share 64 logs of the eigensolver's rotations (40 nao^2
+ * doubles each), all allocated on first use.  nao <= 4096 per molecule.
  */
 int dfjk_batch_scf_guess(dfjk_batch b, const double* const* H_list);
 int dfjk_batch_scf_step(dfjk_batch b, const double* const* H_list, dfjk_scf_info* info);

@@ -65,6 +65,7 @@ struct dfjk_batch_ctx {
     bool scf_ok = false;
     std::vector<int> scf_small, scf_large;
     dfjk::DevBuf d_scf, scf_rec;  // descriptors of scf_small; records by molecule
+    dfjk::DevBuf scf_log;         // logs of rotations of one launch's molecules
     std::vector<hipStream_t> workers;
     std::vector<hipEvent_t> worker_done;
     hipEvent_t built = nullptr;
@@ -248,6 +249,7 @@ void scf_drop(dfjk_batch b) {
     b->scf_large.clear();
     b->d_scf.release();
     b->scf_rec.release();
+    b->scf_log.release();
 }
 
 // Per-molecule SCF handles, and worker streams where one needs them
@@ -288,11 +290,21 @@ int scf_make(dfjk_batch b) {
     if ((rc = b->scf_rec.ensure(sizeof(ScfRecord) * (size_t)b->nmol))) return rc;
     if (b->scf_small.empty()) return DFJK_OK;
     std::vector<ScfMol> desc(b->scf_small.size());
+    // A log is read by the launch after the one that writes it, and on_small's launches
+    // follow one another: the j-th molecule of each shares one log (12.5 MB at
+    // nao=198; a thousand molecules 0.8 GB, not 12.5).
+    const size_t nlog = std::min<size_t>(desc.size(), kMolChunk);
+    std::vector<size_t> log_at(nlog + 1, 0), log_len(nlog, 0);
+    for (size_t j = 0; j < desc.size(); ++j)
+        log_len[j % kMolChunk] = std::max(log_len[j % kMolChunk], EigWork::log_elems(b->mols[b->scf_small[j]].nao));
+    for (size_t j = 0; j < nlog; ++j) log_at[j + 1] = log_at[j] + (log_len[j] + 31) / 32 * 32;
+    if ((rc = b->scf_log.ensure(sizeof(double) * log_at[nlog]))) return rc;
     for (size_t j = 0; j < desc.size(); ++j) {
         const int i = b->scf_small[j];
         const MolDesc& d = b->mols[i];
         if ((rc = scf_describe(b->scf[i], const_cast<double*>(d.D), const_cast<double*>(d.C), d.nocc, d.J, d.K,
-                               static_cast<ScfRecord*>(b->scf_rec.ptr) + i, &desc[j])))
+                               static_cast<ScfRecord*>(b->scf_rec.ptr) + i,
+                               static_cast<double*>(b->scf_log.ptr) + log_at[j % kMolChunk], &desc[j])))
             return rc;
     }
     if ((rc = b->d_scf.ensure(sizeof(ScfMol) * desc.size()))) return rc;

@@ -99,9 +99,10 @@ size_t eig_lds_bytes(int n);
 
 // The SCF step after J and K, and the aufbau of a given F, of up to kMolChunk
 // molecules (scf.hip): mols on the device, h their handles, all at the same
-// iteration.  scf_describe fills one entry; its record goes to rec.
+// iteration.  scf_describe fills one entry; its record goes to rec, its eigensolver's
+// log of rotations (EigWork::log_elems values) to log.
 int scf_describe(dfjk_ctx* h, double* D, double* C, int64_t nocc, const double* J, const double* K, void* rec,
-                 ScfMol* out);
+                 double* log, ScfMol* out);
 int scf_tail_many(hipStream_t st, const ScfMol* mols, dfjk_ctx* const* h, const double* const* H, int nmol);
 int aufbau_many(hipStream_t st, const ScfMol* mols, dfjk_ctx* const* h, const double* const* F, int nmol);
 

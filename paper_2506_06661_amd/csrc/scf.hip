@@ -332,7 +332,8 @@ struct ScfWs {
     ScfRecord* rec;
 };
 
-static int scf_ws(dfjk_ctx* h, bool scf, ScfWs& ws) {
+// log: with the eigensolver's log of rotations, the last part (a batch lends its own)
+static int scf_ws(dfjk_ctx* h, bool scf, ScfWs& ws, bool log = true) {
     const int64_t n = h->nao, n2 = n * n;
     const int space = h->opts.diis_space;
     size_t need = 0;
@@ -342,7 +343,7 @@ static int scf_ws(dfjk_ctx* h, bool scf, ScfWs& ws) {
         return off;
     };
     const size_t oA = take(n2), oV = take(n2), ow = take(n), owork = take(n + 2), oCf = take(n2),
-                 osign = take(n), oiw = take((EigWork::iwork_elems(n) + 1) / 2), olog = take(EigWork::log_elems(n));
+                 osign = take(n), oiw = take((EigWork::iwork_elems(n) + 1) / 2);
     size_t oJ = 0, oK = 0, oF = 0, oG = 0, oFx = 0, oFh = 0, oEh = 0, ogr = 0, oco = 0, opart = 0, oep = 0,
            orec = 0, ofirst = 0;
     if (scf) {
@@ -351,11 +352,12 @@ static int scf_ws(dfjk_ctx* h, bool scf, ScfWs& ws) {
         ogr = take((size_t)space * space), oco = take(16), opart = take(kMaxSums * kSlices), oep = take(1),
         orec = take(sizeof(ScfRecord) / sizeof(double) + 1), ofirst = take(1);
     }
+    const size_t olog = take(log ? EigWork::log_elems(n) : 0);
     if (need * sizeof(double) > h->eig.bytes) h->scf_v_warm = false;  // fresh buffer
     int rc = h->eig.ensure(need * sizeof(double));
     if (rc) return rc;
     double* base = static_cast<double*>(h->eig.ptr);
-    ws.eig = EigWork{base + oA, base + owork, base + olog, reinterpret_cast<int*>(base + oiw), base + ow};
+    ws.eig = EigWork{base + oA, base + owork, log ? base + olog : nullptr, reinterpret_cast<int*>(base + oiw), base + ow};
     ws.V = base + oV;
     ws.Cf = base + oCf;
     ws.sign = base + osign;
@@ -541,11 +543,12 @@ int scf_tail(dfjk_ctx* h, const double* H, double* D, double* C, int64_t nocc, c
 // ---- all molecules of a batch at once (n <= kEigLdsN)
 
 int scf_describe(dfjk_ctx* h, double* D, double* C, int64_t nocc, const double* J, const double* K, void* rec,
-                 ScfMol* out) {
+                 double* log, ScfMol* out) {
     ScfWs ws;
-    if (int rc = scf_ws(h, true, ws)) return rc;
+    if (int rc = scf_ws(h, true, ws, false)) return rc;
     h->scf_ready = true;
     *out = describe(h, ws, D, C, nocc, J, K);
+    out->eig.log = log;
     out->rec = static_cast<ScfRecord*>(rec);
     return DFJK_OK;
 }
