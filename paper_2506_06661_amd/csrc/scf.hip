@@ -401,7 +401,11 @@ int k_build_from_D(dfjk_ctx* h, const double* D, double* K) {
         // eigen-factor path, which fits it
         symmetrize_kernel<<<dim3((unsigned)cdiv(n * n, 256)), 256, 0, st>>>(D, n, ws.eig.A);
         DFJK_LAUNCH_CHECK("symmetrize_kernel");
-        return k_build_density(h, ws.eig.A, K);
+        rc = k_build_density(h, ws.eig.A, K);
+        // its rows of B_P D and of B_P may not fit where the factors' rows, half as many,
+        // do; from kDensityF32 on an eigensolution would take far longer than the build
+        if (rc != DFJK_E_OOM || n >= kDensityF32) return rc;
+        clear_error();
     }
     // D = sum_c w_c v_c v_c^T = sum_c sign_c (sqrt|w_c| v_c)(sqrt|w_c| v_c)^T
     if ((rc = eigh_cols(st, D, ws.V, (int)n, true, ws.eig, (int)n, 1, ws.Cf, ws.sign))) return rc;
