@@ -921,14 +921,14 @@ int run_gemm1(dfjk_ctx* h, const void* C, int64_t ncol, void* X, int64_t ldx, bo
 // finish took 16.9 / 15.3 / 14.7 / 14.4 / 14.5 ms with about 1024 / 2048 / 4096 /
 // 8192 / 16384 workgroups, two factors at nao=500 2.36 / 2.08 / 2.10 / 2.21 / 2.28.
 // Short contractions keep 384 rows a split (naux=103 at nao=1024) unless that
-// leaves CUs idle: then down to
-// kMinRows64 rows: nao=64, naux=256, nocc=16 GEMM2 + finish 0.054 -> 0.018 ms,
-// nao=128, naux=512, nocc=24 0.057 -> 0.030.
+// leaves CUs idle: then down to kMinRows64 rows.  A repeated K, us, with 384 and with
+// fewer rows: nao=112, 7680 rows 92, 38; nao=128, 6144 rows 67, 35; nao=200, 1920
+// rows 78, 36.
+// Partials above kSmallPart make a new handle's first J and K 0.50 ms, not 0.24 (the
+// allocation), so they stay within it where that costs no more than every second
+// split: nao=64, naux=256, nocc=16 takes 64, not 86, 39 us repeated either way.
 // FP32: about 16384 workgroups, no split shorter than 384 rows and no running
 // sum longer than kMaxSum32 terms (the split partials are added in FP64).
-// Partials that fit kSmallPart with 384 rows a split stay within it: a
-// buffer above 2 MiB takes 0.25 ms to allocate on a handle's first call, one below 1 to
-// 40 us.
 constexpr int64_t kMinRows64 = 48, kSmallPart = 2 << 20;
 int64_t syrk_max_splits(int64_t nrows, int64_t ntl, int64_t slot, bool f32) {  // never falls as nrows grows
     int64_t nsplit;
@@ -936,10 +936,10 @@ int64_t syrk_max_splits(int64_t nrows, int64_t ntl, int64_t slot, bool f32) {  /
         nsplit = std::min(std::max(cdiv(16384, ntl), cdiv(nrows, kMaxSum32)), cdiv(nrows, 384));
     } else {
         nsplit = std::max(cdiv(4096, ntl), std::min(cdiv(8192, ntl), nrows / 2048));
-        const int64_t base = cdiv(nrows, 384), fit = kSmallPart / (8 * slot * slot * ntl);
+        const int64_t fit = kSmallPart / (8 * slot * slot * ntl);
         int64_t more = std::min(cdiv(512, ntl), cdiv(nrows, kMinRows64));
-        if (base <= fit) more = std::min(more, fit);
-        nsplit = std::min(nsplit, std::max(base, more));
+        if (more <= 2 * fit) more = std::min(more, fit);
+        nsplit = std::min(nsplit, std::max(cdiv(nrows, 384), more));
     }
     return std::max<int64_t>(nsplit, 1);
 }
