@@ -209,8 +209,9 @@ int dfjk_build_J_diag(dfjk_handle h, const double* D_dev, double* J_dev, double*
  *                     Sec. IV.A.1: a guess density need not be idempotent),
  *                     from the rows of B_P D and of B_P (workspace: X for
  *                     2 * naux * nao rows); through the signed eigen-factors
- *                     of D with a reserved workspace (max_ncol > 0) and, for
- *                     reduced-precision B, for nao < 256.
+ *                     of D (half the rows) with a reserved workspace
+ *                     (max_ncol > 0) and, for nao < 256, with
+ *                     reduced-precision B or where those rows do not fit.
  * Deterministic.
  */
 int dfjk_build_K(dfjk_handle h, const double* Cocc_dev, int64_t nocc, const double* D_dev,

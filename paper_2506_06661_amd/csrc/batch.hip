@@ -4,8 +4,8 @@
 // reduction, J pass 2, J unpack, C to FP32, GEMM1, SYRK, K reduction) runs as
 // ONE launch over all molecules: the grid is the concatenation of every
 // molecule's blocks, molecules in longest-processing-time-first order (cost
-// naux * nao^2 * nocc), and each block finds its molecule by binary search in
-// a prefix table.  GEMM1 runs once per tile bucket (molecules grouped by
+// naux * nao^2 * nocc), and each block finds its molecule in a prefix table
+// (find_mol).  GEMM1 runs once per tile bucket (molecules grouped by
 // ceil(nocc/16)), with the tile of each bucket chosen by the autotuner.  The
 // whole sequence can be captured once into a HIP graph and replayed: no
 // allocation, host synchronisation or memset is enqueued by a build.

@@ -43,7 +43,7 @@ struct EigWork {
     double* A;    // n x n (larger n only)
     double* work; // n + 2 (larger n only)
     double* log;  // log_elems(n): rotations to apply to the eigenvectors
-    int* iwork;   // iwork_elems(n): sweeps, index of each rank, rank of each index, ...
+    int* iwork;   // iwork_elems(n): sweeps, index of each rank (larger n only), rank of each index, ...
     double* w;    // n eigenvalues in ascending order
     __host__ __device__ static int rank_at(int n) { return n + 2; }
     __host__ __device__ static int rounds_at(int n) { return 2 * n + 2; }

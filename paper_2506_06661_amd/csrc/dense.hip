@@ -16,19 +16,19 @@ __host__ __device__ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 
 // 64x64 tile per workgroup, 2x2 waves of 32x32 (2x2 f64 16x16x4 steps).
 constexpr int GT = 64, GK = 16;
 
-template <typename T, bool TA, bool TB>
-__global__ __launch_bounds__(256) void gemm_kernel(int64_t M, int64_t N, int64_t K, T alpha,
-                                                    const T* __restrict__ A, int64_t lda,
-                                                    const T* __restrict__ B, int64_t ldb, T beta,
-                                                    T* __restrict__ C, int64_t ldc) {
-    __shared__ T sA[GK][GT + 1];  // sA[k][m] = op(A)[m][k]
-    __shared__ T sB[GK][GT + 1];  // sB[k][n] = op(B)[k][n]
+template <bool TA, bool TB>
+__global__ __launch_bounds__(256) void gemm_kernel(int64_t M, int64_t N, int64_t K, double alpha,
+                                                    const double* __restrict__ A, int64_t lda,
+                                                    const double* __restrict__ B, int64_t ldb, double beta,
+                                                    double* __restrict__ C, int64_t ldc) {
+    __shared__ double sA[GK][GT + 1];  // sA[k][m] = op(A)[m][k]
+    __shared__ double sB[GK][GT + 1];  // sB[k][n] = op(B)[k][n]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int64_t m0 = (int64_t)blockIdx.y * GT, n0 = (int64_t)blockIdx.x * GT;
-    typename Mma<T>::acc_t acc[2][2];
+    v4d acc[2][2];
     for (int a = 0; a < 2; ++a)
-        for (int b = 0; b < 2; ++b) acc[a][b] = Mma<T>::zero();
+        for (int b = 0; b < 2; ++b) acc[a][b] = Mma<double>::zero();
     for (int64_t k0 = 0; k0 < K; k0 += GK) {
         for (int e = tid; e < GK * GT; e += 256) {
             // element (k, m) of op(A) and (k, n) of op(B); the mapping reads
@@ -36,13 +36,13 @@ __global__ __launch_bounds__(256) void gemm_kernel(int64_t M, int64_t N, int64_t
             int k, m;
             if (TA) { k = e / GT; m = e % GT; } else { m = e / GK; k = e % GK; }
             const int64_t gm = m0 + m, gk = k0 + k;
-            T v = T(0);
+            double v = 0.0;
             if (gm < M && gk < K) v = TA ? A[gk * lda + gm] : A[gm * lda + gk];
             sA[k][m] = v;
             int kb, n;
             if (TB) { n = e / GK; kb = e % GK; } else { kb = e / GT; n = e % GT; }
             const int64_t gn = n0 + n, gkb = k0 + kb;
-            T w = T(0);
+            double w = 0.0;
             if (gn < N && gkb < K) w = TB ? B[gn * ldb + gkb] : B[gkb * ldb + gn];
             sB[kb][n] = w;
         }
@@ -50,23 +50,23 @@ __global__ __launch_bounds__(256) void gemm_kernel(int64_t M, int64_t N, int64_t
 #pragma unroll
         for (int kk = 0; kk < GK / 4; ++kk) {
             const int kr = kk * 4 + (lane >> 4);
-            T a[2], b[2];
+            double a[2], b[2];
             for (int q = 0; q < 2; ++q) {
                 a[q] = sA[kr][wm * 32 + q * 16 + (lane & 15)];
                 b[q] = sB[kr][wn * 32 + q * 16 + (lane & 15)];
             }
             for (int ti = 0; ti < 2; ++ti)
-                for (int tj = 0; tj < 2; ++tj) acc[ti][tj] = Mma<T>::step(a[ti], b[tj], acc[ti][tj]);
+                for (int tj = 0; tj < 2; ++tj) acc[ti][tj] = Mma<double>::step(a[ti], b[tj], acc[ti][tj]);
         }
         __syncthreads();
     }
     for (int ti = 0; ti < 2; ++ti)
         for (int tj = 0; tj < 2; ++tj)
             for (int r = 0; r < 4; ++r) {
-                const int64_t gm = m0 + wm * 32 + ti * 16 + Mma<T>::row(lane, r);
+                const int64_t gm = m0 + wm * 32 + ti * 16 + Mma<double>::row(lane, r);
                 const int64_t gn = n0 + wn * 32 + tj * 16 + (lane & 15);
                 if (gm < M && gn < N) {
-                    const T old = beta == T(0) ? T(0) : beta * C[gm * ldc + gn];
+                    const double old = beta == 0.0 ? 0.0 : beta * C[gm * ldc + gn];
                     C[gm * ldc + gn] = alpha * acc[ti][tj][r] + old;
                 }
             }
@@ -695,13 +695,13 @@ int dgemm(hipStream_t st, bool ta, bool tb, int64_t M, int64_t N, int64_t K, dou
     }
     const dim3 grid((unsigned)cdiv(N, GT), (unsigned)cdiv(M, GT));
     if (!ta && !tb)
-        gemm_kernel<double, false, false><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
+        gemm_kernel<false, false><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
     else if (ta && !tb)
-        gemm_kernel<double, true, false><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
+        gemm_kernel<true, false><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
     else if (!ta && tb)
-        gemm_kernel<double, false, true><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
+        gemm_kernel<false, true><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
     else
-        gemm_kernel<double, true, true><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
+        gemm_kernel<true, true><<<grid, 256, 0, st>>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
     DFJK_LAUNCH_CHECK("gemm_kernel");
     return DFJK_OK;
 }

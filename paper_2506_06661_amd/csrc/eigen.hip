@@ -382,7 +382,6 @@ __device__ __forceinline__ void jacobi_solve(const double* __restrict__ X, int n
             rank = tid;
             di = __builtin_nan("");
         }
-        iwork[1 + rank] = tid;
         iwork[EigWork::rank_at(n) + tid] = rank;
         w[rank] = di * pow2(ex);
     }

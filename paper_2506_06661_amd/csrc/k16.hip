@@ -1395,8 +1395,8 @@ int k16_t(dfjk_ctx* h, const double* C, int64_t ncol, double scale, double* K) {
 
 // ---------------------------------------------------------------- batched
 // The 16-bit exchange over many molecules: every phase is one launch over
-// all molecules' blocks; a block finds its molecule by binary search in the
-// phase's prefix table (molecules longest first).
+// all molecules' blocks; a block finds its molecule in the phase's prefix table
+// (find_mol; molecules longest first).
 template <typename H>
 __global__ __launch_bounds__(kT) void kb16_kernel(int kind, const MolDesc* __restrict__ mols, PhaseList pl) {
     const int64_t b = kind == BP_SYRK16 ? xcd_runs(blockIdx.x, pl.nblk) : (int64_t)blockIdx.x;

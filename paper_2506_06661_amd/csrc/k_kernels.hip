@@ -33,11 +33,6 @@ constexpr int64_t kMaxSum32 = 16384;  // longest FP32 running sum in the SYRK
 
 __host__ __device__ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-__device__ inline int64_t pidx(int64_t a, int64_t b) {
-    const int64_t hi = a > b ? a : b, lo = a > b ? b : a;
-    return hi * (hi + 1) / 2 + lo;
-}
-
 // Storage element of B -> compute type (exact for every pair used here).
 template <typename T, typename TS>
 __device__ inline T to_compute(TS x) {
@@ -899,8 +894,8 @@ int pick_g1_tile(int64_t ncol, bool f32) {
     return best;
 }
 
-// X = (B_P C)^T for every P, with the handle's forced tile or the default
-// split (profiled as the GEMM1 phase).
+// X = (B_P C)^T for every P in one launch, with the handle's forced tile or
+// pick_g1_tile's (profiled as the GEMM1 phase).
 int run_gemm1(dfjk_ctx* h, const void* C, int64_t ncol, void* X, int64_t ldx, bool f32) {
     const int64_t ldc = c_stride(ncol, f32);
     if (h->g1_tile >= 0 && h->g1_tile < kNumG1Tiles) {

@@ -45,8 +45,8 @@ def core_guess(handle: _d.Handle, H: torch.Tensor, nocc: int):
 
 def run_scf(handle: _d.Handle, H: torch.Tensor, nocc: int, D0: torch.Tensor | None = None,
             C0: torch.Tensor | None = None, max_iter: int = 100):
-    """DIIS SCF from D0 (K through C0 when given, else through D0's
-    eigen-factors on the first iteration).  Returns (records, D, C) with one
+    """DIIS SCF from D0 (K through C0 when given, else from D0
+    itself on the first iteration).  Returns (records, D, C) with one
     (e_tot, err_norm, converged) record per J/K build."""
     nao = H.shape[0]
     _d.dfjk_scf_reset(handle.h)
