@@ -5,7 +5,7 @@
 //   Cholesky, for each diagonal block k: factor L_kk and invert it; panel L_ik = M_ik L_kk^-T in place and trailing
 //     update M_ij -= L_ik L_jk^T of the lower block triangle, 64 x 64 tiles on
 //     the FP64 matrix cores.
-//   Substitution, for each panel of 256 rows: the product with all rows above,
+//   Substitution, for each panel of 128 rows: the product with all rows above,
 //     then Q_k <- L_kk^-1 Q_k and Q_i -= L_ik Q_k inside the panel.
 // The 64 x 64 diagonal blocks are applied through their explicit inverses
 // (forward substitution on the identity), which keeps every large step on
@@ -18,7 +18,7 @@ namespace dfjk {
 namespace {
 
 constexpr int NB = 64;    // block size (diagonal blocks, Cholesky panels)
-constexpr int NB2 = 256;  // row panel of the substitution (4 diagonal blocks)
+constexpr int NB2 = 128;  // row panel of the substitution (2 diagonal blocks)
 constexpr int kT = 256;
 constexpr int TP = NB + 16;  // LDS pitch of a 64 x 64 block: 16 modulo 32 doubles
 
@@ -262,9 +262,9 @@ __global__ void zero_upper(double* __restrict__ M, int64_t n, int64_t i0) {
 }
 
 // Q <- L^-1 Q, one launch: a workgroup owns 64 columns and takes the rows in
-// panels of 256, so nothing crosses workgroups.  A wavefront holds 16 columns of
+// panels of 128, so nothing crosses workgroups.  A wavefront holds 16 columns of
 // all the panel's rows in registers, as accumulators: first
-// -L[panel, above] Q[above], in 16-deep chunks (L staged in LDS one
+// -L[panel, above] Q[above], in 32-deep chunks (L staged in LDS one
 // chunk ahead for the four wavefronts, each one's columns of Q straight from
 // global memory into operand registers), then the triangle inside the panel, 64
 // rows at a time: the FP64 result layout (row 4 r + lane / 16 of a 16 x 16 block)
@@ -272,12 +272,11 @@ __global__ void zero_upper(double* __restrict__ M, int64_t n, int64_t i0) {
 // Q_i -= L_ik Q_k without leaving the registers.  Sums start at zero and are added to
 // Q per 256 rows above and per 64 inside the panel: a running result that starts as Q
 // rounds all of it at every term (error of B at naux=1536 1.2e-15, 5.1e-15 together with
-// the same in chol_update).  The matrix cores bound it.
-// naux=1536, 73920 columns: 4.28 ms, 41 TFLOP/s (1155 workgroups in 512 slots: the third
-// round is a quarter full; 4.07 with running results); with an update
-// of all rows below after each panel (Q rewritten 5 times) 5.0 ms, with one
-// product, one copy and one update per 64 rows 7.6 ms.
-constexpr int SK = 16, SP = NB2 + 16;  // chunk depth; LDS pitch (16 modulo 32)
+// the same in chol_update).  Q and the sums of the panel are in registers side by side;
+// panels of 256 rows have no room for that and went through memory at every
+// addition (MEASURE).  The matrix cores bound it.
+constexpr int SK = 32, SP = NB2 + 16;  // chunk depth; LDS pitch (16 modulo 32)
+constexpr int SFOLD = 256;             // rows above per sum
 __global__ __launch_bounds__(kT, 2) void solve(const double* __restrict__ L, int64_t naux,
                                                const double* __restrict__ Linv, double* __restrict__ Q, int64_t ldQ,
                                                int64_t ncol) {
@@ -289,6 +288,7 @@ __global__ __launch_bounds__(kT, 2) void solve(const double* __restrict__ L, int
     const int64_t col = (int64_t)blockIdx.x * 64 + wave * 16 + (lane & 15);
     const bool live = col < ncol;
     double* Qc = Q + (live ? col : ncol - 1) + (lane >> 4) * ldQ;  // this lane's row of a 4-deep step
+    constexpr int KB = NB2 / NB;                                   // blocks per panel
     for (int64_t K0 = 0; K0 < naux; K0 += NB2) {
         const int nrow = naux - K0 < NB2 ? (int)(naux - K0) : NB2, nb = (nrow + NB - 1) / NB;
         // leading dimensions and thread as if new in each panel: their multiples
@@ -298,121 +298,101 @@ __global__ __launch_bounds__(kT, 2) void solve(const double* __restrict__ L, int
         asm volatile("" : "+s"(ld), "+s"(step), "+v"(t));
         const double* Lp = L + K0 * ld;
         double* Qp = Qc + K0 * ldQ;
-        double q[4][16];  // block k, element e: row K0 + 64 k + 4 e + lane / 16
-        // q <- Q_panel + q; with `keep` not in the registers but in Q_panel, q <- 0
-        auto fold = [&](bool keep) {
-            double* p = Qp;
-            int row = (t & 63) >> 4;
-            if (nrow == NB2) {
+        double q[KB][16];  // block k, element e: row K0 + 64 k + 4 e + lane / 16
+        if (nrow == NB2) {
+            const double* p = Qp;
 #pragma unroll
-                for (int g = 0; g < 8; ++g) {
-                    asm volatile("" : "+v"(p));  // one group's addresses at a time
-                    double v[8];
+            for (int e = 0; e < 16 * KB; ++e, p += step) q[e >> 4][e & 15] = *p;
+        } else {
+            const double* p = Qp;
+            asm volatile("" ::: "memory");  // stays a branch
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] = p[e * step];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        double& x = q[g >> 1][8 * (g & 1) + e];
-                        x += v[e];
-                        if (keep) {
-                            if (live) p[e * step] = x;
-                            x = 0.0;
-                        }
-                    }
-                    p += 8 * step;
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 64; ++e) {
-                    asm volatile("" : "+v"(p), "+v"(row) : : "memory");
-                    double& x = q[e >> 4][e & 15];
-                    if (row < nrow) {
-                        x += *p;
-                        if (keep && live) *p = x;
-                    }
-                    if (keep) x = 0.0;
-                    p += step;
-                    row += 4;
-                }
-            }
-        };
-#pragma unroll
-        for (int e = 0; e < 64; ++e) q[e >> 4][e & 15] = 0.0;
+            for (int e = 0; e < 16 * KB; ++e, p += step) q[e >> 4][e & 15] = 4 * e + (lane >> 4) < nrow ? *p : 0.0;
+        }
         // ---- rows above the panel
         if (K0 > 0) {
-            const int ar = t >> 3, akp = 2 * (t & 7);  // staged pairs: row ar + 32 j at k = akp
+            const int ar = t >> 4, akp = 2 * (t & 15);  // staged pairs: row ar + 16 j at k = akp
             const int64_t aoff = ar * ld + akp;
-            const int sw = swz(akp);
-            double ra[8][2], rb[4];
+            double ra[NB2 / 16][2], rb[SK / 4];
             auto load_a = [&](int64_t kc) {
                 if (nrow == NB2) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) __builtin_memcpy(ra[j], Lp + kc + 32 * j * ld + aoff, 16);
+                    for (int j = 0; j < NB2 / 16; ++j) __builtin_memcpy(ra[j], Lp + kc + 16 * j * ld + aoff, 16);
                 } else {
                     asm volatile("" ::: "memory");
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
+                    for (int j = 0; j < NB2 / 16; ++j) {
                         ra[j][0] = ra[j][1] = 0.0;
-                        if (ar + 32 * j < nrow) __builtin_memcpy(ra[j], Lp + kc + 32 * j * ld + aoff, 16);
+                        if (ar + 16 * j < nrow) __builtin_memcpy(ra[j], Lp + kc + 16 * j * ld + aoff, 16);
                     }
                 }
             };
+            // row k of a chunk keeps row m of L at m ^ (k & ~1): the 16 pairs of a store on
+            // different banks
             auto store_a = [&](int buf) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    sA[buf][akp][(ar + 32 * j) ^ sw] = -ra[j][0];
-                    sA[buf][akp + 1][(ar + 32 * j) ^ sw] = -ra[j][1];
+                for (int j = 0; j < NB2 / 16; ++j) {
+                    sA[buf][akp][(ar + 16 * j) ^ akp] = -ra[j][0];
+                    sA[buf][akp + 1][(ar + 16 * j) ^ akp] = -ra[j][1];
                 }
             };
             auto load_b = [&](int64_t kc) {
                 const double* Qk = Qc + kc * ldQ;
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) rb[kk] = Qk[kk * step];
+                for (int kk = 0; kk < SK / 4; ++kk) rb[kk] = Qk[kk * step];
             };
+            v4d acc[KB][4];
+#pragma unroll
+            for (int h = 0; h < KB; ++h)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) acc[h][m] = Mma<double>::zero();
             load_a(0);
             load_b(0);
             store_a(0);
-            load_a(SK);  // K0 is a multiple of NB2: there are at least 16 chunks
+            load_a(SK);  // K0 is a multiple of NB2: there are at least four chunks
             __syncthreads();
             int buf = 0;
             for (int64_t kc = 0; kc < K0; kc += SK) {
-                double b[4];
+                double b[SK / 4];
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) b[kk] = rb[kk];
+                for (int kk = 0; kk < SK / 4; ++kk) b[kk] = rb[kk];
                 if (kc + SK < K0) load_b(kc + SK);
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                    const int kr = 4 * kk + (lane >> 4), ca = (lane & 15) ^ (4 * kk + 2 * (lane >> 5));
+                for (int kk = 0; kk < SK / 4; ++kk) {
+                    const int kr = 4 * kk + (lane >> 4), ca = (lane & 15) ^ (4 * (kk & 3) + 2 * (lane >> 5));
 #pragma unroll
-                    for (int h = 0; h < 4; ++h) {
+                    for (int h = 0; h < KB; ++h) {
                         double a[4];
 #pragma unroll
-                        for (int m = 0; m < 4; ++m) a[m] = sA[buf][kr][64 * h + 16 * m + ca];
+                        for (int m = 0; m < 4; ++m) a[m] = sA[buf][kr][16 * ((4 * h + m) ^ (kk >> 2)) + ca];
 #pragma unroll
-                        for (int m = 0; m < 4; ++m) {
-                            v4d t = {q[h][4 * m], q[h][4 * m + 1], q[h][4 * m + 2], q[h][4 * m + 3]};
-                            t = Mma<double>::step(a[m], b[kk], t);
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) q[h][4 * m + r] = t[r];
-                        }
+                        for (int m = 0; m < 4; ++m) acc[h][m] = Mma<double>::step(a[m], b[kk], acc[h][m]);
                     }
                 }
                 if (kc + SK < K0) {
                     store_a(buf ^ 1);
                     if (kc + 2 * SK < K0) load_a(kc + 2 * SK);
                 }
+                if ((kc + SK) % SFOLD == 0 || kc + SK == K0) {
+#pragma unroll
+                    for (int h = 0; h < KB; ++h)
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) q[h][4 * m + r] += acc[h][m][r];
+                            acc[h][m] = Mma<double>::zero();
+                        }
+                }
                 buf ^= 1;
                 __syncthreads();
-                if ((kc + SK) % NB2 == 0 && kc + SK < K0) fold(true);
             }
         }
-        fold(false);
         // ---- the panel's own triangle
         const double *Lt = Lp + K0, *Li = Linv + K0 * NB;
         Block64<kT> st;
         int rows = NB, buf = 0;
         bool neg = false;
-        // the blocks in order of use: Linv_0, L_10, L_20, L_30, Linv_1, L_21, ...
+        // the blocks in order of use: Linv_0, L_10, Linv_1
         auto fetch = [&](int k, int i) {  // block i == k: the inverse
             rows = i == k ? NB : min(nrow - 64 * i, NB);
             neg = i != k;
@@ -425,9 +405,9 @@ __global__ __launch_bounds__(kT, 2) void solve(const double* __restrict__ L, int
         st.store(S[0], rows, neg, t);
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < KB; ++k) {
 #pragma unroll
-            for (int i = k; i < 4; ++i) {
+            for (int i = k; i < KB; ++i) {
                 if (k >= nb || i >= nb) continue;
                 const int kn = i + 1 < nb ? k : k + 1, in = i + 1 < nb ? i + 1 : k + 1;
                 const bool more = kn < nb;
@@ -466,7 +446,7 @@ __global__ __launch_bounds__(kT, 2) void solve(const double* __restrict__ L, int
         }
         if (live) {
 #pragma unroll
-            for (int e = 0; e < 64; ++e, Qp += step)
+            for (int e = 0; e < 16 * KB; ++e, Qp += step)
                 if (4 * e + (lane >> 4) < nrow) *Qp = q[e >> 4][e & 15];
         }
     }
