@@ -274,7 +274,11 @@ __global__ void zero_upper(double* __restrict__ M, int64_t n, int64_t i0) {
 // rounds all of it at every term (error of B at naux=1536 1.2e-15, 5.1e-15 together with
 // the same in chol_update).  Q and the sums of the panel are in registers side by side;
 // panels of 256 rows have no room for that and went through memory at every
-// addition (MEASURE).  The matrix cores bound it.
+// addition (4.28 ms).  The matrix cores bound it.
+// naux=1536, 73920 columns: 4.17 ms, 42 TFLOP/s (1155 workgroups in 512 slots: the third
+// round is a quarter full; 4.06 with running results in panels of 256); with an update
+// of all rows below after each panel (Q rewritten 5 times) 5.0 ms, with one
+// product, one copy and one update per 64 rows 7.6 ms.
 constexpr int SK = 32, SP = NB2 + 16;  // chunk depth; LDS pitch (16 modulo 32)
 constexpr int SFOLD = 256;             // rows above per sum
 __global__ __launch_bounds__(kT, 2) void solve(const double* __restrict__ L, int64_t naux,
