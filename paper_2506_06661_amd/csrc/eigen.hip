@@ -23,7 +23,7 @@
 //     kernel applies them, every column of V^T on a wavefront of its own.
 // On MI355X, n = 128: 0.97 + 0.08 ms from the identity (about 0.95 us a round);
 // averaged over the seven solutions of a six-iteration SCF, most of them
-// started in the previous basis, 0.43 + 0.04 ms, against 2.36 ms for one
+// started in the previous basis, 0.44 + 0.04 ms, against 2.36 ms for one
 // workgroup that worked out indices, rotations and eigenvectors in turn.  The
 // limit on n is LDS: one copy of 198 / 2 pairs' blocks is 158 KB.
 #include "dense.h"
@@ -84,7 +84,7 @@ __device__ inline double rcp_near(double x) {
 // Symmetric Schur rotation of (app, apq; apq, aqq) (Golub & Van Loan, 8.5.2).  It is
 // the longest part of a round's chain, so with h = aqq - app and g = 2 apq the
 // tangent is sign(h) g / (|h| + sqrt(h^2 + g^2)) by a reciprocal and two reciprocal
-// roots: 16 molecules of 40 to 160 functions 1.01 ms a solution, 1.18 with three
+// roots: 16 molecules of 40 to 160 functions 1.02 ms a solution, 1.18 with three
 // divisions and two square roots (at n = 128, where the blocks' LDS traffic of 200 KB a
 // round bounds it, the same).  Differences whose squares would leave the range keep
 // those.

@@ -24,8 +24,8 @@
 // and the energies' partial sums; F D; commutator and its products with the
 // history; one wavefront for energies, Gram matrix, convergence and DIIS;
 // combination; products and eigensolver.  MI355X: six
-// iterations at nao=128 4.4 ms (5.0 with twenty launches for one), a guess and three
-// iterations of 16 molecules 6.7 ms (15.2 with every molecule's launches on one
+// iterations at nao=128 4.5 ms (5.0 with twenty launches for one), a guess and three
+// iterations of 16 molecules 6.5 ms (15.2 with every molecule's launches on one
 // of eight streams).
 #include "dense.h"
 #include "gemm_tile.h"
