@@ -1235,14 +1235,15 @@ constexpr int kNumG16Tiles = sizeof(kG16Tiles) / sizeof(kG16Tiles[0]);
 inline int pick_g16_tile_16(int64_t ncp);
 
 // Default: the 416-column g1_w tile when it pads the orbital columns by at
-// most 10% more than the best of the other tiles (at nao=2048, naux=8192,
-// nocc=400 on MI355X it took 35.7-36.2 ms against 37.0-37.3 for the
-// 208-column direct tile); else that other tile.
+// most 30% more than the best of the other tiles; else that other tile.  GEMM1 with
+// BF16 B, ms, g1_w and the other (padded columns in brackets): nao=2048, naux=1024: 400
+// (416, 416) 3.71, 4.65; 736 (832, 768) 7.23, 8.51; 560 (832, 624) 6.76, 6.48; 480 (832,
+// 512) 7.05, 6.13; 240 (416, 256) 3.36, 3.16.  naux=512: 640 (832, 640) 3.40, 3.60; 1024
+// (1248, 1024) 5.36, 5.92; 1400 (1664, 1408) 6.96, 8.52; 1760 (2080, 1792) 9.21, 10.9.
 inline int pick_g16_tile(int64_t ncp) {
     const int other = pick_g16_tile_16(ncp);
     const int64_t wo = kG16Tiles[other].cols;
-    const double pad_other = (double)(cdiv(ncp, wo) * wo), pad_w = (double)(cdiv(ncp, 416) * 416);
-    return pad_w <= 1.1 * pad_other ? 7 : other;
+    return 10 * cdiv(ncp, 416) * 416 <= 13 * cdiv(ncp, wo) * wo ? 7 : other;
 }
 
 // The choice among the 16 x 16 x 32 tiles 0..6.
